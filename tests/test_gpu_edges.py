@@ -1,0 +1,29 @@
+"""Kernels at the sizes where they can go wrong: edges of tiles, remainders, the smallest and largest of a
+range, each against float64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21276_amd import binding as Bd
+from paper_2507_21276_amd import synth_inputs as S
+from parity_util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+DT = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def q(x, name):
+    """Values exactly representable in the storage type, as float64."""
+    return torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(DT[name]).to(torch.float64).numpy()
+
+
+@pytest.mark.parametrize("name", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("T,N", [(1, 8), (63, 264), (64, 256), (65, 248), (1000, 24), (130, 7)])
+def test_colsum_edges(name, T, N):
+    """Row chunks of 64, column groups of 256, widths that are not multiples of eight (one column per thread).
+    An element passes through fewer than 40 fp32 additions of partial sums below 6 sqrt(T): 1e-5 of the RMS."""
+    x = q(S.normal(6, "x", (T, N)), name)
+    for acc in (False, True):
+        out = torch.full((N,), 3.0, dtype=torch.float32, device="cuda")
+        Bd.lsk_colsum(dev(x, DT[name]), out, accumulate=acc)
+        assert_close(host(out), x.sum(axis=0) + (3.0 if acc else 0.0), 2e-5, f"colsum {T}x{N}")
