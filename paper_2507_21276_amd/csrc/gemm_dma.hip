@@ -107,9 +107,10 @@ __device__ __forceinline__ typename Mf<T>::V8 frag_value(const Frag<T, KMAJOR>& 
 // MODE 3: as 0 without bias, and the half-split rotary embedding (head_dim 128) applied to the
 //         columns below rope_cols: a wavefront's 128 columns are one head, so the pair
 //         (c, c + 64) sits in accumulator tiles j and j + 2 of the same lane
-template <class T, int BM, int BN, bool AK, bool BK, int MODE>
+template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   typedef typename Mf<T>::V8 V8;
+  static_assert(!KTAIL || (!AK && !BK), "only a k-strided operand has a row per k to clear");
   constexpr int TM = BM, TN = BN;
   constexpr int WM = BM / 2, WN = BN / 2;       // wavefront tile
   constexpr int TI = WM / 32, TJ = WN / 32;     // 32x32 MFMA tiles per wavefront
@@ -151,13 +152,30 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   // gridDim.y > 1: split-K, this workgroup contracts over its share of the k tiles
-  const int nk_all = g.K / TK;
+  const int nk_all = KTAIL ? (g.K + TK - 1) / TK : g.K / TK;
   const int kt0 = (int)((long)blockIdx.y * nk_all / gridDim.y);
   const int nk = (int)((long)(blockIdx.y + 1) * nk_all / gridDim.y) - kt0;
   a_base += kt0 * a_step;
   b_base += kt0 * b_step;
-  issue_tile<BM>(a_base, a_off, smem, wave);
-  issue_tile<BN>(b_base, b_off, smem + A_BYTES, wave);
+  // A contraction length that is not a multiple of TK (weight gradients: any number of tokens): the last tile
+  // starts `shift` rows early, so that every load is in bounds, and the rows it shares with the tile before it
+  // are cleared in LDS, by the lanes that loaded them, before the barrier that publishes the tile.
+  const int shift = KTAIL ? nk_all * TK - g.K : 0;
+  const int t_last = nk_all - 1 - kt0;   // index of the last tile in this workgroup's count
+  auto tile_of = [&](const char* base, long step, int t) {
+    return base + t * step - (KTAIL && t == t_last ? shift * (step / TK) : 0);
+  };
+  auto clear_shared_rows = [&](char* ta, char* tb) {
+    constexpr int NA = BM / 32, NB = BN / 32, KA = 512 / BM, KB = 512 / BN;   // wave loads, k rows per wave load
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+      if ((wave * NA + j) * KA + lane / (BM / 8) < shift)
+        *(f32x4_a*)(ta + (wave * NA + j) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      if ((wave * NB + j) * KB + lane / (BN / 8) < shift)
+        *(f32x4_a*)(tb + (wave * NB + j) * 1024 + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
 
   // Software pipeline of one k tile (4 sub-steps of 16 k): while the MFMAs of a sub-step run, the
   // fragments of the next one are read from LDS, and during LDKS sub-steps direct-to-LDS loads are
@@ -174,16 +192,24 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   constexpr int LPK = NLD / LDKS;        // loads per sub-step
   static_assert(NLD % LDKS == 0, "loads per sub-step");
   constexpr GapPlan<NM, NF, LPK> plan{};
-  if (LD_FIRST > 0) {
-    // what sub-steps LD_FIRST .. 3 of the tile before the first would have issued
-    const int t1 = nk > 1 ? 1 : 0;
+  // tiles 0 .. ST - 2, and what sub-steps LD_FIRST .. 3 of the tile before the first would have issued of the next
 #pragma unroll
-    for (int l = 0; l < (4 - LD_FIRST) * NLD / LDKS; ++l)
-      issue_one<BM, BN>(l, a_base + t1 * a_step, a_off, b_base + t1 * b_step, b_off, smem + BUF_BYTES,
-                        smem + BUF_BYTES + A_BYTES, wave);
+  for (int t = 0; t < ST - 1; ++t) {
+    const int tc = min(t, nk - 1);
+    issue_tile<BM>(tile_of(a_base, a_step, tc), a_off, smem + t * BUF_BYTES, wave);
+    issue_tile<BN>(tile_of(b_base, b_step, tc), b_off, smem + t * BUF_BYTES + A_BYTES, wave);
   }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+  constexpr int NFIRST = (4 - LD_FIRST) * NLD / LDKS;
+  {
+    const int tc = min(ST - 1, nk - 1);
+#pragma unroll
+    for (int l = 0; l < NFIRST; ++l)
+      issue_one<BM, BN>(l, tile_of(a_base, a_step, tc), a_off, tile_of(b_base, b_step, tc), b_off,
+                        smem + (ST - 1) * BUF_BYTES, smem + (ST - 1) * BUF_BYTES + A_BYTES, wave);
+  }
+  wait_loads<(ST - 2) * NLD + NFIRST>();   // tile 0 has landed
+  if (KTAIL && shift && t_last == 0) clear_shared_rows(smem, smem + A_BYTES);
+  wait_lds_and_barrier();
   Frag<T, AK> fa[2][TI];
   Frag<T, BK> fb[2][TJ];
 #pragma unroll
@@ -191,26 +217,31 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
 #pragma unroll
   for (int j = 0; j < TJ; ++j) read_frag<T, BK, BN>(fb[0][j], smem + A_BYTES, wn + j * 32, 0, lane);
 
+  int cur = 0;   // buffer of tile kt
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const char* la = smem + cur * BUF_BYTES;
-    const char* lb = la + A_BYTES;
-    char* na = smem + (cur ^ 1) * BUF_BYTES;
+    const int nxt = cur + 1 == ST ? 0 : cur + 1, prv = cur == 0 ? ST - 1 : cur - 1;
+    char* la = smem + cur * BUF_BYTES;
+    char* lb = la + A_BYTES;
+    char* na = smem + nxt * BUF_BYTES;   // the next tile's
     char* nb = na + A_BYTES;
+    char* pa = smem + prv * BUF_BYTES;   // the one this tile's first sub-steps fill up (ST = 2: the next tile's)
+    char* pb = pa + A_BYTES;
+    cur = nxt;
     // tiles after the last are the last again: fetched, never multiplied
-    const int t1 = min(kt + 1, nk - 1), t2 = min(kt + 2, nk - 1);
-    const char* ga1 = a_base + t1 * a_step;
-    const char* gb1 = b_base + t1 * b_step;
-    const char* ga2 = a_base + t2 * a_step;
-    const char* gb2 = b_base + t2 * b_step;
+    const int t1 = min(kt + ST - 1, nk - 1), t2 = min(kt + ST, nk - 1);
+    const char* ga1 = tile_of(a_base, a_step, t1);
+    const char* gb1 = tile_of(b_base, b_step, t1);
+    const char* ga2 = tile_of(a_base, a_step, t2);
+    const char* gb2 = tile_of(b_base, b_step, t2);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int c = ks & 1;
       wait_frags<T, AK, TI>(fa[c]);
       wait_frags<T, BK, TJ>(fb[c]);
       if (ks == 3) {
-        __builtin_amdgcn_s_waitcnt(0);   // this wavefront's share of the next tile has landed
-        __syncthreads();
+        wait_loads<(ST - 2) * NLD>();    // this wavefront's share of the next tile has landed
+        if (KTAIL && shift && kt + 1 == t_last) clear_shared_rows(na, nb);
+        wait_lds_and_barrier();
       }
       V8 va[TI], vb[TJ];
 #pragma unroll
@@ -241,8 +272,8 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
 #pragma unroll
           for (int l = 0; l < LPK; ++l) {
             if (plan.load_gap[l] != m) continue;
-            issue_one<BM, BN>(ph * LPK + l, ahead ? ga2 : ga1, a_off, ahead ? gb2 : gb1, b_off, ahead ? (char*)la : na,
-                              ahead ? (char*)lb : nb, wave);
+            issue_one<BM, BN>(ph * LPK + l, ahead ? ga2 : ga1, a_off, ahead ? gb2 : gb1, b_off, ahead ? la : pa,
+                              ahead ? lb : pb, wave);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -427,20 +458,36 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   }
 }
 
-template <class T, int BM, int BN, bool AK, bool BK, int MODE>
-ls_status launch(DmaArgs g, hipStream_t st, int splits = 1) {
+template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
+ls_status launch_st(DmaArgs g, hipStream_t st, int splits) {
   static bool attr_set = false;
-  const int lds = 2 * (BM + BN) * 128;
+  const int lds = ST * (BM + BN) * 128;
   if (!attr_set) {
-    LS_CHECK_HIP(hipFuncSetAttribute((const void*)gemm_dma_kernel<T, BM, BN, AK, BK, MODE>,
+    LS_CHECK_HIP(hipFuncSetAttribute((const void*)gemm_dma_kernel<T, BM, BN, AK, BK, MODE, ST, KTAIL>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + BN - 1) / BN;
-  gemm_dma_kernel<T, BM, BN, AK, BK, MODE><<<dim3(g.tiles_m * g.tiles_n, splits), 256, lds, st>>>(g);
+  gemm_dma_kernel<T, BM, BN, AK, BK, MODE, ST, KTAIL><<<dim3(g.tiles_m * g.tiles_n, splits), 256, lds, st>>>(g);
   LS_CHECK_LAUNCH();
   return LS_OK;
+}
+
+template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST>
+ls_status launch_tail(const DmaArgs& g, hipStream_t st, int splits) {
+  if constexpr (!AK && !BK)
+    if (g.K % TK != 0) return launch_st<T, BM, BN, AK, BK, MODE, ST, true>(g, st, splits);
+  return launch_st<T, BM, BN, AK, BK, MODE, ST, false>(g, st, splits);
+}
+
+template <class T, int BM, int BN, bool AK, bool BK, int MODE>
+ls_status launch(const DmaArgs& g, hipStream_t st, int splits = 1) {
+  if constexpr (BM == 128 && BN == 128) {
+    const long wgs = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * splits;
+    if (wgs <= 256) return launch_tail<T, BM, BN, AK, BK, MODE, 4>(g, st, splits);
+  }
+  return launch_tail<T, BM, BN, AK, BK, MODE, 2>(g, st, splits);
 }
 
 // the combinations a decoder block uses: forward (k-major x k-major, 16-bit or
@@ -639,7 +686,8 @@ ls_status gemm_dma_try(int op_dtype, int M, int N, int K, const void* A, long ld
                        const void* bias, int bias_dtype, const float* resid, long ldr, int accumulate,
                        const float* alpha, const int32_t* rope_pos, const float* rope_table, int rope_cols,
                        hipStream_t st) {
-  if (K % TK != 0 || M < 64 || N < 64) return LS_ESTATE;
+  if (M < 64 || N < 64) return LS_ESTATE;
+  if (a_kmajor || b_kmajor ? K % TK != 0 : K < TK) return LS_ESTATE;
   // the epilogue stores 16-byte pieces of rows
   const int per16 = c_dtype == LS_F32 ? 4 : 8;
   if (N % per16 != 0 || ldc % per16 != 0 || (uintptr_t)C % 16 != 0) return LS_ESTATE;

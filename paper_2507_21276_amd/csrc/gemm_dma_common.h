@@ -69,6 +69,15 @@ __device__ __forceinline__ void dma_load(const char* base, uint32_t off, const c
                : "memory", "m0");
 }
 
+// at most N of this wavefront's loads still in flight (loads complete in order)
+template <int N> __device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+// workgroup barrier behind this wavefront's LDS accesses.  Issued from assembly: __syncthreads may also wait for
+// every global load in flight, which the ring of more than two buffers must not do.
+__device__ __forceinline__ void wait_lds_and_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
+
 template <int ROWS>
 __device__ __forceinline__ void issue_tile(const char* tile_base, const uint32_t (&off)[ROWS / 32], char* lds_tile,
                                            int wave) {

@@ -27,3 +27,18 @@ def test_colsum_edges(name, T, N):
         out = torch.full((N,), 3.0, dtype=torch.float32, device="cuda")
         Bd.lsk_colsum(dev(x, DT[name]), out, accumulate=acc)
         assert_close(host(out), x.sum(axis=0) + (3.0 if acc else 0.0), 2e-5, f"colsum {T}x{N}")
+
+
+@pytest.mark.parametrize("name", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,T", [(256, 264, 64), (264, 256, 65), (768, 768, 127), (520, 392, 130), (1000, 2304, 191), (256, 256, 1001),
+                                   (4104, 2568, 64), (4104, 2568, 101), (4104, 2568, 192)])
+def test_weight_gradient_of_any_token_count(name, M, N, T):
+    """dW = dY^T X over T tokens: one k tile, whole tiles, a last tile of 1 .. 63 rows, fewer tiles than the ring
+    holds, both tile sizes.  Operands are exact, sums fp32: T products of RMS 1 with T 2^-24 relative each."""
+    dY, X = q(S.normal(2, "dY", (T, M)), name), q(S.normal(2, "X", (T, N)), name)
+    dYd, Xd = dev(dY, DT[name]), dev(X, DT[name])
+    ref = (torch.from_numpy(dY).cuda().t().contiguous() @ torch.from_numpy(X).cuda()).cpu().numpy()
+    dW = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+    for acc in (False, True):
+        Bd.lsk_gemm(dYd, Xd, dW, M=M, N=N, K=T, a_kmajor=False, b_kmajor=False, lda=M, ldb=N, accumulate=acc)
+        assert_close(host(dW), (1 + acc) * ref, 1e-5, f"dW T={T} acc={acc}")
