@@ -601,7 +601,7 @@ ls_status gemm_dma_splitk_try(int op_dtype, int M, int N, int K, const void* A, 
 // caller that sums them together with its next step.  LS_ESTATE when the shape does not call for a split.
 ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
                                    float* scratch, size_t scratch_floats, int* splits_out, hipStream_t st) {
-  if (!scratch || K % TK != 0 || M < 256 || N < 64 || N % 4 != 0 || (uintptr_t)scratch % 16 != 0) return LS_ESTATE;
+  if (!scratch || K % TK != 0 || M <= 128 || N < 64 || N % 4 != 0 || (uintptr_t)scratch % 16 != 0) return LS_ESTATE;
   if (lda % 8 != 0 || ldb % 8 != 0 || (uintptr_t)A % 16 != 0 || (uintptr_t)B % 16 != 0) return LS_ESTATE;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   const int nk = K / TK;

@@ -42,3 +42,25 @@ def test_weight_gradient_of_any_token_count(name, M, N, T):
     for acc in (False, True):
         Bd.lsk_gemm(dYd, Xd, dW, M=M, N=N, K=T, a_kmajor=False, b_kmajor=False, lda=M, ldb=N, accumulate=acc)
         assert_close(host(dW), (1 + acc) * ref, 1e-5, f"dW T={T} acc={acc}")
+
+
+@pytest.mark.parametrize("name", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (129, 512, 2048), (200, 264, 128), (255, 4096, 4096), (255, 12800, 64)])
+def test_products_of_64_to_255_rows(name, M, N, K):
+    """One tile and two of 128 rows, split along k (>= 32 k tiles, few output tiles) and not, with and without the
+    workspace, and the input-gradient layout.  Exact operands, fp32 sums: K 2^-24 of the RMS at the worst."""
+    A, W = q(S.normal(3, "A", (M, K)), name), q(S.normal(3, "W", (N, K), 0.05), name)
+    Ad, Wd = dev(A, DT[name]), dev(W, DT[name])
+    A64, W64 = torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda()
+    ref = (A64 @ W64.t().contiguous()).cpu().numpy()
+    tol = max(1e-5, K * 2.0 ** -24)
+    out = torch.empty(M, N, dtype=torch.float32, device="cuda")
+    R = S.normal(3, "R", (M, N))
+    ws = torch.empty(8 * M * N, dtype=torch.float32, device="cuda")
+    Bd.lsk_gemm(Ad, Wd, out, M=M, N=N, K=K, resid=dev(R, torch.float32))
+    assert_close(host(out), ref + R, tol, "forward")
+    Bd.lsk_gemm_ws(Ad, Wd, out, ws, resid=dev(R, torch.float32))
+    assert_close(host(out), ref + R, tol, "forward with a workspace")
+    Bk = q(S.normal(3, "Bk", (K, N), 0.05), name)
+    Bd.lsk_gemm(Ad, dev(Bk, DT[name]), out, M=M, N=N, K=K, a_kmajor=True, b_kmajor=False, lda=K, ldb=N)
+    assert_close(host(out), (A64 @ torch.from_numpy(Bk).cuda()).cpu().numpy(), tol, "input gradient")
