@@ -219,43 +219,67 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 }
 
 // ---- plain fp32 FMA path (fp32 stage mode; any strides, any sizes) ---------------
-// 64x64 tile, 256 threads, 4x4 outputs per thread, BK = 16.
+// S x S tiles, 256 threads, (S / 16)^2 outputs per thread, BK = 2048 / S.  A thread issues all of its loads of a k tile
+// at once, a tile ahead of the arithmetic: the launches of a short fp32 task have a few workgroups, and theirs is a
+// chain of load latencies (64 x 64 tiles with BK = 16 and no loads ahead took 20 - 36 us a launch; a training task of
+// 2 x 64 tokens on the two-layer stage of width 128 went from 1406 to 583 us).
+// Every output is the same ascending sum over k for both tile sizes.
+template <int S>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  __shared__ float sa[16][64 + 1], sb[16][64 + 1];
+  constexpr int BKF = 2048 / S, R = S / 16, NL = S * BKF / 256;
+  __shared__ float sa[BKF][S + 1], sb[BKF][S + 1];
   const float* A = (const float*)g.A;
   const float* B = (const float*)g.B;
-  const int tiles_m = (g.M + 63) / 64;
-  const int m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64;
+  const int tiles_m = (g.M + S - 1) / S;
+  const int m0 = (blockIdx.x % tiles_m) * S, n0 = (blockIdx.x / tiles_m) * S;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const long a_rs = g.a_kmajor ? g.lda : 1, a_ks = g.a_kmajor ? 1 : g.lda;
-  const long b_rs = g.b_kmajor ? g.ldb : 1, b_ks = g.b_kmajor ? 1 : g.ldb;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
+  float acc[R][R] = {}, ra[NL], rb[NL];
+  // element i of a tile: (row, k) with the contiguous dimension fastest
+  auto at = [](int i, int kmajor, int& r, int& k) {
+    if (kmajor) { r = i / BKF; k = i % BKF; } else { r = i % S; k = i / S; }
+  };
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
       int r, k;
-      if (g.a_kmajor) { r = i >> 4; k = i & 15; } else { r = i & 63; k = i >> 6; }
-      sa[k][r] = (m0 + r < g.M && k0 + k < g.K) ? A[(long)(m0 + r) * a_rs + (long)(k0 + k) * a_ks] : 0.f;
-      if (g.b_kmajor) { r = i >> 4; k = i & 15; } else { r = i & 63; k = i >> 6; }
-      sb[k][r] = (n0 + r < g.N && k0 + k < g.K) ? B[(long)(n0 + r) * b_rs + (long)(k0 + k) * b_ks] : 0.f;
+      at(threadIdx.x + u * 256, g.a_kmajor, r, k);
+      bool ok = m0 + r < g.M && k0 + k < g.K;
+      ra[u] = ok ? A[g.a_kmajor ? (long)(m0 + r) * g.lda + k0 + k : (long)(k0 + k) * g.lda + m0 + r] : 0.f;
+      at(threadIdx.x + u * 256, g.b_kmajor, r, k);
+      ok = n0 + r < g.N && k0 + k < g.K;
+      rb[u] = ok ? B[g.b_kmajor ? (long)(n0 + r) * g.ldb + k0 + k : (long)(k0 + k) * g.ldb + n0 + r] : 0.f;
+    }
+  };
+  fetch(0);
+  for (int k0 = 0; k0 < g.K; k0 += BKF) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      int r, k;
+      at(threadIdx.x + u * 256, g.a_kmajor, r, k);
+      sa[k][r] = ra[u];
+      at(threadIdx.x + u * 256, g.b_kmajor, r, k);
+      sb[k][r] = rb[u];
     }
     __syncthreads();
+    if (k0 + BKF < g.K) fetch(k0 + BKF);
+#pragma unroll 16
+    for (int k = 0; k < BKF; ++k) {
+      float av[R], bv[R];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float av[4], bv[4];
+      for (int i = 0; i < R; ++i) { av[i] = sa[k][ty * R + i]; bv[i] = sb[k][tx * R + i]; }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = sa[k][ty * 4 + i]; bv[i] = sb[k][tx * 4 + i]; }
+      for (int i = 0; i < R; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+        for (int j = 0; j < R; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
     }
     __syncthreads();
   }
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
+  const float alpha = g.alpha ? *g.alpha : 1.f;
+  for (int i = 0; i < R; ++i)
+    for (int j = 0; j < R; ++j) {
+      const int m = m0 + ty * R + i, n = n0 + tx * R + j;
       if (m >= g.M || n >= g.N) continue;
-      float v = acc[i][j] * (g.alpha ? *g.alpha : 1.f);
+      float v = acc[i][j] * alpha;
       if (g.bias) v += load_as_f(g.bias, n, g.bias_dtype);
       if (g.resid) v += g.resid[(long)m * g.ldr + n];
       float* c = (float*)g.C;
@@ -309,8 +333,10 @@ extern "C" ls_status lsk_gemm_scaled(int op_dtype, int M, int N, int K, const vo
   hipStream_t st = (hipStream_t)stream;
   if (op_dtype == LS_F32) {
     LS_REQUIRE(c_dtype == LS_F32, "gemm: fp32 operands need an fp32 output");
+    // 32 x 32 tiles while 64 x 64 ones would leave compute units without one
     const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    gemm_f32_kernel<<<dim3(tiles), dim3(256), 0, st>>>(g);
+    if (tiles < 256) gemm_f32_kernel<32><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
+    else gemm_f32_kernel<64><<<dim3(tiles), dim3(256), 0, st>>>(g);
     LS_CHECK_LAUNCH();
     return LS_OK;
   }

@@ -64,3 +64,17 @@ def test_products_of_64_to_255_rows(name, M, N, K):
     Bk = q(S.normal(3, "Bk", (K, N), 0.05), name)
     Bd.lsk_gemm(Ad, dev(Bk, DT[name]), out, M=M, N=N, K=K, a_kmajor=True, b_kmajor=False, lda=K, ldb=N)
     assert_close(host(out), (A64 @ torch.from_numpy(Bk).cuda()).cpu().numpy(), tol, "input gradient")
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 65), (128, 128, 128), (64, 256, 64), (130, 70, 129), (1030, 1025, 40)])
+def test_fp32_products_of_both_tile_sizes(M, N, K):
+    """32 x 32 and 64 x 64 tiles, k tiles of 64 and 32, all four layouts, remainders in each dimension.  Sums of K
+    products in order: K 2^-24 of the largest partial sum at the worst, a few 1e-6 of the RMS here."""
+    A, W = S.normal(5, "A", (M, K)), S.normal(5, "W", (N, K))
+    ref = A.astype(np.float32).astype(np.float64) @ W.astype(np.float32).astype(np.float64).T
+    for ak in (True, False):
+        for bk in (True, False):
+            out = torch.full((M, N), 2.0, dtype=torch.float32, device="cuda")
+            Bd.lsk_gemm(dev(A if ak else A.T, torch.float32), dev(W if bk else W.T, torch.float32), out, M=M, N=N, K=K,
+                        a_kmajor=ak, b_kmajor=bk, lda=K if ak else M, ldb=K if bk else N, accumulate=True)
+            assert_close(host(out), ref + 2.0, max(4e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}", atol=1e-6)
