@@ -78,3 +78,26 @@ def test_fp32_products_of_both_tile_sizes(M, N, K):
             Bd.lsk_gemm(dev(A if ak else A.T, torch.float32), dev(W if bk else W.T, torch.float32), out, M=M, N=N, K=K,
                         a_kmajor=ak, b_kmajor=bk, lda=K if ak else M, ldb=K if bk else N, accumulate=True)
             assert_close(host(out), ref + 2.0, max(4e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}", atol=1e-6)
+
+
+@pytest.mark.parametrize("name", ["bf16", "f16"])
+@pytest.mark.parametrize("kind", [Bd.LS_ACT_GELU_TANH, Bd.LS_ACT_GELU_ERF])
+@pytest.mark.parametrize("n", [8, 1000, 1003])
+def test_gelu_of_16_bit_operands(name, kind, n):
+    """Eight units per thread and one (n not a multiple of eight, an unaligned start), the tails and zero included.
+    fp32 inside, so every value is off by half an ulp of the storage type and 1e-5 of itself (the erf form cancels in
+    its tail: 1e-6 absolute), subnormals aside."""
+    u = q(np.concatenate([S.normal(9, "u", (n,)) * 3.0])[:n], name)
+    u[:8] = q(np.array([0.0, -0.0, 12.0, -12.0, -6.0, -9.0, 300.0, -300.0]), name)
+    dg = q(S.normal(9, "dg", (n,)), name)
+    x = torch.from_numpy(u).requires_grad_(True)
+    y = torch.nn.functional.gelu(x, approximate="tanh" if kind == Bd.LS_ACT_GELU_TANH else "none")
+    y.backward(torch.from_numpy(dg))
+    half_ulp = 2.0 ** (-9 if name == "bf16" else -12) * 2
+    for skip in (0, 1):
+        buf = lambda v: torch.cat([torch.zeros(skip, dtype=DT[name], device="cuda"), dev(v, DT[name])])[skip:]  # noqa: E731
+        ud, gd, out, dout = buf(u), buf(dg), buf(u), buf(u)
+        Bd.lsk_gelu_fwd(ud, out, kind)
+        Bd.lsk_gelu_bwd(gd, ud, dout, kind)
+        for got, ref in ((host(out), y.detach().numpy()), (host(dout), x.grad.numpy())):
+            assert (np.abs(got - ref) <= (half_ulp + 1e-5) * np.abs(ref) + 2e-6).all()
