@@ -131,6 +131,12 @@ ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, cons
 }
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim);
 ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
+size_t gemm_dma_wgrad_scratch_floats(long M, long N);
+ls_status gemm_dma_wgrad_splitk(int, int, int, int, const void*, long, const void*, long, float*, long, int, const float*,
+                                float*, size_t, hipStream_t);
+ls_status gemm_dma_dgrad_splitk(int, int, int, int, const void*, long, const void*, long, void*, long, float*, size_t,
+                                hipStream_t);
+bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
                                    hipStream_t);
 extern "C" {
 ls_status lsk_finish_resid_norm(const float*, int, int, int, const void*, const float*, float*, int, const void*,
@@ -525,6 +531,29 @@ ls_status check_kv(const ls_stage* s, const ls_kv* kv, int B, const int32_t* new
       LS_REQUIRE(kv->ctx_len_host[b] >= 0, "request %d has negative context length", b);
       LS_REQUIRE((tot + c.page_size - 1) / c.page_size <= kv->max_pages_per_req,
                  "request %d needs %ld tokens of KV but the block table holds %d pages of %d", b, tot,
+// Serving calls of one to four rows: matrix-vector kernels that take the steps around each projection with them
+ls_status block_forward_gemv(const ls_stage* s, int l, int T, const FwdBufs& f, const int32_t* pos, const int32_t* req,
+                             int B, const ls_kv* kv, int max_ctx, const int32_t* chunk_start, int n_decode,
+                             hipStream_t st) {
+  const ls_config& c = s->cfg;
+  const LayerOff& o = s->off[l];
+  const int d = c.d_model, F = c.d_ff, mt = c.mma_dtype;
+  const bool gpt = c.block == LS_BLOCK_GPT_PRELN;
+  const int nk = gpt ? 0 : 1;
+  const size_t slab = (size_t)kv->n_pages * c.n_heads * c.page_size * c.head_dim * osz(s);
+  void* kp = (char*)kv->k_pool + (size_t)l * slab;
+  void* vp = (char*)kv->v_pool + (size_t)l * slab;
+  LS_TRY(lsk_gemv_norm_qkv(mt, T, c.n_heads, c.head_dim, f.x, nk, pptr(s, o.n1_g), gpt ? pptr(s, o.n1_b) : nullptr,
+                           c.norm_eps, wptr(s, o.w_qkv), gpt ? pptr(s, o.b_qkv) : nullptr, pos, req,
+                           gpt ? nullptr : s->rope_table, f.qkv, kp, vp, kv->block_table, kv->max_pages_per_req,
+                           c.page_size, st));
+  LS_TRY(serve_attention(s, T, f, pos, req, B, kv, kp, vp, max_ctx, chunk_start, n_decode, st));
+  LS_TRY(lsk_gemv_resid(mt, T, d, d, f.o, wptr(s, o.w_o), gpt ? pptr(s, o.b_o) : nullptr, f.x, f.x1, st));
+  LS_TRY(lsk_gemv_norm_act(mt, T, d, F, c.act, f.x1, nk, pptr(s, o.n2_g), gpt ? pptr(s, o.n2_b) : nullptr, c.norm_eps,
+                           wptr(s, o.w_up), gpt ? pptr(s, o.b_up) : nullptr, f.act, st));
+  return lsk_gemv_resid(mt, T, d, F, f.act, wptr(s, o.w_dn), gpt ? pptr(s, o.b_dn) : nullptr, f.x1, f.y, st);
+}
+
                  kv->max_pages_per_req, c.page_size);
       LS_REQUIRE(c.block != LS_BLOCK_LLAMA || tot <= c.max_pos, "request %d reaches position %ld >= max_pos %d",
                  b, tot, c.max_pos);
@@ -545,7 +574,8 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
   for (int l = 0; l < c.n_layers; ++l) {
     FwdBufs f{w.xa, w.xb, w.xa, nullptr, nullptr, nullptr, nullptr, nullptr,
               w.h, w.qkv, w.o, w.h, w.up, w.act, w.scratch};
-    if (fused) LS_TRY(block_forward_fused(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, st));
+    if (gemv) LS_TRY(block_forward_gemv(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, st));
+    else if (fused) LS_TRY(block_forward_fused(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, st));
     else LS_TRY(block_forward(s, l, T, f, w.pos, w.req, B, 0, kv, max_ctx, chunk_start, n_decode, st, &h1_ready));
   }
   return lsk_convert(w.xa, LS_F32, Y, c.io_dtype, (size_t)T * c.d_model, st);
@@ -553,6 +583,7 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
 
 }  // namespace
 
+  const bool gemv = decode_gemv_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
 extern "C" {
 
 ls_status ls_create(const ls_config* cfg, ls_stage** out) {

@@ -9,6 +9,7 @@ import torch
 from oracle import stage_oracle as O
 from paper_2507_21276_amd import binding as Bd
 from paper_2507_21276_amd import synth_inputs as S
+from test_gpu_stage import make_stage
 from parity_util import (TOL, assert_close, dev, gather_rows_from_pool, host, out_rounding_bound,
                          pool_from_oracle_cache, rel_err)
 
@@ -195,4 +196,40 @@ def test_decode_steps_of_a_stage_whose_widths_take_the_fused_path(which, mma):
         Kg = gather_rows_from_pool(kph, table, b, lo, hi)
         for l in range(nL):
             assert rel_err(Kg[l], cache[l][b][0][lo:hi]) <= tol
+    st.close()
+
+
+@pytest.mark.parametrize("mma", ["f16", "bf16"])
+@pytest.mark.parametrize("rows", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("shape", ["gpt_narrow", "gpt_odd", "llama", "llama_deep", "gpt_wide"])
+def test_decode_of_few_rows(mma, rows, shape):
+    """The matrix-vector kernels (one, two, four rows a pass; three rows leave one unused) and the first batch above
+    them: contractions of a part of a load, of odd numbers of loads, each number of wavefronts sharing one, both
+    blocks, head sizes 32, 64, 128.  Bar: that of the stage tests."""
+    cfg = {"gpt_narrow": S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=2, d_model=96, n_heads=3, head_dim=32, d_ff=200),
+           "gpt_odd": S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=2, d_model=576, n_heads=9, d_ff=1544),
+           "llama": S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=2, d_model=256, n_heads=2, d_ff=704),
+           "llama_deep": S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_model=256, n_heads=2, d_ff=8712),
+           "gpt_wide": S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=1, d_model=2112, n_heads=33, d_ff=256)}[shape]
+    old = [0, 15, 16, 130, 7][:rows]
+    st, flat, _ = make_stage(cfg, mma=mma, io="f32")
+    table, n_pages = S.page_tables(np.array(old), np.ones(rows, np.int64), cfg["page_size"])
+    cache = O.new_cache(cfg, rows)
+    for l in range(cfg["n_layers"]):
+        for b, n in enumerate(old):
+            cache[l][b] = [q(S.normal(11, f"{w}{l}{b}", (n, cfg["n_heads"], cfg["head_dim"])), mma) for w in "KV"]
+    kp, vp = pool_from_oracle_cache(cache, table, n_pages, cfg)
+    kv = Bd.KV(st, n_pages, table, old)
+    kv.k_pool.copy_(dev(kp, DT[mma]).view_as(kv.k_pool))
+    kv.v_pool.copy_(dev(vp, DT[mma]).view_as(kv.v_pool))
+    X = S.make_activations(cfg, "X", (rows, cfg["d_model"]))
+    Y = torch.empty(rows, cfg["d_model"], dtype=torch.float32, device="cuda")
+    st.stage_decode(dev(X, torch.float32), rows, kv, Y, st.new_workspace(rows))
+    ref = O.stage_decode(cfg, flat.astype(np.float64), X.astype(np.float64), cache)
+    assert_close(host(Y), ref, TOL["bf16"], shape)
+    for pool, i in ((kv.k_pool, 0), (kv.v_pool, 1)):
+        got = host(pool).reshape(kp.shape)
+        for b, n in enumerate(old):
+            row = gather_rows_from_pool(got, table, b, n, n + 1)
+            assert_close(row, np.stack([cache[l][b][i][n:n + 1] for l in range(cfg["n_layers"])]), TOL["bf16"], f"row {b}")
     st.close()
