@@ -130,13 +130,8 @@ ls_status lsk_gemm_partials(int, int, int, int, const void*, long, const void*, 
 ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, const void*, void*, void*, void*);
 }
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim);
-ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
-size_t gemm_dma_wgrad_scratch_floats(long M, long N);
-ls_status gemm_dma_wgrad_splitk(int, int, int, int, const void*, long, const void*, long, float*, long, int, const float*,
-                                float*, size_t, hipStream_t);
-ls_status gemm_dma_dgrad_splitk(int, int, int, int, const void*, long, const void*, long, void*, long, float*, size_t,
-                                hipStream_t);
 bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
+ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
                                    hipStream_t);
 extern "C" {
 ls_status lsk_finish_resid_norm(const float*, int, int, int, const void*, const float*, float*, int, const void*,
@@ -518,19 +513,6 @@ ls_status block_forward_fused(const ls_stage* s, int l, int T, const FwdBufs& f,
                                pptr(s, nx.n1_g), gpt ? pptr(s, nx.n1_b) : nullptr, pt, c.norm_eps, f.h1, mt, st);
 }
 
-ls_status check_kv(const ls_stage* s, const ls_kv* kv, int B, const int32_t* new_tokens, int* max_ctx) {
-  const ls_config& c = s->cfg;
-  LS_REQUIRE(kv && kv->k_pool && kv->v_pool && kv->block_table && kv->ctx_len, "kv: null field");
-  LS_REQUIRE(kv->n_pages > 0 && kv->max_pages_per_req > 0, "kv: non-positive page counts");
-  int mc = 0;
-  for (int b = 0; b < B; ++b) {
-    const int nt = new_tokens ? new_tokens[b] : 1;
-    LS_REQUIRE(nt > 0, "request %d has %d new tokens", b, nt);
-    if (kv->ctx_len_host) {
-      const long tot = (long)kv->ctx_len_host[b] + nt;
-      LS_REQUIRE(kv->ctx_len_host[b] >= 0, "request %d has negative context length", b);
-      LS_REQUIRE((tot + c.page_size - 1) / c.page_size <= kv->max_pages_per_req,
-                 "request %d needs %ld tokens of KV but the block table holds %d pages of %d", b, tot,
 // Serving calls of one to four rows: matrix-vector kernels that take the steps around each projection with them
 ls_status block_forward_gemv(const ls_stage* s, int l, int T, const FwdBufs& f, const int32_t* pos, const int32_t* req,
                              int B, const ls_kv* kv, int max_ctx, const int32_t* chunk_start, int n_decode,
@@ -554,6 +536,19 @@ ls_status block_forward_gemv(const ls_stage* s, int l, int T, const FwdBufs& f, 
   return lsk_gemv_resid(mt, T, d, F, f.act, wptr(s, o.w_dn), gpt ? pptr(s, o.b_dn) : nullptr, f.x1, f.y, st);
 }
 
+ls_status check_kv(const ls_stage* s, const ls_kv* kv, int B, const int32_t* new_tokens, int* max_ctx) {
+  const ls_config& c = s->cfg;
+  LS_REQUIRE(kv && kv->k_pool && kv->v_pool && kv->block_table && kv->ctx_len, "kv: null field");
+  LS_REQUIRE(kv->n_pages > 0 && kv->max_pages_per_req > 0, "kv: non-positive page counts");
+  int mc = 0;
+  for (int b = 0; b < B; ++b) {
+    const int nt = new_tokens ? new_tokens[b] : 1;
+    LS_REQUIRE(nt > 0, "request %d has %d new tokens", b, nt);
+    if (kv->ctx_len_host) {
+      const long tot = (long)kv->ctx_len_host[b] + nt;
+      LS_REQUIRE(kv->ctx_len_host[b] >= 0, "request %d has negative context length", b);
+      LS_REQUIRE((tot + c.page_size - 1) / c.page_size <= kv->max_pages_per_req,
+                 "request %d needs %ld tokens of KV but the block table holds %d pages of %d", b, tot,
                  kv->max_pages_per_req, c.page_size);
       LS_REQUIRE(c.block != LS_BLOCK_LLAMA || tot <= c.max_pos, "request %d reaches position %ld >= max_pos %d",
                  b, tot, c.max_pos);
@@ -569,6 +564,7 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
                         const FwdWs& w, const int32_t* chunk_start, int n_decode, hipStream_t st) {
   const ls_config& c = s->cfg;
   LS_TRY(lsk_convert(X, c.io_dtype, w.xa, LS_F32, (size_t)T * c.d_model, st));
+  const bool gemv = decode_gemv_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
   const bool fused = fused_decode_ok(s, T);
   bool h1_ready = false;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -583,7 +579,6 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
 
 }  // namespace
 
-  const bool gemv = decode_gemv_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
 extern "C" {
 
 ls_status ls_create(const ls_config* cfg, ls_stage** out) {

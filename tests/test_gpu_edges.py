@@ -6,7 +6,8 @@ import torch
 
 from paper_2507_21276_amd import binding as Bd
 from paper_2507_21276_amd import synth_inputs as S
-from parity_util import assert_close, dev, host
+from parity_util import TOL, assert_close, dev, host
+from test_gpu_stage import check_train, make_stage, run_train
 
 pytestmark = pytest.mark.gpu
 DT = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
@@ -101,3 +102,19 @@ def test_gelu_of_16_bit_operands(name, kind, n):
         Bd.lsk_gelu_bwd(gd, ud, dout, kind)
         for got, ref in ((host(out), y.detach().numpy()), (host(dout), x.grad.numpy())):
             assert (np.abs(got - ref) <= (half_ulp + 1e-5) * np.abs(ref) + 2e-6).all()
+
+
+@pytest.mark.parametrize("which", ["gpt", "llama"])
+@pytest.mark.parametrize("B,L", [(2, 255), (3, 333), (1, 1024)])
+def test_training_with_gradients_split_along_the_contraction(which, B, L):
+    """Few output tiles and enough k tiles that weight and input gradients are summed from parts: token counts with a
+    last k tile of 1, 39 and 64 rows, gradients overwritten and accumulated.  Bars of the stage tests (f16 operands)."""
+    cfg = (S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=1, d_model=256, n_heads=4, d_ff=1536) if which == "gpt" else
+           S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_model=256, n_heads=2, d_ff=840))
+    check_train(cfg, B, L, "f16", io="f32", tol=TOL["bf16"])
+    st, _, _ = make_stage(cfg, mma="f16", io="f32")
+    X, dY = (S.make_activations(cfg, n, (B, L, cfg["d_model"])) for n in ("X", "dY"))
+    _, _, once = run_train(st, cfg, X, dY, B, L)
+    _, _, twice = run_train(st, cfg, X, dY, B, L, accumulate_twice=True)
+    assert_close(twice, 2 * once, 1e-6, "accumulated gradients")
+    st.close()
