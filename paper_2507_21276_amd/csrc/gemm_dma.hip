@@ -624,6 +624,93 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   return LS_OK;
 }
 
+namespace {
+
+// C = (C +) alpha * sum over the splits, in order
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial, int splits, long MN, int N, float* C,
+                                                           long ldc, int accumulate, const float* alpha_dev) {
+  const long i4 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i4 >= MN) return;
+  float* c = C + i4 / N * ldc + i4 % N;
+  f32x4 v = *(const f32x4*)(partial + i4);
+#pragma unroll 4
+  for (int s = 1; s < splits; ++s) v += *(const f32x4*)(partial + s * MN + i4);
+  v *= alpha_dev ? *alpha_dev : 1.f;
+  *(f32x4*)c = accumulate ? *(const f32x4*)c + v : v;
+}
+
+// Parts into which a product of `tiles` 128 x 128 tiles over nk k tiles is split so that the chip is full once.  A
+// workgroup alone on its compute unit takes 0.65 us per k tile (two share one at 1.4 us: nothing is gained beyond 256
+// workgroups); the sum of the parts is a launch of 4 us and moves MN (parts + 1) floats at about 4 TB/s.
+// Weight gradients over 4096 tokens, one part -> split: 768 x 768 (7 parts) 36 -> 19 us, 2304 x 768 (2) 37 -> 31 us;
+// 3072 x 768 (144 tiles) stays whole (39 us; in three parts, two workgroups a compute unit, 39 us as well).
+int splits_to_fill(long tiles, int nk, long MN) {
+  int best = 1;
+  float best_us = 1e30f;
+  for (int s = 1; s <= 8 && s * tiles <= 256 && nk / s >= 4; ++s) {
+    const float us = (float)((nk + s - 1) / s) * 0.65f + (s > 1 ? 4.f + (float)MN * 4.f * (s + 1) / 4e6f : 0.f);
+    if (us < 0.9f * best_us) { best = s; best_us = us; }
+  }
+  return best;
+}
+
+}  // namespace
+
+// Floats of scratch that the gradient of an M x N weight matrix may use, whatever the token count
+size_t gemm_dma_wgrad_scratch_floats(long M, long N) {
+  const long tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  if (tiles > 128) return 0;
+  const long most = 256 / tiles < 8 ? 256 / tiles : 8;
+  return (size_t)(most * M * N);
+}
+
+// Weight gradient C[M, N] (fp32) = (C +) alpha A^T B over K rows of A [K][M] and B [K][N], split along K into partial
+// products where the output has few tiles.  LS_ESTATE where the launch is better in one piece or not covered.
+ls_status gemm_dma_wgrad_splitk(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
+                                float* C, long ldc, int accumulate, const float* alpha, float* scratch,
+                                size_t scratch_floats, hipStream_t st) {
+  if (!scratch || (uintptr_t)scratch % 16 != 0 || M < 64 || N < 64 || M % 8 != 0 || N % 8 != 0 || K < TK) return LS_ESTATE;
+  if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 4 != 0 || ((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16 != 0) return LS_ESTATE;
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
+  const int splits = splits_to_fill(tiles, (K + TK - 1) / TK, MN);
+  if (splits < 2 || (size_t)(splits * MN) > scratch_floats) return LS_ESTATE;
+  DmaArgs g{M, N, K, A, lda, 0, B, ldb, 0, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
+            nullptr, 0};
+  g.split_stride = MN;
+  if (op_dtype == LS_BF16) LS_TRY((launch<bf16_t, 128, 128, false, false, 2>(g, st, splits)));
+  else if (op_dtype == LS_F16) LS_TRY((launch<f16_t, 128, 128, false, false, 2>(g, st, splits)));
+  else return LS_ESTATE;
+  wgrad_reduce_kernel<<<(unsigned)((MN / 4 + 255) / 256), 256, 0, st>>>(scratch, splits, MN, N, C, ldc, accumulate, alpha);
+  LS_CHECK_LAUNCH();
+  return LS_OK;
+}
+
+// Input gradient C[M, N] (operand type) = A W over K columns of A [M][K] and rows of W [K][N], split along K into
+// partial products where the output has few tiles.  LS_ESTATE where the launch is better in one piece or not covered.
+ls_status gemm_dma_dgrad_splitk(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
+                                void* C, long ldc, float* scratch, size_t scratch_floats, hipStream_t st) {
+  if (!scratch || (uintptr_t)scratch % 16 != 0 || M < 64 || N < 64 || N % 8 != 0 || K % TK != 0) return LS_ESTATE;
+  if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || ((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16 != 0) return LS_ESTATE;
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
+  const int splits = splits_to_fill(tiles, K / TK, MN);
+  if (splits < 2 || (size_t)(splits * MN) > scratch_floats) return LS_ESTATE;
+  DmaArgs g{M, N, K, A, lda, 1, B, ldb, 0, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
+            nullptr, 0};
+  g.split_stride = MN;
+  const unsigned grid = (unsigned)((MN / 4 + 255) / 256);
+  if (op_dtype == LS_BF16) {
+    LS_TRY((launch<bf16_t, 128, 128, true, false, 2>(g, st, splits)));
+    splitk_reduce_kernel<bf16_t><<<grid, 256, 0, st>>>(scratch, splits, MN, N, C, ldc, LS_BF16, nullptr, 0, nullptr, 0);
+  } else if (op_dtype == LS_F16) {
+    LS_TRY((launch<f16_t, 128, 128, true, false, 2>(g, st, splits)));
+    splitk_reduce_kernel<f16_t><<<grid, 256, 0, st>>>(scratch, splits, MN, N, C, ldc, LS_F16, nullptr, 0, nullptr, 0);
+  } else {
+    return LS_ESTATE;
+  }
+  LS_CHECK_LAUNCH();
+  return LS_OK;
+}
+
 // Weight-streaming product for a few rows (decode batches, M <= 128): tiles of 64 x 128 so that
 // three workgroups share a compute unit (128 x 128 and two workgroups above 64 rows), the weights stream through LDS as whole cache lines,
 // and the contraction is split until the chip has about three workgroups per compute unit.

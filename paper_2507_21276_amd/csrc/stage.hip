@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -130,6 +131,11 @@ ls_status lsk_gemm_partials(int, int, int, int, const void*, long, const void*, 
 ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, const void*, void*, void*, void*);
 }
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim);
+size_t gemm_dma_wgrad_scratch_floats(long M, long N);
+ls_status gemm_dma_wgrad_splitk(int, int, int, int, const void*, long, const void*, long, float*, long, int, const float*,
+                                float*, size_t, hipStream_t);
+ls_status gemm_dma_dgrad_splitk(int, int, int, int, const void*, long, const void*, long, void*, long, float*, size_t,
+                                hipStream_t);
 bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
 ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
                                    hipStream_t);
@@ -308,7 +314,8 @@ size_t carve_fwd(const ls_stage* s, void* base, int T, FwdWs* w) {
 // backward scratch
 struct BwdWs {
   int32_t* pos;
-  float *g, *g1, *dvec, *partial, *gscale;
+  float *g, *g1, *dvec, *partial, *gscale, *wsplit;
+  size_t wsplit_floats;
   void *g16, *dact, *dup, *dh, *dqkv, *d_o;
 };
 size_t carve_bwd(const ls_stage* s, void* base, int T, BwdWs* w) {
@@ -332,6 +339,17 @@ size_t carve_bwd(const ls_stage* s, void* base, int T, BwdWs* w) {
   const size_t cf = lsk_colsum_partial_floats(T, (int)widest);
   if (cf > pf) pf = cf;
   v.partial = (float*)b.take(pf * 4);
+  // partial products of the gradients: at most 256 tiles of 64 KB, eight parts of a result
+  v.wsplit_floats = 0;
+  if (c.mma_dtype != LS_F32) {
+    const size_t most = (size_t)8 * T * (d > (size_t)c.d_ff ? d : (size_t)c.d_ff), tiles = (size_t)256 * 128 * 128;
+    v.wsplit_floats = most < tiles ? most : tiles;
+    for (const size_t n : {3 * d, d, (size_t)s->up_cols, (size_t)c.d_ff}) {
+      const size_t f = gemm_dma_wgrad_scratch_floats((long)n, (long)d);
+      if (f > v.wsplit_floats) v.wsplit_floats = f;
+    }
+  }
+  v.wsplit = (float*)b.take(v.wsplit_floats * 4);
   if (w) *w = v;
   return b.used;
 }
@@ -809,34 +827,52 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
   const float* inv = w.gscale + 1;
   LS_TRY(lsk_convert_scaled(dY, c.io_dtype, w.g, LS_F32, (size_t)T * d, w.gscale, st));
   LS_TRY(lsk_convert_scaled(dY, c.io_dtype, w.g16, mt, (size_t)T * d, w.gscale, st));
+  // dW [M, N] (+)= 2^-e dOut^T In over the tokens
+  auto weight_grad = [&](int M, int N, const void* dOut, const void* In, float* dW) -> ls_status {
+    LsTimed timed(M >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);
+    if (mt != LS_F32) {
+      const ls_status r = gemm_dma_wgrad_splitk(mt, M, N, T, dOut, M, In, N, dW, N, acc, inv, w.wsplit, w.wsplit_floats, st);
+      if (r != LS_ESTATE) return r;
+    }
+    return lsk_gemm_scaled(mt, M, N, T, dOut, M, 0, In, N, 0, dW, N, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st);
+  };
+  // dIn [T, N] = dOut [T, K] W [K, N]
+  auto input_grad = [&](int N, int K, const void* dOut, const void* W, void* dIn) -> ls_status {
+    LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);
+    if (mt != LS_F32) {
+      const ls_status r = gemm_dma_dgrad_splitk(mt, T, N, K, dOut, K, W, N, dIn, N, w.wsplit, w.wsplit_floats, st);
+      if (r != LS_ESTATE) return r;
+    }
+    return lsk_gemm(mt, T, N, K, dOut, K, 1, W, N, 0, dIn, N, mt, nullptr, 0, nullptr, 0, 0, st);
+  };
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerOff& o = s->off[l];
     const Saved& v = sv[l];
     // y = x1 + act W_dn^T (+ b_dn)
     if (gpt) {
-      LS_TRY(lsk_gemm(mt, T, F, d, w.g16, d, 1, wptr(s, o.w_dn), F, 0, w.dact, F, mt, nullptr, 0, nullptr, 0, 0, st));
+      LS_TRY(input_grad(F, d, w.g16, wptr(s, o.w_dn), w.dact));
     } else if (mt == LS_F32) {
-      LS_TRY(lsk_gemm(mt, T, F, d, w.g16, d, 1, wptr(s, o.w_dn), F, 0, w.dact, F, mt, nullptr, 0, nullptr, 0, 0, st));
+      LS_TRY(input_grad(F, d, w.g16, wptr(s, o.w_dn), w.dact));
       LS_TRY(lsk_swiglu_bwd(w.dact, v.up, w.dup, mt, T, F, st));
     } else {
       // the activation's backward in the epilogue of the product that feeds it (no dact round trip)
       LS_TRY(lsk_gemm_swiglu_bwd(mt, T, F, d, w.g16, wptr(s, o.w_dn), v.up, w.dup, w.dact, st));
     }
-    LS_TRY(lsk_gemm_scaled(mt, d, F, T, w.g16, d, 0, v.act, F, 0, dParams + o.w_dn, F, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st));
+    LS_TRY(weight_grad(d, F, w.g16, v.act, dParams + o.w_dn));
     if (gpt) {
       LS_TRY(lsk_colsum_scaled(w.g16, mt, T, d, d, dParams + o.b_dn, acc, w.partial, inv, st));
       LS_TRY(lsk_gelu_bwd(w.dact, v.up, w.dup, mt, (size_t)T * F, c.act, st));
     }
     // up = h2 W_up^T (+ b_up)
-    LS_TRY(lsk_gemm(mt, T, d, U, w.dup, U, 1, wptr(s, o.w_up), d, 0, w.dh, d, mt, nullptr, 0, nullptr, 0, 0, st));
-    LS_TRY(lsk_gemm_scaled(mt, U, d, T, w.dup, U, 0, v.h2, d, 0, dParams + o.w_up, d, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st));
+    LS_TRY(input_grad(d, U, w.dup, wptr(s, o.w_up), w.dh));
+    LS_TRY(weight_grad(U, d, w.dup, v.h2, dParams + o.w_up));
     if (gpt) LS_TRY(lsk_colsum_scaled(w.dup, mt, T, U, U, dParams + o.b_up, acc, w.partial, inv, st));
     // h2 = norm2(x1);  g1 = g + norm2_bwd(dh)
     LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x1, v.mean2, v.rstd2, pptr(s, o.n2_g), pt, T, d, w.g, w.g1, w.g16, mt,
                         dParams + o.n2_g, gpt ? dParams + o.n2_b : nullptr, acc, w.partial, inv, st));
     // x1 = x + o W_o^T (+ b_o)
-    LS_TRY(lsk_gemm(mt, T, d, d, w.g16, d, 1, wptr(s, o.w_o), d, 0, w.d_o, d, mt, nullptr, 0, nullptr, 0, 0, st));
-    LS_TRY(lsk_gemm_scaled(mt, d, d, T, w.g16, d, 0, v.o, d, 0, dParams + o.w_o, d, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st));
+    LS_TRY(input_grad(d, d, w.g16, wptr(s, o.w_o), w.d_o));
+    LS_TRY(weight_grad(d, d, w.g16, v.o, dParams + o.w_o));
     if (gpt) LS_TRY(lsk_colsum_scaled(w.g16, mt, T, d, d, dParams + o.b_o, acc, w.partial, inv, st));
     if (gpt)
       LS_TRY(lsk_attn_bwd(mt == LS_F32 ? 0 : 1, v.qkv, v.o, w.d_o, v.lse, mt, B, L, c.n_heads, c.head_dim, w.dqkv,
@@ -845,8 +881,8 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
       LS_TRY(lsk_attn_bwd_rope(mt == LS_F32 ? 0 : 1, v.qkv, v.o, w.d_o, v.lse, mt, B, L, c.n_heads, c.head_dim,
                                w.dqkv, w.dvec, w.pos, s->rope_table, st));
     // qkv = h1 W_qkv^T (+ b_qkv)
-    LS_TRY(lsk_gemm(mt, T, d, 3 * d, w.dqkv, 3 * d, 1, wptr(s, o.w_qkv), d, 0, w.dh, d, mt, nullptr, 0, nullptr, 0, 0, st));
-    LS_TRY(lsk_gemm_scaled(mt, 3 * d, d, T, w.dqkv, 3 * d, 0, v.h1, d, 0, dParams + o.w_qkv, d, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st));
+    LS_TRY(input_grad(d, 3 * d, w.dqkv, wptr(s, o.w_qkv), w.dh));
+    LS_TRY(weight_grad(3 * d, d, w.dqkv, v.h1, dParams + o.w_qkv));
     if (gpt) LS_TRY(lsk_colsum_scaled(w.dqkv, mt, T, 3 * d, 3 * d, dParams + o.b_qkv, acc, w.partial, inv, st));
     // h1 = norm1(x);  g = g1 + norm1_bwd(dh)
     LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x_in, v.mean1, v.rstd1, pptr(s, o.n1_g), pt, T, d, w.g1, w.g, w.g16, mt,
