@@ -600,15 +600,35 @@ ls_status gemm_dma_splitk_try(int op_dtype, int M, int N, int K, const void* A, 
   return LS_ESTATE;
 }
 
+ls_status gemm_dma16_partials(int, int, int, int, const void*, long, const void*, long, float*, int, hipStream_t);
+
 // The first half of gemm_dma_splitk_try: the partial products stay in `scratch` as [splits][M][N] for a
 // caller that sums them together with its next step.  LS_ESTATE when the shape does not call for a split.
 ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
                                    float* scratch, size_t scratch_floats, int* splits_out, hipStream_t st) {
   if (!scratch || K % TK != 0 || M <= 128 || N < 64 || N % 4 != 0 || (uintptr_t)scratch % 16 != 0) return LS_ESTATE;
   if (lda % 8 != 0 || ldb % 8 != 0 || (uintptr_t)A % 16 != 0 || (uintptr_t)B % 16 != 0) return LS_ESTATE;
-  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
   const int nk = K / TK;
-  if (tiles >= 200 || nk < 32) return LS_ESTATE;
+  if (nk < 32) return LS_ESTATE;
+  // 256 x 256 tiles in as many parts as fill the chip once: 1.45 us per k tile of four times the arithmetic and 8 us to
+  // write a tile of partial sums, against 0.62 us for a 128 x 128 tile alone on its compute unit and 1.4 us for two
+  // sharing one.  The sum of the parts (a launch, and its traffic at about 4 TB/s) takes another kernel's place (9 us).
+  // Eight blocks of d 4096: 48 decode rows and a 200-token prompt 3652 -> 3495 us (FFN-up in two parts 66 us, was 80;
+  // QKV in five 38, was 43), 890 prompt rows 4051 -> 3934 us (FFN-down in four 90 us, was 110).
+  const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256);
+  const int s256 = (int)(256 / tiles256 < 8 ? 256 / tiles256 : 8), s128 = (int)(512 / tiles < 8 ? 512 / tiles : 8);
+  auto sum_us = [&](int parts) { return 4.f + (float)MN * 4.f * (parts + 1) / 4e6f; };
+  const float us128 = tiles >= 200 ? (float)nk * (tiles <= 256 ? 0.62f : 1.4f * (float)((tiles + 511) / 512)) + 9.f
+                                   : (float)((nk + s128 - 1) / s128) * (s128 * tiles <= 256 ? 0.62f : 1.4f) + sum_us(s128);
+  const bool wide = N >= 256 && s256 >= 2 && nk / s256 >= 8 && (size_t)(s256 * MN) <= scratch_floats &&
+                    (float)((nk + s256 - 1) / s256) * 1.45f + 8.f + sum_us(s256) < 0.9f * us128;
+  if (wide) {
+    LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, s256, st));
+    *splits_out = s256;
+    return LS_OK;
+  }
+  if (tiles >= 200) return LS_ESTATE;
   int splits = (int)(512 / tiles);
   if (splits > 8) splits = 8;
   while (splits > 1 && nk / splits < 8) --splits;

@@ -162,7 +162,13 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-  const int nk = g.K / TK;
+  int nk = g.K / TK;
+  if constexpr (MODE == 2) {   // gridDim.y > 1: split-K, this workgroup contracts over its share of the k tiles
+    const int kt0 = (int)((long)blockIdx.y * nk / gridDim.y);
+    nk = (int)((long)(blockIdx.y + 1) * nk / gridDim.y) - kt0;
+    a_base += kt0 * a_step;
+    b_base += kt0 * b_step;
+  }
   issue_tile<BM>(a_base, a_off, smem, wave);
   issue_tile<BN>(b_base, b_off, smem + A_BYTES, wave);
 
@@ -428,8 +434,10 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
           *(f32x4_a*)((T*)g.C + (long)m * g.ldc + n) = v;
         } else if constexpr (MODE == 1) {
           *(f32x4*)((float*)g.C + (long)m * g.ldc + n) = v + c_old[it];
+        } else if constexpr (MODE == 2) {
+          *(f32x4*)((float*)g.C + blockIdx.y * g.split_stride + (long)m * g.ldc + n) = v;
         } else {
-          *(f32x4*)((float*)g.C + (long)m * g.ldc + n) = MODE == 4 ? c_old[it] + v : v;
+          *(f32x4*)((float*)g.C + (long)m * g.ldc + n) = c_old[it] + v;
         }
       };
       if (m0 + wm + pass * ROWS_P + ROWS_P <= g.M && n0 + wn + WN <= g.N) {
@@ -467,7 +475,7 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
 }
 
 template <class T, bool AK, bool BK, int MODE>
-ls_status launch16(DmaArgs g, hipStream_t st) {
+ls_status launch16(DmaArgs g, hipStream_t st, int splits = 1) {
   static bool attr_set = false;
   const int lds = 2 * (256 + 256) * 128;
   if (!attr_set) {
@@ -477,7 +485,7 @@ ls_status launch16(DmaArgs g, hipStream_t st) {
   }
   g.tiles_m = (g.M + 255) / 256;
   g.tiles_n = (g.N + 255) / 256;
-  gemm_dma16_kernel<T, AK, BK, MODE><<<dim3(g.tiles_m * g.tiles_n), 256, lds, st>>>(g);
+  gemm_dma16_kernel<T, AK, BK, MODE><<<dim3(g.tiles_m * g.tiles_n, splits), 256, lds, st>>>(g);
   LS_CHECK_LAUNCH();
   return LS_OK;
 }
@@ -525,6 +533,18 @@ ls_status gemm_dma16_try(int op_dtype, int M, int N, int K, const void* A, long 
             accumulate, alpha, 0, 0, 0, rope_pos, rope_table, rope_cols};
   if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, st);
   if (op_dtype == LS_F16) return dispatch16<f16_t>(g, st);
+  return LS_ESTATE;
+}
+
+// Partial products [splits][M][N] (fp32) of the forward layout, whatever the number of tiles.  The caller has checked
+// sizes (K a multiple of 64, at least one k tile per part, N % 4 == 0) and alignment (16 bytes, ld % 8 == 0).
+ls_status gemm_dma16_partials(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
+                              float* scratch, int splits, hipStream_t st) {
+  DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
+            nullptr, 0};
+  g.split_stride = (long)M * N;
+  if (op_dtype == LS_BF16) return launch16<bf16_t, true, true, 2>(g, st, splits);
+  if (op_dtype == LS_F16) return launch16<f16_t, true, true, 2>(g, st, splits);
   return LS_ESTATE;
 }
 

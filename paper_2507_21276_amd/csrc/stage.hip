@@ -428,35 +428,49 @@ ls_status block_forward(const ls_stage* s, int l, int T, const FwdBufs& f, const
   // to the pages rotates q and k in the same pass (a prompt chunk of 512 rows has too few tiles for the fused
   // epilogue, and a rotary kernel of its own before the page write cost 13 us per block).
   const bool roped = !gpt && mt != LS_F32 && (!kv || gemm_qkv_rope_fuses(mt, T, d, c.head_dim));
+  // Serving calls whose projection is split over k: one kernel sums the parts, rotates q and k and writes the pages (in
+  // place of a reduce kernel and the rotary / page kernel).  LS_ESTATE from the split-K launcher means "this shape is
+  // not split": the plain path runs instead.  Any other status is a failure of the launch itself and ends the call.
+  int splits = 0;
+  auto split = [&](int N, int K, const void* in, const void* W, bool* done) -> ls_status {
+    *done = false;
+    if (!kv || mt == LS_F32 || !f.scratch) return LS_OK;
+    const ls_status r = gemm_dma_splitk_partials(mt, T, N, K, in, K, W, K, f.scratch, serve_scratch_floats(s), &splits, st);
+    *done = r == LS_OK;
+    return r == LS_ESTATE ? LS_OK : r;
+  };
+  const size_t slab = kv ? (size_t)kv->n_pages * c.n_heads * c.page_size * c.head_dim * osz(s) : 0;
+  void* kp = kv ? (char*)kv->k_pool + (size_t)l * slab : nullptr;
+  void* vp = kv ? (char*)kv->v_pool + (size_t)l * slab : nullptr;
+  bool split_qkv = false;
   if (roped) {
     LS_TRY(lsk_gemm_qkv_rope(mt, T, d, f.h1, wptr(s, o.w_qkv), f.qkv, c.n_heads, c.head_dim, pos, s->rope_table, st));
   } else {
-    LS_TRY(linear(s, T, 3 * d, d, f.h1, wptr(s, o.w_qkv), f.qkv, mt, gpt ? pptr(s, o.b_qkv) : nullptr, nullptr,
-                  f.scratch, st));
-    if (!gpt && !kv) LS_TRY(lsk_rope(f.qkv, mt, T, c.n_heads, c.head_dim, pos, s->rope_table, 1.0f, st));
+    if ((((uintptr_t)kp | (uintptr_t)vp) & 7) == 0)   // four values a store
+      LS_TRY(split(3 * d, d, f.h1, wptr(s, o.w_qkv), &split_qkv));
+    if (!split_qkv) {
+      LS_TRY(linear(s, T, 3 * d, d, f.h1, wptr(s, o.w_qkv), f.qkv, mt, gpt ? pptr(s, o.b_qkv) : nullptr, nullptr,
+                    f.scratch, st));
+      if (!gpt && !kv) LS_TRY(lsk_rope(f.qkv, mt, T, c.n_heads, c.head_dim, pos, s->rope_table, 1.0f, st));
+    }
   }
   if (kv) {
-    const size_t slab = (size_t)kv->n_pages * c.n_heads * c.page_size * c.head_dim * osz(s);
-    void* kp = (char*)kv->k_pool + (size_t)l * slab;
-    void* vp = (char*)kv->v_pool + (size_t)l * slab;
-    LS_TRY(lsk_rope_kv_write(f.qkv, mt, T, c.n_heads, c.head_dim, pos, req, gpt || roped ? nullptr : s->rope_table, kp, vp,
-                             kv->block_table, kv->max_pages_per_req, c.page_size, st));
+    if (split_qkv)
+      LS_TRY(lsk_finish_qkv(f.scratch, splits, T, c.n_heads, c.head_dim, gpt ? pptr(s, o.b_qkv) : nullptr, pt, pos, req,
+                            gpt ? nullptr : s->rope_table, f.qkv, mt, kp, vp, kv->block_table, kv->max_pages_per_req,
+                            c.page_size, st));
+    else
+      LS_TRY(lsk_rope_kv_write(f.qkv, mt, T, c.n_heads, c.head_dim, pos, req, gpt || roped ? nullptr : s->rope_table, kp,
+                               vp, kv->block_table, kv->max_pages_per_req, c.page_size, st));
     LS_TRY(serve_attention(s, T, f, pos, req, B, kv, kp, vp, max_ctx, chunk_start, n_decode, st));
   } else {
     LS_TRY(lsk_attn_fwd(mt == LS_F32 ? 0 : 1, f.qkv, mt, B, L, c.n_heads, c.head_dim, f.o, f.lse, st));
   }
   // serving calls whose output projection is split over k (prompt chunks): the kernel that sums the partial
   // products also adds the residual and normalises for the FFN, in place of a reduce kernel and a norm kernel
-  int splits = 0;
-  // LS_ESTATE from the split-K launcher means "this shape is not split": the plain path runs instead.
-  // Any other status is a failure of the launch itself and ends the call.
-  bool split_o = false;
-  if (kv && mt != LS_F32 && d <= 8192 && d % 4 == 0 && f.scratch) {
-    const ls_status r = gemm_dma_splitk_partials(mt, T, d, d, f.o, d, wptr(s, o.w_o), d, f.scratch,
-                                                 serve_scratch_floats(s), &splits, st);
-    if (r != LS_OK && r != LS_ESTATE) return r;
-    split_o = r == LS_OK;
-  }
+  const bool norm_fits = d <= 8192 && d % 4 == 0;
+  bool split_o = false, split_up = false, split_dn = false;
+  if (norm_fits) LS_TRY(split(d, d, f.o, wptr(s, o.w_o), &split_o));
   if (split_o) {
     LS_TRY(lsk_finish_resid_norm(f.scratch, splits, T, d, gpt ? pptr(s, o.b_o) : nullptr, f.x, f.x1, nk, pptr(s, o.n2_g),
                                  gpt ? pptr(s, o.n2_b) : nullptr, pt, c.norm_eps, f.h2, mt, st));
@@ -465,18 +479,17 @@ ls_status block_forward(const ls_stage* s, int l, int T, const FwdBufs& f, const
     LS_TRY(lsk_norm_fwd(nk, f.x1, T, d, pptr(s, o.n2_g), gpt ? pptr(s, o.n2_b) : nullptr, pt, c.norm_eps,
                         f.h2, mt, f.mean2, f.rstd2, st));
   }
-  LS_TRY(linear(s, T, s->up_cols, d, f.h2, wptr(s, o.w_up), f.up, mt, gpt ? pptr(s, o.b_up) : nullptr, nullptr,
-                f.scratch, st));
-  if (gpt) LS_TRY(lsk_gelu_fwd(f.up, f.act, mt, (size_t)T * F, c.act, st));
-  else LS_TRY(lsk_swiglu_fwd(f.up, f.act, mt, T, F, st));
-  // the same for the down projection, whose sum kernel normalises for the next block
-  bool split_dn = false;
-  if (h1_ready && kv && mt != LS_F32 && d <= 8192 && d % 4 == 0 && f.scratch) {
-    const ls_status r = gemm_dma_splitk_partials(mt, T, d, F, f.act, F, wptr(s, o.w_dn), F, f.scratch,
-                                                 serve_scratch_floats(s), &splits, st);
-    if (r != LS_OK && r != LS_ESTATE) return r;
-    split_dn = r == LS_OK;
+  LS_TRY(split(s->up_cols, d, f.h2, wptr(s, o.w_up), &split_up));
+  if (split_up) {
+    LS_TRY(lsk_finish_act(f.scratch, splits, T, F, c.act, gpt ? pptr(s, o.b_up) : nullptr, pt, f.act, mt, st));
+  } else {
+    LS_TRY(linear(s, T, s->up_cols, d, f.h2, wptr(s, o.w_up), f.up, mt, gpt ? pptr(s, o.b_up) : nullptr, nullptr,
+                  f.scratch, st));
+    if (gpt) LS_TRY(lsk_gelu_fwd(f.up, f.act, mt, (size_t)T * F, c.act, st));
+    else LS_TRY(lsk_swiglu_fwd(f.up, f.act, mt, T, F, st));
   }
+  // the same for the down projection, whose sum kernel normalises for the next block
+  if (h1_ready && norm_fits) LS_TRY(split(d, F, f.act, wptr(s, o.w_dn), &split_dn));
   if (split_dn) {
     const bool last = l + 1 == c.n_layers;
     const LayerOff& nx = s->off[last ? l : l + 1];

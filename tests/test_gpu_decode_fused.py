@@ -233,3 +233,29 @@ def test_decode_of_few_rows(mma, rows, shape):
             row = gather_rows_from_pool(got, table, b, n, n + 1)
             assert_close(row, np.stack([cache[l][b][i][n:n + 1] for l in range(cfg["n_layers"])]), TOL["bf16"], f"row {b}")
     st.close()
+
+
+@pytest.mark.parametrize("mma", ["f16", "bf16"])
+@pytest.mark.parametrize("rows", [(129,), (48, 152), (100, 157)])
+def test_prompt_chunks_with_split_projections(mma, rows):
+    """Projections of 129, 200 and 257 rows left as partial products (256 x 256 tiles for QKV, 128 x 128 for the short
+    FFN) and summed together with the rotary embedding and page write, the residual and norm, and the activation.
+    Bar: that of the stage tests; the page rows too."""
+    cfg = S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_ff=256)
+    st, flat, _ = make_stage(cfg, mma=mma, io="f32")
+    n, old = len(rows), np.zeros(len(rows), np.int64)
+    table, n_pages = S.page_tables(old, np.array(rows), cfg["page_size"])
+    kv = Bd.KV(st, n_pages, table, old)
+    X = S.make_activations(cfg, "X", (sum(rows), cfg["d_model"]))
+    Y = torch.empty(sum(rows), cfg["d_model"], dtype=torch.float32, device="cuda")
+    st.stage_prefill(dev(X, torch.float32), list(rows), kv, Y, st.new_workspace(sum(rows)))
+    cache = O.new_cache(cfg, n)
+    starts = np.concatenate([[0], np.cumsum(rows)])
+    ref = O.stage_prefill(cfg, flat.astype(np.float64), [X[starts[b]:starts[b + 1]].astype(np.float64) for b in range(n)], cache)
+    assert_close(host(Y), np.concatenate(ref), TOL["bf16"], "Y")
+    shape = (cfg["n_layers"], n_pages, cfg["n_heads"], cfg["page_size"], cfg["head_dim"])
+    for pool, i in ((kv.k_pool, 0), (kv.v_pool, 1)):
+        got = host(pool).reshape(shape)
+        for b, r in enumerate(rows):
+            assert_close(gather_rows_from_pool(got, table, b, 0, r)[0], cache[0][b][i], TOL["bf16"], f"pages of {b}")
+    st.close()
