@@ -1,4 +1,4 @@
-// Decode batches (at most 128 rows): the split-K projections leave fp32 partial
+// Decode batches (at most 128 rows) and serving calls of a few hundred rows: the split-K projections leave fp32 partial
 // products; the kernels here sum them in a fixed order and apply, in the same
 // pass, the step that follows the projection in the block:
 //   QKV projection   -> bias, rotary embedding of q and k, K/V page write
