@@ -120,7 +120,8 @@ ls_status lsk_grad_scale(const void*, int, size_t, float*, void*);
 ls_status lsk_norm_bwd_scaled(int, const void*, int, const float*, const float*, const float*, const void*, int,
                               int, int, const float*, float*, void*, int, float*, float*, int, float*,
                               const float*, void*);
-ls_status lsk_colsum_scaled(const void*, int, int, int, long, float*, int, float*, const float*, void*);
+ls_status lsk_colsum_partials(const void*, int, int, int, long, float*, void*);
+ls_status lsk_colsum_finish(int, const LsColsum*, int, int, const float*, void*);
 ls_status lsk_attn_prefill_mfma(const void*, int, int, const int32_t*, int, int, const void*, const void*,
                                 const int32_t*, const int32_t*, int, int, void*, void*);
 ls_status lsk_gemm_qkv_rope(int, int, int, const void*, const void*, void*, int, int, const int32_t*, const float*,
@@ -314,7 +315,7 @@ size_t carve_fwd(const ls_stage* s, void* base, int T, FwdWs* w) {
 // backward scratch
 struct BwdWs {
   int32_t* pos;
-  float *g, *g1, *dvec, *partial, *gscale, *wsplit;
+  float *g, *g1, *dvec, *partial, *gscale, *wsplit, *bias_partial;
   size_t wsplit_floats;
   void *g16, *dact, *dup, *dh, *dqkv, *d_o;
 };
@@ -334,11 +335,11 @@ size_t carve_bwd(const ls_stage* s, void* base, int T, BwdWs* w) {
   v.dqkv = b.take(T * 3 * d * e);
   v.d_o = b.take(T * d * e);
   v.dvec = (float*)b.take(lsk_attn_bwd_scratch_floats(1, T, c.n_heads) * 4);
-  size_t pf = lsk_norm_bwd_partial_floats(T, c.d_model);
-  const size_t widest = (size_t)(3 * c.d_model > s->up_cols ? 3 * c.d_model : s->up_cols);
-  const size_t cf = lsk_colsum_partial_floats(T, (int)widest);
-  if (cf > pf) pf = cf;
+  const size_t pf = lsk_norm_bwd_partial_floats(T, c.d_model);
   v.partial = (float*)b.take(pf * 4);
+  // column sums of the four bias gradients of a block, finished together
+  v.bias_partial = c.block == LS_BLOCK_GPT_PRELN
+                       ? (float*)b.take(lsk_colsum_partial_floats(T, 5 * c.d_model + s->up_cols) * 4) : nullptr;
   // partial products of the gradients: at most 256 tiles of 64 KB, eight parts of a result
   v.wsplit_floats = 0;
   if (c.mma_dtype != LS_F32) {
@@ -849,6 +850,16 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     }
     return lsk_gemm_scaled(mt, M, N, T, dOut, M, 0, In, N, 0, dW, N, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st);
   };
+  // bias gradients: the chunks' sums as each block's gradients appear, one launch for all four at its end
+  LsColsum sums[kMaxColsums];
+  int n_sums = 0;
+  float* sums_at = w.bias_partial;
+  auto bias_grad = [&](const void* dOut, int N, float* db) -> ls_status {
+    sums[n_sums++] = LsColsum{sums_at, N, db};
+    float* at = sums_at;
+    sums_at += lsk_colsum_partial_floats(T, N);
+    return lsk_colsum_partials(dOut, mt, T, N, N, at, st);
+  };
   // dIn [T, N] = dOut [T, K] W [K, N]
   auto input_grad = [&](int N, int K, const void* dOut, const void* W, void* dIn) -> ls_status {
     LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);
@@ -873,20 +884,20 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     }
     LS_TRY(weight_grad(d, F, w.g16, v.act, dParams + o.w_dn));
     if (gpt) {
-      LS_TRY(lsk_colsum_scaled(w.g16, mt, T, d, d, dParams + o.b_dn, acc, w.partial, inv, st));
+      LS_TRY(bias_grad(w.g16, d, dParams + o.b_dn));
       LS_TRY(lsk_gelu_bwd(w.dact, v.up, w.dup, mt, (size_t)T * F, c.act, st));
     }
     // up = h2 W_up^T (+ b_up)
     LS_TRY(input_grad(d, U, w.dup, wptr(s, o.w_up), w.dh));
     LS_TRY(weight_grad(U, d, w.dup, v.h2, dParams + o.w_up));
-    if (gpt) LS_TRY(lsk_colsum_scaled(w.dup, mt, T, U, U, dParams + o.b_up, acc, w.partial, inv, st));
+    if (gpt) LS_TRY(bias_grad(w.dup, U, dParams + o.b_up));
     // h2 = norm2(x1);  g1 = g + norm2_bwd(dh)
     LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x1, v.mean2, v.rstd2, pptr(s, o.n2_g), pt, T, d, w.g, w.g1, w.g16, mt,
                         dParams + o.n2_g, gpt ? dParams + o.n2_b : nullptr, acc, w.partial, inv, st));
     // x1 = x + o W_o^T (+ b_o)
     LS_TRY(input_grad(d, d, w.g16, wptr(s, o.w_o), w.d_o));
     LS_TRY(weight_grad(d, d, w.g16, v.o, dParams + o.w_o));
-    if (gpt) LS_TRY(lsk_colsum_scaled(w.g16, mt, T, d, d, dParams + o.b_o, acc, w.partial, inv, st));
+    if (gpt) LS_TRY(bias_grad(w.g16, d, dParams + o.b_o));
     if (gpt)
       LS_TRY(lsk_attn_bwd(mt == LS_F32 ? 0 : 1, v.qkv, v.o, w.d_o, v.lse, mt, B, L, c.n_heads, c.head_dim, w.dqkv,
                           w.dvec, st));
@@ -896,7 +907,12 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     // qkv = h1 W_qkv^T (+ b_qkv)
     LS_TRY(input_grad(d, 3 * d, w.dqkv, wptr(s, o.w_qkv), w.dh));
     LS_TRY(weight_grad(3 * d, d, w.dqkv, v.h1, dParams + o.w_qkv));
-    if (gpt) LS_TRY(lsk_colsum_scaled(w.dqkv, mt, T, 3 * d, 3 * d, dParams + o.b_qkv, acc, w.partial, inv, st));
+    if (gpt) LS_TRY(bias_grad(w.dqkv, 3 * d, dParams + o.b_qkv));
+    if (gpt) {
+      LS_TRY(lsk_colsum_finish(n_sums, sums, T, acc, inv, st));
+      n_sums = 0;
+      sums_at = w.bias_partial;
+    }
     // h1 = norm1(x);  g = g1 + norm1_bwd(dh)
     LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x_in, v.mean1, v.rstd1, pptr(s, o.n1_g), pt, T, d, w.g1, w.g, w.g16, mt,
                         dParams + o.n1_g, gpt ? dParams + o.n1_b : nullptr, acc, w.partial, inv, st));
