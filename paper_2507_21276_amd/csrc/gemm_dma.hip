@@ -611,18 +611,18 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
   const int nk = K / TK;
   if (nk < 32) return LS_ESTATE;
-  // 256 x 256 tiles in as many parts as fill the chip once: 1.45 us per k tile of four times the arithmetic and 8 us to
-  // write a tile of partial sums, against 0.62 us for a 128 x 128 tile alone on its compute unit and 1.4 us for two
-  // sharing one.  The sum of the parts (a launch, and its traffic at about 4 TB/s) takes another kernel's place (9 us).
-  // Eight blocks of d 4096: 48 decode rows and a 200-token prompt 3652 -> 3495 us (FFN-up in two parts 66 us, was 80;
-  // QKV in five 38, was 43), 890 prompt rows 4051 -> 3934 us (FFN-down in four 90 us, was 110).
+  // Where 128 x 128 tiles are too many to split: 256 x 256 tiles in as many parts as fill the chip once, at 1.8 us per k
+  // tile of four times the arithmetic and 8 us to write a tile of partial sums, against 0.62 us for a 128 x 128 tile
+  // alone on its compute unit and 1.4 us for two sharing one.  The sum of the parts (a launch, and its traffic at about
+  // 4 TB/s) takes another kernel's place (9 us).  Eight blocks of d 4096: 48 decode rows and a 200-token prompt 3652 ->
+  // 3495 us (FFN-up in two parts 66 us, was 80), 890 prompt rows 4051 -> 3934 us (FFN-down in four 90 us, was 110).
+  // Fewer tiles stay with the split 128 x 128 ones: at 576 and 640 rows the large tiles made the whole call 4 % longer.
   const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-  const int s256 = (int)(256 / tiles256 < 8 ? 256 / tiles256 : 8), s128 = (int)(512 / tiles < 8 ? 512 / tiles : 8);
-  auto sum_us = [&](int parts) { return 4.f + (float)MN * 4.f * (parts + 1) / 4e6f; };
-  const float us128 = tiles >= 200 ? (float)nk * (tiles <= 256 ? 0.62f : 1.4f * (float)((tiles + 511) / 512)) + 9.f
-                                   : (float)((nk + s128 - 1) / s128) * (s128 * tiles <= 256 ? 0.62f : 1.4f) + sum_us(s128);
-  const bool wide = N >= 256 && s256 >= 2 && nk / s256 >= 8 && (size_t)(s256 * MN) <= scratch_floats &&
-                    (float)((nk + s256 - 1) / s256) * 1.45f + 8.f + sum_us(s256) < 0.9f * us128;
+  const int s256 = (int)(256 / tiles256 < 8 ? 256 / tiles256 : 8);
+  const float us128 = (float)nk * (tiles <= 256 ? 0.62f : 1.4f * (float)((tiles + 511) / 512)) + 9.f;
+  const float us256 = (float)nk / (float)(s256 > 0 ? s256 : 1) * 1.8f + 12.f + (float)MN * 4.f * (s256 + 1) / 4e6f;
+  const bool wide = tiles >= 200 && N >= 256 && s256 >= 2 && nk / s256 >= 8 && (size_t)(s256 * MN) <= scratch_floats &&
+                    us256 < 0.95f * us128;
   if (wide) {
     LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, s256, st));
     *splits_out = s256;

@@ -238,8 +238,8 @@ def test_decode_of_few_rows(mma, rows, shape):
 @pytest.mark.parametrize("mma", ["f16", "bf16"])
 @pytest.mark.parametrize("rows", [(129,), (48, 152), (100, 157)])
 def test_prompt_chunks_with_split_projections(mma, rows):
-    """Projections of 129, 200 and 257 rows left as partial products (256 x 256 tiles for QKV, 128 x 128 for the short
-    FFN) and summed together with the rotary embedding and page write, the residual and norm, and the activation.
+    """Projections of 129, 200 and 257 rows left as partial products (128 x 128 tiles; 256 x 256 for QKV at 257) of the
+    block, and summed together with the rotary embedding and page write, the residual and norm, and the activation.
     Bar: that of the stage tests; the page rows too."""
     cfg = S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_ff=256)
     st, flat, _ = make_stage(cfg, mma=mma, io="f32")
