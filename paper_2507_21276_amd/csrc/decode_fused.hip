@@ -13,10 +13,32 @@ ls_status gemm_dma_skinny_partials(int, int, int, int, const void*, long, const 
 
 namespace {
 
+// N partial products, all of them requested before the first is added
+template <int N>
+__device__ __forceinline__ void add_parts(f32x4& v, const float* p, long stride) {
+  f32x4 t[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = *(const f32x4*)(p + i * stride);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v += t[i];
+}
+// Sum over the parts in ascending order, in one or two round trips to memory for up to 16 of them: eight at a time and
+// then the rest at once.  A loop over a run-time count, unrolled by eight, fetched the rest (all of up to eight parts) one
+// load and one wait after the other.
 __device__ __forceinline__ f32x4 sum_partials(const float* partial, int splits, long stride, long i) {
-  f32x4 v = *(const f32x4*)(partial + i);
-#pragma unroll 8
-  for (int s = 1; s < splits; ++s) v += *(const f32x4*)(partial + s * stride + i);
+  f32x4 v = {-0.f, -0.f, -0.f, -0.f};   // -0 + x is x, for every x
+  const float* p = partial + i;
+  for (; splits > 8; splits -= 8, p += 8 * stride) add_parts<8>(v, p, stride);
+  switch (splits) {
+    case 8: add_parts<8>(v, p, stride); break;
+    case 7: add_parts<7>(v, p, stride); break;
+    case 6: add_parts<6>(v, p, stride); break;
+    case 5: add_parts<5>(v, p, stride); break;
+    case 4: add_parts<4>(v, p, stride); break;
+    case 3: add_parts<3>(v, p, stride); break;
+    case 2: add_parts<2>(v, p, stride); break;
+    default: add_parts<1>(v, p, stride); break;
+  }
   return v;
 }
 

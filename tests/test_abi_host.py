@@ -176,3 +176,37 @@ def test_no_instruction_touches_a_register_with_an_assembly_issued_lds_read_in_f
         text = out.read_text()
         assert "ds_read_b64_tr_b16" in text
         assert isa_lint.scan(text) == {}, src
+
+
+def _kernel_asm(tmp_path, src):
+    """The source's device assembly, with the flags that the library is built with."""
+    import shutil
+    import subprocess
+    from paper_2507_21276_amd import build
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    out = tmp_path / (src + ".s")
+    subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, src), "-o", str(out)],
+                   check=True, capture_output=True)
+    return out.read_text()
+
+
+def _innermost_loops(body):
+    """Line lists of the loops of a function that hold no other loop."""
+    at = {l.split(":")[0]: i for i, l in enumerate(body) if l.startswith(".LBB")}
+    spans = [(at[t], i) for i, l in enumerate(body) if re.match(r"s_(c?branch)", l)
+             for t in l.split()[-1:] if t in at and at[t] <= i]
+    return [body[a:b + 1] for a, b in spans if not any(a <= c and d <= b and (a, b) != (c, d) for c, d in spans)]
+
+
+def test_sums_of_partial_products_wait_for_several_parts_at_once(tmp_path):
+    """No loop of the kernels that sum split-K parts fetches one part and waits for it before it asks for the next."""
+    text = _kernel_asm(tmp_path, "decode_fused.hip")
+    seen = 0
+    for name in re.findall(r"^(_ZN\S*finish_\w+):", text, re.M):
+        body = [l.strip() for l in text[text.index(name + ":"):].split(".Lfunc_end")[0].splitlines()]
+        for loop in _innermost_loops(body):
+            loads = sum(l.startswith("global_load_dwordx4") for l in loop)
+            seen += loads > 1
+            assert not (loads == 1 and any("vmcnt" in l for l in loop)), (name, loop)
+    assert seen >= 8

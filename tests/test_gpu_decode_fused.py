@@ -56,6 +56,19 @@ def test_partials_sum_to_the_product(name, M, N, K):
         partials_of(name, M, N, K, 41, floats=M * N - 4)
 
 
+@pytest.mark.parametrize("splits", range(1, 19))
+def test_parts_are_summed_in_ascending_order(splits):
+    """Every count of a group of eight parts and its rest: bit-equal to the parts added one after the other in fp32."""
+    T, d = 3, 1032
+    part = dev(S.normal(45, "part", (splits, T, d)), torch.float32)
+    ref = part[0].clone()
+    for s in range(1, splits):
+        ref += part[s]
+    x_out = torch.full((T, d), float("nan"), dtype=torch.float32, device="cuda")
+    Bd.lsk_finish_resid_norm(part, splits, T, d, x_out, kind=-1)
+    assert torch.equal(x_out, ref)
+
+
 @pytest.mark.parametrize("kind", [0, 1, -1])
 @pytest.mark.parametrize("name", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("T,d,splits", [(64, 4096, 10), (5, 768, 1), (33, 1600, 3)])
