@@ -6,6 +6,8 @@
 //   FFN-up           -> bias, GELU or SwiGLU
 // so that a decode step launches one small kernel per projection instead of a
 // reduce kernel plus the elementwise kernel after it.
+#include <type_traits>
+
 #include "common.h"
 
 ls_status gemm_dma_skinny_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
@@ -67,45 +69,66 @@ __device__ __forceinline__ f32x4 load4_param(const void* p, int c, int dt) {
 
 // one workgroup of up to 1024 threads per row (a decode batch has few rows, so the parallelism has to
 // come from the columns): x_out = sum of partials + bias + resid; h = norm(x_out) (kind 0 LayerNorm,
-// 1 RMSNorm, < 0 none).  d % 4 == 0, d <= 8192 = 1024 threads x FN_MAX float4.
+// 1 RMSNorm, < 0 none).  d % 4 == 0, d <= 8192 = 1024 threads x FN_MAX float4; FN float4 per thread.
+// VEC: the parameters are bf16 and 8-byte aligned.  Their bits are requested before the partial sums and converted where
+// they are used, so that they arrive under the sums; converted where they are loaded, the compiler waits for each of them
+// first.  With FN = 2 the gain and shift are requested after the sums, for want of registers.
+// At most 64 registers: two workgroups of 1024 threads on a compute unit.  As one kernel of 66 registers for both FN it
+// held one of them, which cost calls of more rows than compute units and, more, calls beside a training task: decode of 64
+// rows on eight blocks of d 4096 next to a forward and backward of 2048 tokens 5.27 ms, now 5.01; alone 2.605 -> 2.564;
+// 32 rows on six blocks of d 768 347 -> 327 us.
 constexpr int FN_MAX = 2;
-template <class TH>
-__global__ __launch_bounds__(1024) void finish_resid_norm_kernel(const float* partial, int splits, int T, int d,
-                                                                const void* bias, const float* resid, float* x_out,
-                                                                int kind, const void* gamma, const void* beta,
-                                                                int pdt, float eps, TH* h) {
+template <class TH, bool VEC, int FN>
+__global__ __launch_bounds__(1024, 8) void finish_resid_norm_kernel(const float* partial, int splits, int T, int d,
+                                                                   const void* bias, const float* resid, float* x_out,
+                                                                   int kind, const void* gamma, const void* beta,
+                                                                   int pdt, float eps, TH* h) {
   __shared__ float red[16];
   const long row = blockIdx.x, stride = (long)T * d;
-  f32x4 v[FN_MAX], ga[FN_MAX], be[FN_MAX];
-  // the norm's parameters arrive under the partial sums and the two block sums (fetched after them, an element at a time:
-  // 5.5 us at 32 x 768, now 5.2; 6.1 fetched here an element at a time)
+  const float* part = partial + row * d;
+  f32x4 v[FN];
+  bf16x4 ga[FN], be[FN];
+  // a parameter that does not exist: bits of the partial sums in its place, not used (behind a branch on its pointer the
+  // compiler waits for what is in flight)
+  auto raw = [&](const void* p, int c) { return VEC ? *(const bf16x4*)((const bf16_t*)(p ? p : partial) + c) : bf16x4{}; };
+  auto value = [&](const void* p, int c, bf16x4 bits) {
+    f32x4 r;
 #pragma unroll
-  for (int i = 0; i < FN_MAX; ++i) {
-    const int c = (threadIdx.x + i * (int)blockDim.x) * 4;
-    ga[i] = be[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (c < d && kind >= 0) {
-      ga[i] = load4_param(gamma, c, pdt);
-      if (kind == 0 && beta) be[i] = load4_param(beta, c, pdt);
+    for (int e = 0; e < 4; ++e) r[e] = VEC ? (float)bits[e] : load_as_f(p, c + e, pdt);
+    return r;
+  };
+  auto ask = [&] {
+#pragma unroll
+    for (int i = 0; i < FN; ++i) {
+      const int c = (threadIdx.x + i * (int)blockDim.x) * 4;
+      if (c < d) {
+        ga[i] = raw(gamma, c);
+        be[i] = raw(beta, c);
+      }
     }
-  }
+  };
+  if constexpr (FN == 1) ask();
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < FN_MAX; ++i) {
+  for (int i = 0; i < FN; ++i) {
     const int c = (threadIdx.x + i * (int)blockDim.x) * 4;
     v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (c < d) {
-      v[i] = sum_partials(partial, splits, stride, row * d + c);
-      if (bias) v[i] += load4_param(bias, c, pdt);
-      if (resid) v[i] += *(const f32x4*)(resid + row * d + c);
+      const bf16x4 bi = raw(bias, c);
+      const f32x4 re = *(const f32x4*)((resid ? resid : partial) + row * d + c);
+      v[i] = sum_partials(part, splits, stride, c);
+      if (bias) v[i] += value(bias, c, bi);
+      if (resid) v[i] += re;
       *(f32x4*)(x_out + row * d + c) = v[i];
       s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
     }
   }
   if (kind < 0) return;
+  if constexpr (FN > 1) ask();   // under the block sums only: there are no registers for more
   const float mu = kind == 0 ? block_sum(s, red) / d : 0.f;
   float q = 0.f;
 #pragma unroll
-  for (int i = 0; i < FN_MAX; ++i)
+  for (int i = 0; i < FN; ++i)
     if ((threadIdx.x + i * (int)blockDim.x) * 4 < d)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -114,15 +137,14 @@ __global__ __launch_bounds__(1024) void finish_resid_norm_kernel(const float* pa
       }
   const float r = 1.0f / sqrtf(block_sum(q, red) / d + eps);
 #pragma unroll
-  for (int i = 0; i < FN_MAX; ++i) {
+  for (int i = 0; i < FN; ++i) {
     const int c = (threadIdx.x + i * (int)blockDim.x) * 4;
     if (c < d) {
+      const f32x4 gv = value(gamma, c, ga[i]);
       f32x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[e] = (v[i][e] - mu) * r * ga[i][e];
-        if (kind == 0 && beta) o[e] += be[i][e];
-      }
+      for (int e = 0; e < 4; ++e) o[e] = (v[i][e] - mu) * r * gv[e];
+      if (kind == 0 && beta) o += value(beta, c, be[i]);
       store4<TH>(h + row * d + c, o);
     }
   }
@@ -237,12 +259,18 @@ ls_status lsk_finish_resid_norm(const float* partial, int splits, int T, int d, 
   hipStream_t st = (hipStream_t)stream;
   int nt = (d / 4 + 63) / 64 * 64;   // one float4 per thread up to 4096 columns, two beyond
   if (nt > 1024) nt = 1024;
-  if (hdt == LS_F32)
-    finish_resid_norm_kernel<float><<<T, nt, 0, st>>>(partial, splits, T, d, bias, resid, x_out, kind, gamma, beta, pdt, eps, (float*)h);
-  else if (hdt == LS_BF16)
-    finish_resid_norm_kernel<bf16_t><<<T, nt, 0, st>>>(partial, splits, T, d, bias, resid, x_out, kind, gamma, beta, pdt, eps, (bf16_t*)h);
-  else
-    finish_resid_norm_kernel<f16_t><<<T, nt, 0, st>>>(partial, splits, T, d, bias, resid, x_out, kind, gamma, beta, pdt, eps, (f16_t*)h);
+  const bool vec = pdt == LS_BF16 && (((uintptr_t)bias | (uintptr_t)gamma | (uintptr_t)beta) & 7) == 0;
+  auto go = [&](auto* out) {
+    typedef std::remove_pointer_t<decltype(out)> TH;
+    auto run = [&](auto kernel) {
+      kernel<<<T, nt, 0, st>>>(partial, splits, T, d, bias, resid, x_out, kind, gamma, beta, pdt, eps, out);
+    };
+    if (d <= 4096) vec ? run(finish_resid_norm_kernel<TH, true, 1>) : run(finish_resid_norm_kernel<TH, false, 1>);
+    else vec ? run(finish_resid_norm_kernel<TH, true, FN_MAX>) : run(finish_resid_norm_kernel<TH, false, FN_MAX>);
+  };
+  if (hdt == LS_F32) go((float*)h);
+  else if (hdt == LS_BF16) go((bf16_t*)h);
+  else go((f16_t*)h);
   LS_CHECK_LAUNCH();
   return LS_OK;
 }

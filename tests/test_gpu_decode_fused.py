@@ -95,6 +95,24 @@ def test_finish_residual_and_norm(kind, name, T, d, splits):
     assert_close(host(x2), x_ref - bias, 1e-6, "in place")
 
 
+@pytest.mark.parametrize("params", ["bf16", "bf16_unaligned", "f32"])
+@pytest.mark.parametrize("d", [4, 4096, 4100, 8192])
+def test_finish_residual_and_norm_at_the_edges(params, d):
+    """One and two float4 per thread, the smallest row and the largest; parameters read as vectors and one by one.
+    fp32 sums, sums of squares of at most 8192 terms: 1e-5 of the RMS as in the test above."""
+    T, splits, dt = 3, 9, DT[params.split("_")[0]]
+    part, resid = S.normal(46, "part", (splits, T, d)), S.normal(46, "resid", (T, d))
+    p = [q(m + S.normal(46, n, (d,), 0.1), "bf16") for n, m in (("bias", 0.0), ("g", 1.0), ("b", 0.0))]
+    skip = params == "bf16_unaligned"
+    bias, g, b = [torch.cat([torch.zeros(int(skip), dtype=dt, device="cuda"), dev(v, dt)])[int(skip):] for v in p]
+    x_ref = part.astype(np.float32).astype(np.float64).sum(0) + p[0] + resid.astype(np.float32)
+    x_out, h = (torch.empty(T, d, dtype=torch.float32, device="cuda") for _ in range(2))
+    Bd.lsk_finish_resid_norm(dev(part, torch.float32), splits, T, d, x_out, bias=bias, resid=dev(resid, torch.float32),
+                             kind=0, gamma=g, beta=b, h=h)
+    assert_close(host(x_out), x_ref, 1e-6, "x_out")
+    assert_close(host(h), O.layer_norm(x_ref, p[1], p[2], 1e-5)[0], 1e-5, "normalised output")
+
+
 @pytest.mark.parametrize("name", ["f16", "bf16"])
 @pytest.mark.parametrize("act,T,F,splits", [("swiglu", 64, 11008, 4), ("swiglu", 3, 704, 1), ("gelu_tanh", 40, 1024, 7),
                                             ("gelu_erf", 9, 3072, 2)])
