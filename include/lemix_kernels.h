@@ -337,11 +337,15 @@ ls_status lsk_finish_qkv(const float* partial, int splits, int T, int h, int dh,
  * throughput.
  */
 enum {
-  LSK_TIMED_GEMM = 0,        /* lsk_gemm / lsk_gemm_scaled / lsk_gemm_qkv_rope / lsk_gemm_ws with 256 rows or more */
+  LSK_TIMED_GEMM = 0,        /* projections and gradient products of 256 rows of the result or more: lsk_gemm / lsk_gemm_scaled /
+                                lsk_gemm_qkv_rope / lsk_gemm_swiglu_bwd / lsk_gemm_ws, and the products that a stage call splits
+                                along the contraction (weight and input gradients with the sum of their parts; of a serving
+                                call's projections the parts alone, their sum is in an lsk_finish_*) */
   LSK_TIMED_ATTN_FWD = 1,    /* matrix-core attention forward (training and prompt chunks) */
   LSK_TIMED_ATTN_BWD = 2,    /* matrix-core attention backward (all its kernels) */
   LSK_TIMED_DECODE_ATTN = 3, /* the paged decode-attention kernel and its merge */
-  LSK_TIMED_DECODE_GEMM = 4, /* weight-streaming projections of decode batches (lsk_gemm_partials, lsk_gemm_ws below 256 rows) */
+  LSK_TIMED_DECODE_GEMM = 4, /* the same of fewer rows, and the projections of decode batches: lsk_gemm_partials, and the matrix-vector
+                                kernels of calls of a few rows with the steps that run inside them */
   LSK_TIMED_FINISH = 5,      /* lsk_finish_* */
   LSK_TIMED_KINDS = 6
 };

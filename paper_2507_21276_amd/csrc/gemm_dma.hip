@@ -623,7 +623,10 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   const float us256 = (float)nk / (float)(s256 > 0 ? s256 : 1) * 1.8f + 12.f + (float)MN * 4.f * (s256 + 1) / 4e6f;
   const bool wide = tiles >= 200 && N >= 256 && s256 >= 2 && nk / s256 >= 8 && (size_t)(s256 * MN) <= scratch_floats &&
                     us256 < 0.95f * us128;
+  // counted here, behind the decision: a caller that is refused runs another entry point, which counts itself
+  const int kind = M >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM;
   if (wide) {
+    LsTimed timed(kind, st);
     LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, s256, st));
     *splits_out = s256;
     return LS_OK;
@@ -637,6 +640,7 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
             nullptr, 0};
   g.split_stride = (long)M * N;
+  LsTimed timed(kind, st);
   if (op_dtype == LS_BF16) LS_TRY((launch<bf16_t, 128, 128, true, true, 2>(g, st, splits)));
   else if (op_dtype == LS_F16) LS_TRY((launch<f16_t, 128, 128, true, true, 2>(g, st, splits)));
   else return LS_ESTATE;

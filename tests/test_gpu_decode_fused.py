@@ -290,3 +290,19 @@ def test_prompt_chunks_with_split_projections(mma, rows):
         for b, r in enumerate(rows):
             assert_close(gather_rows_from_pool(got, table, b, 0, r)[0], cache[0][b][i], TOL["bf16"], f"pages of {b}")
     st.close()
+
+
+@pytest.mark.parametrize("rows,kind", [(200, "decode_gemm"), (300, "gemm")])
+def test_recording_counts_projections_that_leave_partial_products(rows, kind):
+    """A prompt chunk's four projections of a block are all recorded, under the kind of their row count: three of them
+    are split along the contraction and summed by lsk_finish_* here."""
+    cfg = S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_ff=256)
+    st, _, _ = make_stage(cfg, mma="f16", io="f32")
+    table, n_pages = S.page_tables(np.zeros(1, np.int64), np.array([rows]), cfg["page_size"])
+    kv = Bd.KV(st, n_pages, table, [0])
+    X = dev(S.make_activations(cfg, "X", (rows, cfg["d_model"])), torch.float32)
+    Bd.lsk_timing_begin()
+    st.stage_prefill(X, [rows], kv, torch.empty_like(X), st.new_workspace(rows))
+    seen = Bd.lsk_timing_end()
+    assert seen[kind][1] == 4 and seen["gemm"][1] + seen["decode_gemm"][1] == 4 and seen["finish"][1] >= 2
+    st.close()
