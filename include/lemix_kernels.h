@@ -281,6 +281,19 @@ ls_status lsk_colsum_scaled(const void* x, int dtype, int T, int N, long ld, flo
                             int accumulate, float* partial, const float* alpha_dev, void* stream);
 
 /*
+ * The gradients of a linear map over T tokens, with an fp32 workspace (null or too small: as without one):
+ *   weights dW[M,N] (fp32) = (accumulate ? dW : 0) + alpha * dOut[T,M]^T In[T,N]
+ *   input   dIn[T,N] (op_dtype) = dOut[T,K] W[K,N]
+ * as lsk_gemm_scaled / lsk_gemm compute them (same operand rules, rows without gaps).  A result with too few tiles for
+ * the chip is computed in up to eight parts along the contraction, [part][row][column] in `scratch`, which are then
+ * added in order.  parts [host, may be null]: how many this call used.
+ */
+ls_status lsk_gemm_wgrad(int op_dtype, int M, int N, int T, const void* dOut, const void* In, float* dW, int accumulate,
+                         const float* alpha_dev, float* scratch, size_t scratch_floats, int* parts, void* stream);
+ls_status lsk_gemm_dgrad(int op_dtype, int T, int N, int K, const void* dOut, const void* W, void* dIn, float* scratch,
+                         size_t scratch_floats, int* parts, void* stream);
+
+/*
  * Decode batches (Autoregressive Generation: decoding requests extend their
  * prefilled context one token per iteration; at most 128 rows per call).  The
  * projections of such a batch stream the weights once and split the
@@ -338,9 +351,9 @@ ls_status lsk_finish_qkv(const float* partial, int splits, int T, int h, int dh,
  */
 enum {
   LSK_TIMED_GEMM = 0,        /* projections and gradient products of 256 rows of the result or more: lsk_gemm / lsk_gemm_scaled /
-                                lsk_gemm_qkv_rope / lsk_gemm_swiglu_bwd / lsk_gemm_ws, and the products that a stage call splits
-                                along the contraction (weight and input gradients with the sum of their parts; of a serving
-                                call's projections the parts alone, their sum is in an lsk_finish_*) */
+                                lsk_gemm_qkv_rope / lsk_gemm_swiglu_bwd / lsk_gemm_ws / lsk_gemm_wgrad / lsk_gemm_dgrad, and the
+                                projections that a serving call splits along the contraction (the parts alone: their sum is
+                                in an lsk_finish_*) */
   LSK_TIMED_ATTN_FWD = 1,    /* matrix-core attention forward (training and prompt chunks) */
   LSK_TIMED_ATTN_BWD = 2,    /* matrix-core attention backward (all its kernels) */
   LSK_TIMED_DECODE_ATTN = 3, /* the paged decode-attention kernel and its merge */

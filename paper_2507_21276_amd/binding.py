@@ -91,6 +91,8 @@ SIGNATURES = {
     "lsk_convert": (_I, [_VP, _I, _VP, _I, _SZ, _VP]),
     "lsk_grad_scale": (_I, [_VP, _I, _SZ, _VP, _VP]),
     "lsk_gemm_scaled": (_I, [_I, _I, _I, _I, _VP, _L, _I, _VP, _L, _I, _VP, _L, _I, _VP, _I, _VP, _L, _I, _VP, _VP]),
+    "lsk_gemm_wgrad": (_I, [_I, _I, _I, _I, _VP, _VP, _VP, _I, _VP, _VP, _SZ, C.POINTER(_I), _VP]),
+    "lsk_gemm_dgrad": (_I, [_I, _I, _I, _I, _VP, _VP, _VP, _VP, _SZ, C.POINTER(_I), _VP]),
     "lsk_convert_scaled": (_I, [_VP, _I, _VP, _I, _SZ, _VP, _VP]),
     "lsk_norm_bwd_scaled": (_I, [_I, _VP, _I, _VP, _VP, _VP, _VP, _I, _I, _I, _VP, _VP, _VP, _I, _VP, _VP, _I,
                                  _VP, _VP, _VP]),
@@ -496,6 +498,23 @@ def lsk_timing_end():
 
 def _opt(t):
     return _p(t) if t is not None else None
+
+
+def lsk_gemm_wgrad(dout, x, dw, scratch, alpha=None, accumulate=False, stream=None):
+    """dw[M, N] (+)= alpha dout[T, M]^T x[T, N] with an fp32 workspace: returns the number of parts it was computed in."""
+    parts = C.c_int(0)
+    _check(lib().lsk_gemm_wgrad(CODE_OF_TORCH[dout.dtype], dout.shape[1], x.shape[1], dout.shape[0], _p(dout), _p(x), _p(dw),
+                                int(accumulate), _opt(alpha), _opt(scratch), scratch.numel() if scratch is not None else 0,
+                                C.byref(parts), _stream(stream)))
+    return parts.value
+
+
+def lsk_gemm_dgrad(dout, w, dx, scratch, stream=None):
+    """dx[T, N] = dout[T, K] w[K, N] with an fp32 workspace: returns the number of parts it was computed in."""
+    parts = C.c_int(0)
+    _check(lib().lsk_gemm_dgrad(CODE_OF_TORCH[dout.dtype], dout.shape[0], w.shape[1], dout.shape[1], _p(dout), _p(w), _p(dx),
+                                _opt(scratch), scratch.numel() if scratch is not None else 0, C.byref(parts), _stream(stream)))
+    return parts.value
 
 
 def lsk_gemm_partials(x, w, partial, stream=None):

@@ -396,6 +396,43 @@ extern "C" ls_status lsk_gemm_ws(int op_dtype, int M, int N, int K, const void* 
   return lsk_gemm(op_dtype, M, N, K, X, ldx, 1, W, ldw, 1, C, ldc, c_dtype, bias, bias_dtype, resid, ldr, 0, stream);
 }
 
+ls_status gemm_dma_wgrad_splitk(int, int, int, int, const void*, long, const void*, long, float*, long, int, const float*,
+                                float*, size_t, int*, hipStream_t);
+ls_status gemm_dma_dgrad_splitk(int, int, int, int, const void*, long, const void*, long, void*, long, float*, size_t, int*,
+                                hipStream_t);
+
+// The two gradients of a linear map with an fp32 workspace: split along the contraction into partial products where the
+// result has too few tiles for the chip, in one piece otherwise.
+extern "C" ls_status lsk_gemm_wgrad(int op_dtype, int M, int N, int T, const void* dOut, const void* In, float* dW,
+                                    int accumulate, const float* alpha_dev, float* scratch, size_t scratch_floats,
+                                    int* parts, void* stream) {
+  LS_REQUIRE(M > 0 && N > 0 && T > 0 && dOut && In && dW, "gemm_wgrad: bad argument");
+  LsTimed timed(M >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, stream);
+  int n = 1;
+  ls_status r = LS_ESTATE;
+  if (op_dtype != LS_F32)
+    r = gemm_dma_wgrad_splitk(op_dtype, M, N, T, dOut, M, In, N, dW, N, accumulate, alpha_dev, scratch, scratch_floats, &n,
+                              (hipStream_t)stream);
+  if (r == LS_ESTATE)
+    r = lsk_gemm_scaled(op_dtype, M, N, T, dOut, M, 0, In, N, 0, dW, N, LS_F32, nullptr, 0, nullptr, 0, accumulate,
+                        alpha_dev, stream);
+  if (parts) *parts = n;
+  return r;
+}
+extern "C" ls_status lsk_gemm_dgrad(int op_dtype, int T, int N, int K, const void* dOut, const void* W, void* dIn,
+                                    float* scratch, size_t scratch_floats, int* parts, void* stream) {
+  LS_REQUIRE(T > 0 && N > 0 && K > 0 && dOut && W && dIn, "gemm_dgrad: bad argument");
+  LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, stream);
+  int n = 1;
+  ls_status r = LS_ESTATE;
+  if (op_dtype != LS_F32)
+    r = gemm_dma_dgrad_splitk(op_dtype, T, N, K, dOut, K, W, N, dIn, N, scratch, scratch_floats, &n, (hipStream_t)stream);
+  if (r == LS_ESTATE)
+    r = lsk_gemm(op_dtype, T, N, K, dOut, K, 1, W, N, 0, dIn, N, op_dtype, nullptr, 0, nullptr, 0, 0, stream);
+  if (parts) *parts = n;
+  return r;
+}
+
 ls_status gemm_dma16_swiglu_bwd_try(int, int, int, int, const void*, long, const void*, long, const void*, void*,
                                     hipStream_t);
 

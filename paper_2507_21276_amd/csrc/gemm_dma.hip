@@ -692,7 +692,7 @@ size_t gemm_dma_wgrad_scratch_floats(long M, long N) {
 // products where the output has few tiles.  LS_ESTATE where the launch is better in one piece or not covered.
 ls_status gemm_dma_wgrad_splitk(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
                                 float* C, long ldc, int accumulate, const float* alpha, float* scratch,
-                                size_t scratch_floats, hipStream_t st) {
+                                size_t scratch_floats, int* splits_out, hipStream_t st) {
   if (!scratch || (uintptr_t)scratch % 16 != 0 || M < 64 || N < 64 || M % 8 != 0 || N % 8 != 0 || K < TK) return LS_ESTATE;
   if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 4 != 0 || ((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16 != 0) return LS_ESTATE;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
@@ -706,13 +706,15 @@ ls_status gemm_dma_wgrad_splitk(int op_dtype, int M, int N, int K, const void* A
   else return LS_ESTATE;
   wgrad_reduce_kernel<<<(unsigned)((MN / 4 + 255) / 256), 256, 0, st>>>(scratch, splits, MN, N, C, ldc, accumulate, alpha);
   LS_CHECK_LAUNCH();
+  *splits_out = splits;
   return LS_OK;
 }
 
 // Input gradient C[M, N] (operand type) = A W over K columns of A [M][K] and rows of W [K][N], split along K into
 // partial products where the output has few tiles.  LS_ESTATE where the launch is better in one piece or not covered.
 ls_status gemm_dma_dgrad_splitk(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
-                                void* C, long ldc, float* scratch, size_t scratch_floats, hipStream_t st) {
+                                void* C, long ldc, float* scratch, size_t scratch_floats, int* splits_out,
+                                hipStream_t st) {
   if (!scratch || (uintptr_t)scratch % 16 != 0 || M < 64 || N < 64 || N % 8 != 0 || K % TK != 0) return LS_ESTATE;
   if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || ((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16 != 0) return LS_ESTATE;
   const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128), MN = (long)M * N;
@@ -732,6 +734,7 @@ ls_status gemm_dma_dgrad_splitk(int op_dtype, int M, int N, int K, const void* A
     return LS_ESTATE;
   }
   LS_CHECK_LAUNCH();
+  *splits_out = splits;
   return LS_OK;
 }
 

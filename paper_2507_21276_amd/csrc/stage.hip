@@ -133,10 +133,6 @@ ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, cons
 }
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim);
 size_t gemm_dma_wgrad_scratch_floats(long M, long N);
-ls_status gemm_dma_wgrad_splitk(int, int, int, int, const void*, long, const void*, long, float*, long, int, const float*,
-                                float*, size_t, hipStream_t);
-ls_status gemm_dma_dgrad_splitk(int, int, int, int, const void*, long, const void*, long, void*, long, float*, size_t,
-                                hipStream_t);
 bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
 ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
                                    hipStream_t);
@@ -842,13 +838,8 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
   LS_TRY(lsk_convert_scaled(dY, c.io_dtype, w.g, LS_F32, (size_t)T * d, w.gscale, st));
   LS_TRY(lsk_convert_scaled(dY, c.io_dtype, w.g16, mt, (size_t)T * d, w.gscale, st));
   // dW [M, N] (+)= 2^-e dOut^T In over the tokens
-  auto weight_grad = [&](int M, int N, const void* dOut, const void* In, float* dW) -> ls_status {
-    LsTimed timed(M >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);
-    if (mt != LS_F32) {
-      const ls_status r = gemm_dma_wgrad_splitk(mt, M, N, T, dOut, M, In, N, dW, N, acc, inv, w.wsplit, w.wsplit_floats, st);
-      if (r != LS_ESTATE) return r;
-    }
-    return lsk_gemm_scaled(mt, M, N, T, dOut, M, 0, In, N, 0, dW, N, LS_F32, nullptr, 0, nullptr, 0, acc, inv, st);
+  auto weight_grad = [&](int M, int N, const void* dOut, const void* In, float* dW) {
+    return lsk_gemm_wgrad(mt, M, N, T, dOut, In, dW, acc, inv, w.wsplit, w.wsplit_floats, nullptr, st);
   };
   // bias gradients: the chunks' sums as each block's gradients appear, one launch for all four at its end
   LsColsum sums[kMaxColsums];
@@ -861,13 +852,8 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     return lsk_colsum_partials(dOut, mt, T, N, N, at, st);
   };
   // dIn [T, N] = dOut [T, K] W [K, N]
-  auto input_grad = [&](int N, int K, const void* dOut, const void* W, void* dIn) -> ls_status {
-    LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);
-    if (mt != LS_F32) {
-      const ls_status r = gemm_dma_dgrad_splitk(mt, T, N, K, dOut, K, W, N, dIn, N, w.wsplit, w.wsplit_floats, st);
-      if (r != LS_ESTATE) return r;
-    }
-    return lsk_gemm(mt, T, N, K, dOut, K, 1, W, N, 0, dIn, N, mt, nullptr, 0, nullptr, 0, 0, st);
+  auto input_grad = [&](int N, int K, const void* dOut, const void* W, void* dIn) {
+    return lsk_gemm_dgrad(mt, T, N, K, dOut, W, dIn, w.wsplit, w.wsplit_floats, nullptr, st);
   };
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerOff& o = s->off[l];
