@@ -15,33 +15,57 @@ ls_status gemm_dma_skinny_partials(int, int, int, int, const void*, long, const 
 
 namespace {
 
-// N partial products, all of them requested before the first is added
-template <int N>
-__device__ __forceinline__ void add_parts(f32x4& v, const float* p, long stride) {
-  f32x4 t[N];
+// N partial products at C columns, all of them requested before the first is added.  p is the same for the whole wavefront
+// and `at`, in bytes, unsigned: a scalar address for each part and one register for a column's offset.  (The empty
+// statement keeps the compiler from forming the addresses of all counts ahead of the switch below, in two vector
+// registers each.)
+template <int N, int C>
+__device__ __forceinline__ void add_parts(f32x4 (&v)[C], const float* p, long stride, const uint32_t (&at)[C]) {
+  f32x4 t[N][C];
 #pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = *(const f32x4*)(p + i * stride);
+  for (int c = 0; c < C; ++c) {
+    uint32_t a = at[c];
+    asm("" : "+v"(a));
 #pragma unroll
-  for (int i = 0; i < N; ++i) v += t[i];
-}
-// Sum over the parts in ascending order, in one or two round trips to memory for up to 16 of them: eight at a time and
-// then the rest at once.  A loop over a run-time count, unrolled by eight, fetched the rest (all of up to eight parts) one
-// load and one wait after the other.
-__device__ __forceinline__ f32x4 sum_partials(const float* partial, int splits, long stride, long i) {
-  f32x4 v = {-0.f, -0.f, -0.f, -0.f};   // -0 + x is x, for every x
-  const float* p = partial + i;
-  for (; splits > 8; splits -= 8, p += 8 * stride) add_parts<8>(v, p, stride);
-  switch (splits) {
-    case 8: add_parts<8>(v, p, stride); break;
-    case 7: add_parts<7>(v, p, stride); break;
-    case 6: add_parts<6>(v, p, stride); break;
-    case 5: add_parts<5>(v, p, stride); break;
-    case 4: add_parts<4>(v, p, stride); break;
-    case 3: add_parts<3>(v, p, stride); break;
-    case 2: add_parts<2>(v, p, stride); break;
-    default: add_parts<1>(v, p, stride); break;
+    for (int i = 0; i < N; ++i) t[i][c] = *(const f32x4*)((const char*)(p + i * stride) + a);
   }
-  return v;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[c] += t[i][c];
+}
+// Sums over the parts in ascending order, at one column or at two of the same row: eight loads at a time, and then the
+// rest at once, so one or two round trips to memory for up to 16 parts at one column or eight at two.  A loop over a
+// run-time count, unrolled by eight, fetched the rest (all of up to eight parts) one load and one wait after the other.
+template <int C>
+__device__ __forceinline__ void sum_partials(f32x4 (&v)[C], const float* row, int splits, long stride, const int (&col)[C]) {
+  constexpr int G = 8 / C;
+  uint32_t at[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    v[c] = f32x4{-0.f, -0.f, -0.f, -0.f};   // -0 + x is x, for every x
+    at[c] = (uint32_t)col[c] * 4u;
+  }
+  for (; splits > G; splits -= G, row += G * stride) add_parts<G>(v, row, stride, at);
+  if constexpr (C == 1) {
+    switch (splits) {
+      case 8: add_parts<8>(v, row, stride, at); return;
+      case 7: add_parts<7>(v, row, stride, at); return;
+      case 6: add_parts<6>(v, row, stride, at); return;
+      case 5: add_parts<5>(v, row, stride, at); return;
+    }
+  }
+  switch (splits) {
+    case 4: add_parts<4>(v, row, stride, at); break;
+    case 3: add_parts<3>(v, row, stride, at); break;
+    case 2: add_parts<2>(v, row, stride, at); break;
+    default: add_parts<1>(v, row, stride, at); break;
+  }
+}
+__device__ __forceinline__ f32x4 sum_partials(const float* row, int splits, long stride, int col) {
+  f32x4 v[1];
+  sum_partials(v, row, splits, stride, {col});
+  return v[0];
 }
 
 template <class TH> __device__ __forceinline__ void store4(TH* p, f32x4 v) {
@@ -150,76 +174,99 @@ __global__ __launch_bounds__(1024, 8) void finish_resid_norm_kernel(const float*
   }
 }
 
+// The two kernels below: a workgroup takes a piece of one row, so that its addresses are scalar, and both columns of a
+// pair are asked for at once.  With row and column divided out of one running index and a sum after the other they took 72
+// registers (46 and 52 now); d 4096, 64 rows, two parts: gate and up 3.6 -> 3.2 us, q, k and v 4.3 -> 3.6 us.
+
 // four hidden units per thread.  act LS_ACT_SWIGLU: the projection has 2F columns (gate, then up).
 template <class TH>
-__global__ void finish_act_kernel(const float* partial, int splits, int T, int F, int act, const void* bias, int pdt,
-                                  TH* out) {
+__global__ __launch_bounds__(256) void finish_act_kernel(const float* partial, int splits, int T, int t0, int F, int pieces, int act,
+                                                         const void* bias, int pdt, TH* out) {
   const int cols = act == LS_ACT_SWIGLU ? 2 * F : F;
-  const long stride = (long)T * cols, n4 = (long)T * (F / 4);
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < n4; idx += (long)gridDim.x * blockDim.x) {
-    const long t = idx / (F / 4);
-    const int f = (int)(idx % (F / 4)) * 4;
-    f32x4 a = sum_partials(partial, splits, stride, t * cols + f), o;
-    if (bias) a += load4_param(bias, f, pdt);
-    if (act == LS_ACT_SWIGLU) {
-      f32x4 u = sum_partials(partial, splits, stride, t * cols + F + f);
-      if (bias) u += load4_param(bias, F + f, pdt);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = a[e] / (1.f + __expf(-a[e])) * u[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = gelu_f(a[e], act);
+  const long stride = (long)T * cols;
+  const int f = (int)(blockIdx.x % pieces * blockDim.x + threadIdx.x) * 4;
+  if (f >= F) return;
+  const long t = t0 + blockIdx.x / pieces;
+  const float* row = partial + t * cols;
+  f32x4 o;
+  if (act == LS_ACT_SWIGLU) {
+    f32x4 v[2];
+    sum_partials(v, row, splits, stride, {f, F + f});
+    f32x4 a = v[0], u = v[1];
+    if (bias) {
+      a += load4_param(bias, f, pdt);
+      u += load4_param(bias, F + f, pdt);
     }
-    store4<TH>(out + t * F + f, o);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = a[e] / (1.f + __expf(-a[e])) * u[e];
+  } else {
+    f32x4 a = sum_partials(row, splits, stride, f);
+    if (bias) a += load4_param(bias, f, pdt);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = gelu_f(a[e], act);
   }
+  store4<TH>(out + t * F + f, o);
 }
 
 // one thread per (row, q / k / v, head, four pairs i .. i + 3 < dh / 2); rotation of q and k by
 // pos[row] when a table is given; the values go to the qkv buffer and those of k and v also to
 // the request's page slot.  dh % 8 == 0.
 template <class TH>
-__global__ void finish_qkv_kernel(const float* partial, int splits, int T, int h, int dh, const void* bias, int pdt,
-                                  const int32_t* pos, const int32_t* req, const float* table, TH* qkv, TH* k_pool,
-                                  TH* v_pool, const int32_t* block_table, int max_pages, int page) {
+__global__ __launch_bounds__(512) void finish_qkv_kernel(const float* partial, int splits, int T, int t0, int h, int dh, int pieces,
+                                                         const void* bias, int pdt, const int32_t* pos, const int32_t* req,
+                                                         const float* table, TH* qkv, TH* k_pool, TH* v_pool,
+                                                         const int32_t* block_table, int max_pages, int page) {
   const int half = dh / 2, d = h * dh, q4 = half / 4;
-  const long stride = (long)T * 3 * d, n = (long)T * 3 * h * q4;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < n; idx += (long)gridDim.x * blockDim.x) {
-    const int i = (int)(idx % q4) * 4, hp = (int)((idx / q4) % (3 * h));   // hp = part * h + head
-    const int part = hp / h, head = hp % h;
-    const long t = idx / ((long)q4 * 3 * h);
-    const long qi = t * 3 * d + (long)hp * dh + i;
-    f32x4 xa = sum_partials(partial, splits, stride, qi), xb = sum_partials(partial, splits, stride, qi + half);
-    if (bias) {
-      xa += load4_param(bias, hp * dh + i, pdt);
-      xb += load4_param(bias, hp * dh + i + half, pdt);
-    }
-    const int p = pos[t];
-    if (table && part < 2) {
-      const float* tb = table + ((long)p * half + i) * 2;   // (cos, sin) pairs
-      const f32x4 cs0 = *(const f32x4*)tb, cs1 = *(const f32x4*)(tb + 4);
-      const f32x4 c = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn = {cs0[1], cs0[3], cs1[1], cs1[3]};
-      const f32x4 ra = xa * c - xb * sn, rb = xb * c + xa * sn;
-      xa = ra; xb = rb;
-    }
-    typedef TH V4 __attribute__((ext_vector_type(4)));
-    V4 oa, ob;
+  const long stride = (long)T * 3 * d;
+  const int idx = (int)(blockIdx.x % pieces * blockDim.x + threadIdx.x);
+  if (idx >= 3 * h * q4) return;
+  const int i = idx % q4 * 4, hp = idx / q4;   // hp = part * h + head
+  const int part = hp / h, head = hp % h;
+  const int col = hp * dh + i;
+  const long t = t0 + blockIdx.x / pieces;
+  const float* row = partial + t * 3 * d;
+  const int p = pos[t], rq = req[t];   // asked for ahead of the sums: the page and the rotation wait for them
+  f32x4 v[2];
+  sum_partials(v, row, splits, stride, {col, col + half});
+  f32x4 xa = v[0], xb = v[1];
+  if (bias) {
+    xa += load4_param(bias, col, pdt);
+    xb += load4_param(bias, col + half, pdt);
+  }
+  if (table && part < 2) {
+    const float* tb = table + ((long)p * half + i) * 2;   // (cos, sin) pairs
+    const f32x4 cs0 = *(const f32x4*)tb, cs1 = *(const f32x4*)(tb + 4);
+    const f32x4 c = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn = {cs0[1], cs0[3], cs1[1], cs1[3]};
+    const f32x4 ra = xa * c - xb * sn, rb = xb * c + xa * sn;
+    xa = ra; xb = rb;
+  }
+  typedef TH V4 __attribute__((ext_vector_type(4)));
+  V4 oa, ob;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { oa[e] = from_f<TH>(xa[e]); ob[e] = from_f<TH>(xb[e]); }
-    *(V4*)(qkv + qi) = oa;
-    *(V4*)(qkv + qi + half) = ob;
-    if (part > 0) {
-      TH* pool = part == 1 ? k_pool : v_pool;
-      const int pg = block_table[(long)req[t] * max_pages + p / page];
-      const long dst = (((long)pg * h + head) * page + p % page) * dh + i;
-      *(V4*)(pool + dst) = oa;
-      *(V4*)(pool + dst + half) = ob;
-    }
+  for (int e = 0; e < 4; ++e) { oa[e] = from_f<TH>(xa[e]); ob[e] = from_f<TH>(xb[e]); }
+  TH* to = qkv + t * 3 * d + col;
+  *(V4*)to = oa;
+  *(V4*)(to + half) = ob;
+  if (part > 0) {
+    TH* pool = part == 1 ? k_pool : v_pool;
+    const int pg = block_table[(long)rq * max_pages + p / page];
+    const long dst = (((long)pg * h + head) * page + p % page) * dh + i;
+    *(V4*)(pool + dst) = oa;
+    *(V4*)(pool + dst + half) = ob;
   }
 }
 
-inline unsigned grid_of(long n, unsigned cap = 8192) {
-  long g = (n + 255) / 256;
-  return (unsigned)(g < 1 ? 1 : (g > cap ? cap : g));
+// launches of the two kernels above for T rows of n threads each, in pieces of 256 to `widest` threads, of which those that
+// leave the fewest lanes idle: go(first row, pieces of a row, workgroups, threads of one)
+template <class Go>
+void for_rows(int T, int n, int widest, Go go) {
+  int pieces = 0, threads = 0;
+  for (int p = (n + widest - 1) / widest; p <= (n + 255) / 256; ++p) {
+    const int nt = ((n + p - 1) / p + 63) / 64 * 64;
+    if (!pieces || (long)p * nt < (long)pieces * threads) { pieces = p; threads = nt; }
+  }
+  const int most = (1 << 22) / pieces > 0 ? (1 << 22) / pieces : 1;   // rows of a launch: fewer than 2^32 threads
+  for (long t = 0; t < T; t += most) go((int)t, pieces, (unsigned)(T - t < most ? T - t : most) * (unsigned)pieces, threads);
 }
 inline bool half_type(int dt) { return dt == LS_BF16 || dt == LS_F16; }
 
@@ -283,10 +330,14 @@ ls_status lsk_finish_act(const float* partial, int splits, int T, int F, int act
   LS_REQUIRE(act == LS_ACT_GELU_TANH || act == LS_ACT_GELU_ERF || act == LS_ACT_SWIGLU, "finish_act: unknown activation %d", act);
   LS_REQUIRE((uintptr_t)partial % 16 == 0 && (uintptr_t)out % 16 == 0, "finish_act: buffers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
-  const unsigned g = grid_of((long)T * (F / 4));
-  if (odt == LS_F32) finish_act_kernel<float><<<g, 256, 0, st>>>(partial, splits, T, F, act, bias, pdt, (float*)out);
-  else if (odt == LS_BF16) finish_act_kernel<bf16_t><<<g, 256, 0, st>>>(partial, splits, T, F, act, bias, pdt, (bf16_t*)out);
-  else finish_act_kernel<f16_t><<<g, 256, 0, st>>>(partial, splits, T, F, act, bias, pdt, (f16_t*)out);
+  for_rows(T, F / 4, 256, [&](int t0, int pieces, unsigned wgs, int nt) {
+    if (odt == LS_F32)
+      finish_act_kernel<float><<<wgs, nt, 0, st>>>(partial, splits, T, t0, F, pieces, act, bias, pdt, (float*)out);
+    else if (odt == LS_BF16)
+      finish_act_kernel<bf16_t><<<wgs, nt, 0, st>>>(partial, splits, T, t0, F, pieces, act, bias, pdt, (bf16_t*)out);
+    else
+      finish_act_kernel<f16_t><<<wgs, nt, 0, st>>>(partial, splits, T, t0, F, pieces, act, bias, pdt, (f16_t*)out);
+  });
   LS_CHECK_LAUNCH();
   return LS_OK;
 }
@@ -303,13 +354,15 @@ ls_status lsk_finish_qkv(const float* partial, int splits, int T, int h, int dh,
              "finish_qkv: buffers must be aligned to their vector accesses");
   LS_REQUIRE(half_type(dt), "finish_qkv: 16-bit q, k, v only");
   hipStream_t st = (hipStream_t)stream;
-  const unsigned g = grid_of((long)T * 3 * h * (dh / 8));
-  if (dt == LS_BF16)
-    finish_qkv_kernel<bf16_t><<<g, 256, 0, st>>>(partial, splits, T, h, dh, bias, pdt, pos, req, table, (bf16_t*)qkv,
-                                                (bf16_t*)k_pool, (bf16_t*)v_pool, block_table, max_pages, page);
-  else
-    finish_qkv_kernel<f16_t><<<g, 256, 0, st>>>(partial, splits, T, h, dh, bias, pdt, pos, req, table, (f16_t*)qkv,
-                                               (f16_t*)k_pool, (f16_t*)v_pool, block_table, max_pages, page);
+  for_rows(T, 3 * h * (dh / 8), 512, [&](int t0, int pieces, unsigned wgs, int nt) {
+    if (dt == LS_BF16)
+      finish_qkv_kernel<bf16_t><<<wgs, nt, 0, st>>>(partial, splits, T, t0, h, dh, pieces, bias, pdt, pos, req, table,
+                                                   (bf16_t*)qkv, (bf16_t*)k_pool, (bf16_t*)v_pool, block_table, max_pages,
+                                                   page);
+    else
+      finish_qkv_kernel<f16_t><<<wgs, nt, 0, st>>>(partial, splits, T, t0, h, dh, pieces, bias, pdt, pos, req, table,
+                                                  (f16_t*)qkv, (f16_t*)k_pool, (f16_t*)v_pool, block_table, max_pages, page);
+  });
   LS_CHECK_LAUNCH();
   return LS_OK;
 }

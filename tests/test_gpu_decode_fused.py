@@ -115,7 +115,7 @@ def test_finish_residual_and_norm_at_the_edges(params, d):
 
 @pytest.mark.parametrize("name", ["f16", "bf16"])
 @pytest.mark.parametrize("act,T,F,splits", [("swiglu", 64, 11008, 4), ("swiglu", 3, 704, 1), ("gelu_tanh", 40, 1024, 7),
-                                            ("gelu_erf", 9, 3072, 2)])
+                                            ("gelu_erf", 9, 3072, 2), ("swiglu", 2, 4, 8), ("gelu_tanh", 5, 1028, 9)])
 def test_finish_activation(name, act, T, F, splits):
     cols = 2 * F if act == "swiglu" else F
     part = S.normal(43, "part", (splits, T, cols), 0.7)
@@ -128,7 +128,7 @@ def test_finish_activation(name, act, T, F, splits):
 
 
 @pytest.mark.parametrize("name,h,dh,P,rope,with_bias", [("f16", 2, 128, 16, True, False), ("bf16", 3, 64, 8, True, False),
-                                                      ("f16", 4, 32, 16, False, True)])
+                                                      ("f16", 4, 32, 16, False, True), ("bf16", 32, 128, 16, True, True)])
 def test_finish_qkv_rotary_and_page_write(name, h, dh, P, rope, with_bias):
     d = h * dh
     ctx = np.array([0, 5, 16, 100, 333, 47])
