@@ -219,14 +219,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 }
 
 // ---- plain fp32 FMA path (fp32 stage mode; any strides, any sizes) ---------------
-// S x S tiles, 256 threads, (S / 16)^2 outputs per thread, BK = 2048 / S.  A thread issues all of its loads of a k tile
+// S x S tiles, 256 threads, (S / 16)^2 outputs per thread, k tiles of BKF.  A thread issues all of its loads of a k tile
 // at once, a tile ahead of the arithmetic: the launches of a short fp32 task have a few workgroups, and theirs is a
-// chain of load latencies (64 x 64 tiles with BK = 16 and no loads ahead took 20 - 36 us a launch; a training task of
-// 2 x 64 tokens on the two-layer stage of width 128 went from 1406 to 583 us).
+// chain of load latencies (64 x 64 tiles with BKF = 16 and no loads ahead took 20 - 36 us a launch; a training task of
+// 2 x 64 tokens on the two-layer stage of width 128 went from 1406 to 573 us).
 // Every output is the same ascending sum over k for both tile sizes.
-template <int S>
+template <int S, int BKF>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  constexpr int BKF = 2048 / S, R = S / 16, NL = S * BKF / 256;
+  constexpr int R = S / 16, NL = S * BKF / 256, KU = S == 32 ? 16 : BKF;
   __shared__ float sa[BKF][S + 1], sb[BKF][S + 1];
   const float* A = (const float*)g.A;
   const float* B = (const float*)g.B;
@@ -262,15 +262,19 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     }
     __syncthreads();
     if (k0 + BKF < g.K) fetch(k0 + BKF);
+    // a short last k tile is not worked off to its end
+#pragma unroll 1
+    for (int kb = 0; kb < BKF && k0 + kb < g.K; kb += KU) {
 #pragma unroll 16
-    for (int k = 0; k < BKF; ++k) {
-      float av[R], bv[R];
+      for (int k = kb; k < kb + KU; ++k) {
+        float av[R], bv[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) { av[i] = sa[k][ty * R + i]; bv[i] = sb[k][tx * R + i]; }
+        for (int i = 0; i < R; ++i) { av[i] = sa[k][ty * R + i]; bv[i] = sb[k][tx * R + i]; }
 #pragma unroll
-      for (int i = 0; i < R; ++i)
+        for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+          for (int j = 0; j < R; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+      }
     }
     __syncthreads();
   }
@@ -333,10 +337,12 @@ extern "C" ls_status lsk_gemm_scaled(int op_dtype, int M, int N, int K, const vo
   hipStream_t st = (hipStream_t)stream;
   if (op_dtype == LS_F32) {
     LS_REQUIRE(c_dtype == LS_F32, "gemm: fp32 operands need an fp32 output");
-    // 32 x 32 tiles while 64 x 64 ones would leave compute units without one
+    // 32 x 32 tiles while 64 x 64 ones would leave compute units without one.  These take k tiles of 16: workgroups that
+    // share a unit hide each other's loads, and the padding of a short contraction is less (k tiles of 32 -> 16: 6144 x
+    // 2048 over 16 30.8 -> 23.6 us, over 80 57 -> 47, 4096 x 2048 over 1024 358 -> 350; 1024 x 1024 over 4096 430 -> 433)
     const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles < 256) gemm_f32_kernel<32><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
-    else gemm_f32_kernel<64><<<dim3(tiles), dim3(256), 0, st>>>(g);
+    if (tiles < 256) gemm_f32_kernel<32, 64><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
+    else gemm_f32_kernel<64, 16><<<dim3(tiles), dim3(256), 0, st>>>(g);
     LS_CHECK_LAUNCH();
     return LS_OK;
   }

@@ -67,9 +67,9 @@ def test_products_of_64_to_255_rows(name, M, N, K):
     assert_close(host(out), (A64 @ torch.from_numpy(Bk).cuda()).cpu().numpy(), tol, "input gradient")
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 65), (128, 128, 128), (64, 256, 64), (130, 70, 129), (1030, 1025, 40)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 65), (128, 128, 128), (64, 256, 64), (130, 70, 129), (1030, 1025, 40), (1030, 1025, 16), (1030, 1025, 1)])
 def test_fp32_products_of_both_tile_sizes(M, N, K):
-    """32 x 32 and 64 x 64 tiles, k tiles of 64 and 32, all four layouts, remainders in each dimension.  Sums of K
+    """32 x 32 and 64 x 64 tiles, k tiles of 64 and 16, all four layouts, remainders in each dimension.  Sums of K
     products in order: K 2^-24 of the largest partial sum at the worst, a few 1e-6 of the RMS here."""
     A, W = S.normal(5, "A", (M, K)), S.normal(5, "W", (N, K))
     ref = A.astype(np.float32).astype(np.float64) @ W.astype(np.float32).astype(np.float64).T
