@@ -280,7 +280,9 @@ ls_status launch(const GemvArgs& g, hipStream_t st) {
 
 template <int EPI, bool NORM>
 ls_status run(GemvArgs g, int dt, hipStream_t st) {
-  // one or two loads deep per wavefront where that is possible with all eight
+  // One to four loads of a row for each of the wavefronts that share it.  More of them (two loads each) for rows of
+  // 4097 - 8192 elements is slower, as a workgroup then covers half as many rows between two barriers: four blocks of d
+  // 5120 510 -> 539 us for one row and 550 -> 609 for two, two blocks of d 6144 247 -> 268, of d 8192 299 -> 302.
   const int nc = (g.K + CHUNK - 1) / CHUNK;
   g.wk = nc <= 1 ? 1 : nc <= 4 ? 2 : nc <= 16 ? 4 : 8;
   auto go = [&](auto t) {

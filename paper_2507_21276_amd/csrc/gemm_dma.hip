@@ -1,9 +1,10 @@
 // Large-tile MFMA GEMM whose operand tiles go from global memory straight into
 // LDS (16-byte direct-to-LDS loads, no register staging, no LDS store
 // instructions).  256 x 256 x 64 tiles (4 wavefronts of 128 x 128) or 128 x 128 x 64
-// tiles (4 wavefronts of 64 x 64) for problems with few tiles, 32x32x16 MFMA, two
-// LDS buffers.  Used when the contraction length is a multiple of 64; the
-// register-staged kernel in gemm.hip covers everything else.
+// tiles (4 wavefronts of 64 x 64) for problems with few tiles, or 64 x 128 ones for decode batches; 32x32x16 MFMA; two
+// LDS buffers, or a ring of four for the smaller tiles where a compute unit has one workgroup (see launch()).  Used when
+// the contraction length is a multiple of 64, or of any length from 64 on when both operands are k-strided (KTAIL:
+// weight gradients over any number of tokens); the register-staged kernel in gemm.hip covers everything else.
 //
 // LDS layouts (a direct-to-LDS wave load writes 1 KB: lane i -> bytes 16 i):
 //   k-major operand  (element (r,k) at r*ld + k): [256 rows][64 k], 128 B per
@@ -666,8 +667,10 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial,
 // Parts into which a product of `tiles` 128 x 128 tiles over nk k tiles is split so that the chip is full once.  A
 // workgroup alone on its compute unit takes 0.65 us per k tile (two share one at 1.4 us: nothing is gained beyond 256
 // workgroups); the sum of the parts is a launch of 4 us and moves MN (parts + 1) floats at about 4 TB/s.
-// Weight gradients over 4096 tokens, one part -> split: 768 x 768 (7 parts) 36 -> 19 us, 2304 x 768 (2) 37 -> 31 us;
-// 3072 x 768 (144 tiles) stays whole (39 us; in three parts, two workgroups a compute unit, 39 us as well).
+// Weight gradients over 4096 tokens, alone, one part -> split: 768 x 768 (6 parts) 33 -> 18 us, 2304 x 768 (2) 34 -> 28,
+// 256 x 256 (8) 33 -> 11.5; 3072 x 768 (144 tiles) stays whole (39 us in a task; in three parts, two workgroups a compute
+// unit, 39 us as well).  A further part has to gain 10 % over the last one taken: the estimate is no better than that.
+// The forward splits above go by an older rule (512 workgroups, from 32 k tiles on) that these figures do not cover.
 int splits_to_fill(long tiles, int nk, long MN) {
   int best = 1;
   float best_us = 1e30f;

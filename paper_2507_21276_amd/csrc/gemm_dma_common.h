@@ -60,7 +60,10 @@ __device__ __forceinline__ void tile_offsets(uint32_t (&off)[ROWS / 32], long ld
 // One direct-to-LDS wave load in the scalar-base form: address = uniform 64-bit base + per-lane 32-bit
 // offset, LDS destination in M0.  Issued from assembly: the builtin takes a flat pointer, which the
 // compiler forms with a 64-bit vector add per load (1 % of the GEMM leg).  The compiler therefore does not
-// count these loads: every wait for them in this file is explicit (s_waitcnt with vmcnt(0)).
+// count these loads: every wait for them is explicit.  The kernels with two LDS buffers wait for all of them (vmcnt(0)); with
+// more buffers wait_loads<N> leaves the N loads of the tiles after the next in flight, so N is the number of loads that a
+// wavefront has issued since, and every wavefront issues the same number for every tile (past the last tile, the last again).
+// Memory operations of the compiler's own in between only make such a wait longer: loads complete in order.
 __device__ __forceinline__ void dma_load(const char* base, uint32_t off, const char* lds_dst) {
   const uint32_t l = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds_dst;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
