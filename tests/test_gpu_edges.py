@@ -81,6 +81,54 @@ def test_fp32_products_of_both_tile_sizes(M, N, K):
             assert_close(host(out), ref + 2.0, max(4e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}", atol=1e-6)
 
 
+@pytest.mark.parametrize("M,N,K", [(16, 16, 4), (17, 33, 15), (33, 128, 77), (1, 512, 128), (512, 528, 130), (528, 272, 193),
+                                   (256, 250, 200), (40, 72, 385), (72, 40, 388), (1000, 1000, 49), (1000, 1000, 48)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_fp32_products_of_few_tiles(M, N, K, offset):
+    """Both tile sizes and every number of wavefronts, shares of the contraction that are short or empty, all four layouts
+    with everything the epilogue adds, operands that 16-byte loads can and cannot read.  K products summed in order: K 2^-24
+    of the largest partial sum at the worst, 2e-6 of the RMS for the few of a split sum."""
+    A, W, R, b = S.normal(6, "A", (M, K)), S.normal(6, "W", (N, K)), S.normal(6, "R", (M, N)), S.normal(6, "b", (N,))
+    f64 = lambda x: x.astype(np.float32).astype(np.float64)  # noqa: E731
+    ref = f64(A) @ f64(W).T + f64(b) + f64(R) + 2.0
+
+    def at(x):   # the values, `offset` elements behind an aligned address
+        buf = torch.empty(x.size + offset, dtype=torch.float32, device="cuda")
+        buf[offset:] = dev(x, torch.float32).reshape(-1)
+        return buf[offset:]
+    for ak in (True, False):
+        for bk in (True, False):
+            out = torch.full((M, N), 2.0, dtype=torch.float32, device="cuda")
+            Bd.lsk_gemm(at(A if ak else A.T), at(W if bk else W.T), out, M=M, N=N, K=K, a_kmajor=ak, b_kmajor=bk,
+                        lda=K if ak else M, ldb=K if bk else N, bias=dev(b, torch.float32), resid=dev(R, torch.float32),
+                        accumulate=True)
+            assert_close(host(out), ref, max(2e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}")
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("L", [1, 15, 16, 17, 64, 65, 130])
+def test_fp32_attention_over_batches_of_keys(dh, L):
+    """Sequences that end inside a batch of 16 keys, at its edge, and leave wavefronts without a key; forward and backward
+    against float64.  Sums of up to 130 terms and an exponential of arguments of a few units in fp32: below 1e-5 of the RMS."""
+    B, h = 2, 3
+    d = h * dh
+    qkv, dO = (torch.from_numpy(S.normal(9, n, (B * L, w)).astype(np.float32)).cuda() for n, w in (("qkv", 3 * d), ("dO", d)))
+    o, dqkv = torch.empty(B * L, d, device="cuda"), torch.empty(B * L, 3 * d, device="cuda")
+    lse = torch.empty(B * L, h, device="cuda")
+    Bd.lsk_attn_fwd(0, qkv, B, L, h, dh, o, lse)
+    Bd.lsk_attn_bwd(0, qkv, o, dO, lse, B, L, h, dh, dqkv)
+    x = qkv.double().reshape(B, L, 3, h, dh).permute(2, 0, 3, 1, 4).contiguous().requires_grad_()
+    s = (x[0] @ x[1].transpose(-1, -2).contiguous()) / dh ** 0.5
+    s = s.masked_fill(torch.ones(L, L, device="cuda").triu(1).bool(), float("-inf"))
+    ref = (torch.softmax(s, -1) @ x[2]).permute(0, 2, 1, 3).reshape(B * L, d)
+    ref.backward(dO.double())
+    assert_close(host(o), ref.detach().cpu().numpy(), 1e-5, "o")
+    assert_close(host(lse), torch.logsumexp(s, -1).permute(0, 2, 1).reshape(B * L, h).detach().cpu().numpy(), 1e-5, "lse")
+    g = x.grad.permute(1, 3, 0, 2, 4).reshape(B * L, 3, d).cpu().numpy()
+    for i, nm in enumerate(("dq", "dk", "dv")):
+        assert_close(host(dqkv).reshape(B * L, 3, d)[:, i], g[:, i], 1e-5, nm, atol=1e-5 if L == 1 else 0.0)
+
+
 @pytest.mark.parametrize("name", ["bf16", "f16"])
 @pytest.mark.parametrize("kind", [Bd.LS_ACT_GELU_TANH, Bd.LS_ACT_GELU_ERF])
 @pytest.mark.parametrize("n", [8, 1000, 1003])
