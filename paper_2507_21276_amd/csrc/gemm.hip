@@ -220,9 +220,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 
 // ---- plain fp32 FMA path (fp32 stage mode; any strides, any sizes) ---------------
 // S x S tiles, 256 threads, (S / 16)^2 outputs per thread, k tiles of BKF.  A thread issues all of its loads of a k tile
-// at once, a tile ahead of the arithmetic: the launches of a short fp32 task have a few workgroups, and theirs is a
-// chain of load latencies (64 x 64 tiles with BKF = 16 and no loads ahead took 20 - 36 us a launch; a training task of
-// 2 x 64 tokens on the two-layer stage of width 128 went from 1406 to 573 us).
+// at once, a tile ahead of the arithmetic.
 // Every output is the same ascending sum over k for both tile sizes.
 template <int S, int BKF>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
@@ -318,6 +316,8 @@ ls_status gemm_dma_try(int, int, int, int, const void*, long, int, const void*, 
                        const void*, int, const float*, long, int, const float*, const int32_t*, const float*, int,
                        hipStream_t);
 
+ls_status gemm_f32_few_tiles(int, int, int, const void*, long, int, const void*, long, int, void*, long, const void*, int,
+                             const float*, long, int, const float*, hipStream_t);
 ls_status gemm_dma_splitk_try(int, int, int, int, const void*, long, const void*, long, void*, long, int, const void*,
                               int, const float*, long, float*, size_t, hipStream_t);
 ls_status gemm_dma_skinny_try(int, int, int, int, const void*, long, const void*, long, void*, long, int, const void*,
@@ -337,12 +337,20 @@ extern "C" ls_status lsk_gemm_scaled(int op_dtype, int M, int N, int K, const vo
   hipStream_t st = (hipStream_t)stream;
   if (op_dtype == LS_F32) {
     LS_REQUIRE(c_dtype == LS_F32, "gemm: fp32 operands need an fp32 output");
-    // 32 x 32 tiles while 64 x 64 ones would leave compute units without one.  These take k tiles of 16: workgroups that
-    // share a unit hide each other's loads, and the padding of a short contraction is less (k tiles of 32 -> 16: 6144 x
-    // 2048 over 16 30.8 -> 23.6 us, over 80 57 -> 47, 4096 x 2048 over 1024 358 -> 350; 1024 x 1024 over 4096 430 -> 433)
+    // 64 x 64 tiles where they give every compute unit one; fewer go to the matrix instruction (gemm_f32.hip), except for
+    // short contractions over many results, which are bound by their stores (960 x 1024 over 16 5.6 us here, 6.0 there;
+    // over 48 7.7 and 8.2; over 80 11.1 and 8.8).  64 x 64 tiles take k tiles of 16: workgroups that share a unit hide each
+    // other's loads, and the padding of a short contraction is less (k tiles of 32 -> 16: 6144 x 2048 over 16 30.8 -> 23.6
+    // us, over 80 57 -> 47, 4096 x 2048 over 1024 358 -> 350)
     const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles < 256) gemm_f32_kernel<32, 64><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
-    else gemm_f32_kernel<64, 16><<<dim3(tiles), dim3(256), 0, st>>>(g);
+    if (tiles >= 256) {
+      gemm_f32_kernel<64, 16><<<dim3(tiles), dim3(256), 0, st>>>(g);
+    } else if (tiles > 64 && K <= 48) {
+      gemm_f32_kernel<32, 64><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
+    } else {
+      return gemm_f32_few_tiles(M, N, K, A, lda, a_kmajor, B, ldb, b_kmajor, C, ldc, bias, bias_dtype, resid, ldr,
+                                accumulate, alpha_dev, st);
+    }
     LS_CHECK_LAUNCH();
     return LS_OK;
   }
