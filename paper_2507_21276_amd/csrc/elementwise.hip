@@ -231,19 +231,45 @@ __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(int kind, const floa
   }
 }
 
-// Backward in one pass over the data, one wavefront per row and NB_ROWS rows per
+// eight parameters as they are in memory; the type is looked at when they are used, so that the loads of a row are all
+// requested before the first of them is waited for
+template <bool P32> struct RawParam {
+  u32x4 v[P32 ? 2 : 1];
+  __device__ __forceinline__ void load(const void* p, int c) {
+    const u32x4* q = (const u32x4*)((const char*)p + (size_t)c * (P32 ? 4 : 2));
+    v[0] = q[0];
+    if constexpr (P32) v[1] = q[1];
+  }
+  __device__ __forceinline__ void get(int dt, float (&o)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (P32) {
+        const uint32_t bits = v[i / 4][i % 4];
+        o[i] = __uint_as_float(bits);
+      } else {
+        const uint16_t h = (uint16_t)(v[0][i / 2] >> (i % 2 * 16));
+        o[i] = dt == LS_BF16 ? to_f(__builtin_bit_cast(bf16_t, h)) : to_f(__builtin_bit_cast(f16_t, h));
+      }
+    }
+  }
+};
+
+// Backward in one pass over the data, one wavefront per row and `rows` rows (8 or 16) per
 // 512-thread workgroup: the row's dh and xhat stay in registers between the two
 // row means and dx, each wave keeps its dgamma / dbeta column sums in registers
 // and the eight waves' sums are combined in a fixed order through LDS into
 // partial[workgroup][2][d] (RMSNorm leaves the dbeta half unwritten).  Needs d % 8 == 0, d <= 512 * NIT, 16-byte alignment.
-template <class TD, int KIND, int NIT>
+// PRE: a row's loads, those of the residual gradient and the parameters among them, are one round trip, none of them
+// behind a branch (columns past the end repeat the last eight).  Wider rows have no registers for that.  With
+// the finishing launch, 1024 rows of 768: 13.6 -> 10.1 us, 4096 rows 21.3 -> 19.0 (up to four round trips a row before).
+template <class TD, int KIND, int NIT, bool PRE, bool P32>
 __global__ __launch_bounds__(512) void norm_bwd_rows_kernel(const TD* dh, const float* x, const float* mean,
                                                             const float* rstd, const void* gamma, int pdt,
-                                                            int T, int d, const float* dres, float* dx,
+                                                            int T, int d, int rows, const float* dres, float* dx,
                                                             TD* dx16, float* partial) {
   extern __shared__ float sred[];  // [8][d]
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r0 = blockIdx.x * NB_ROWS, r1 = min(T, r0 + NB_ROWS);
+  const int r0 = blockIdx.x * rows, r1 = min(T, r0 + rows);
   constexpr int NB = KIND == 0 ? NIT : 1;
   float dg[NIT][8], db[NB][8];
 #pragma unroll
@@ -258,16 +284,34 @@ __global__ __launch_bounds__(512) void norm_bwd_rows_kernel(const TD* dh, const 
     const size_t off = (size_t)row * d;
     const float mu = KIND == 0 ? mean[row] : 0.f, r = rstd[row];
     Raw8<TD> g[NIT];
+    Raw8<float> dr[PRE ? NIT : 1];
+    RawParam<P32> gp[PRE ? NIT : 1];
     float xh[NIT][8];
     float s1 = 0.f, s2 = 0.f;
+    if constexpr (PRE) {
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
+        const int c = min(lane * 8 + it * 512, d - 8);
+        g[it].load(dh + off + c);
+        Ld8<float>::load(x + off + c, xh[it]);
+        gp[it].load(gamma, c);
+      }
+      if (dres)
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) dr[it].load(dres + off + min(lane * 8 + it * 512, d - 8));
+    }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int c = lane * 8 + it * 512;
       if (c < d) {
         float gam[8];
-        g[it].load(dh + off + c);
-        Ld8<float>::load(x + off + c, xh[it]);
-        load8_param(gamma, c, pdt, gam);
+        if constexpr (PRE) {
+          gp[it].get(pdt, gam);
+        } else {
+          g[it].load(dh + off + c);
+          Ld8<float>::load(x + off + c, xh[it]);
+          load8_param(gamma, c, pdt, gam);
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const float dxh = g[it].get(i) * gam[i];
@@ -284,8 +328,14 @@ __global__ __launch_bounds__(512) void norm_bwd_rows_kernel(const TD* dh, const 
       const int c = lane * 8 + it * 512;
       if (c < d) {
         float gam[8], o[8];
-        load8_param(gamma, c, pdt, gam);
-        if (dres) Ld8<float>::load(dres + off + c, o);
+        if constexpr (PRE) {
+          gp[it].get(pdt, gam);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) o[i] = dr[it].get(i);
+        } else {
+          load8_param(gamma, c, pdt, gam);
+          if (dres) Ld8<float>::load(dres + off + c, o);
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const float gi = g[it].get(i);
@@ -420,33 +470,42 @@ __global__ __launch_bounds__(256) void norm_bwd_finish_kernel(const float* parti
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-template <class TD, int KIND, int NIT>
+// Rows per workgroup of the one-pass kernel: one per wavefront while two would leave compute units without a workgroup or
+// with half of their registers idle; beyond, two, as every workgroup also sums its rows' columns and writes 2 d of them.
+// us with the finishing launch, one row -> two: d 768, 128 rows 7.4, 8.9; 1024 rows 10.1, 10.9; 1500 rows 11.7, 11.7; 2048
+// rows 13.4, 12.6; d 4096, 16 rows 14.6, 26.9; 1024 rows 29.5, 44.1; 2048 rows 37.2, 51.8; 3000 rows 61.6, 58.2.
+inline int norm_bwd_few_rows(int d) { return d <= 1024 ? 1280 : 2048; }
+inline int norm_bwd_rows_per_wg(int T, int d) { return T <= norm_bwd_few_rows(d) ? 8 : 16; }
+
+template <class TD, int KIND, int NIT, bool PRE>
 ls_status launch_norm_bwd_rows(const void* dh, const float* x, const float* mean, const float* rstd,
                                const void* gamma, int pdt, int T, int d, const float* dres, float* dx,
                                void* dx16, float* partial, hipStream_t st) {
-  static bool attr_set = false;
   const size_t lds = (size_t)8 * d * sizeof(float);
-  auto* kern = norm_bwd_rows_kernel<TD, KIND, NIT>;
-  if (!attr_set) {
-    LS_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 512 * NIT * 4));
-    attr_set = true;
-  }
-  kern<<<(T + NB_ROWS - 1) / NB_ROWS, 512, lds, st>>>((const TD*)dh, x, mean, rstd, gamma, pdt, T, d, dres, dx,
-                                                      (TD*)dx16, partial);
-  return LS_OK;
+  const int rows = norm_bwd_rows_per_wg(T, d);
+  auto go = [&](auto* kern, bool& attr_set) -> ls_status {
+    if (!attr_set) {
+      LS_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 512 * NIT * 4));
+      attr_set = true;
+    }
+    kern<<<(T + rows - 1) / rows, 512, lds, st>>>((const TD*)dh, x, mean, rstd, gamma, pdt, T, d, rows, dres, dx,
+                                                  (TD*)dx16, partial);
+    return LS_OK;
+  };
+  static bool set16 = false, set32 = false;
+  return PRE && pdt == LS_F32 ? go(norm_bwd_rows_kernel<TD, KIND, NIT, PRE, PRE>, set32)
+                              : go(norm_bwd_rows_kernel<TD, KIND, NIT, PRE, false>, set16);
 }
 
 template <class TD>
 ls_status launch_norm_bwd(int kind, const void* dh, const float* x, const float* mean, const float* rstd,
                           const void* gamma, int pdt, int T, int d, const float* dres, float* dx, void* dx16,
-                          float* partial, hipStream_t st) {
-  // LayerNorm's second set of column sums does not fit the register file beyond 2048 columns
-  const bool rows_ok = d <= (kind == 0 ? 2048 : 4096) && aligned16(dh) && aligned16(x) && aligned16(gamma) && aligned16(dx) &&
-                       aligned16(partial) && (!dres || aligned16(dres)) && (!dx16 || aligned16(dx16));
+                          float* partial, bool rows_ok, hipStream_t st) {
   if (rows_ok) {
-#define LS_NB(K, N) launch_norm_bwd_rows<TD, K, N>(dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, st)
-    if (kind == 0) return LS_NB(0, 4);
-    return d <= 2048 ? LS_NB(1, 4) : LS_NB(1, 8);
+#define LS_NB(K, N, P) launch_norm_bwd_rows<TD, K, N, P>(dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, st)
+    if (d <= 1024) return kind == 0 ? LS_NB(0, 2, true) : LS_NB(1, 2, true);
+    if (kind == 0) return LS_NB(0, 4, false);
+    return d <= 2048 ? LS_NB(1, 4, false) : LS_NB(1, 8, false);
 #undef LS_NB
   }
   const int nchunk = (T + NB_ROWS - 1) / NB_ROWS;
@@ -730,7 +789,9 @@ ls_status lsk_norm_fwd(int kind, const float* x, int T, int d, const void* gamma
 }
 
 size_t lsk_norm_bwd_partial_floats(int T, int d) {
-  return (size_t)((T + NB_ROWS - 1) / NB_ROWS) * 2 * d + 2 * (size_t)T;
+  // never less for more rows: a workspace sized for T holds every shorter call
+  const int few = norm_bwd_few_rows(d), by8 = ((T < few ? T : few) + 7) / 8, by16 = (T + NB_ROWS - 1) / NB_ROWS;
+  return (size_t)(by8 > by16 ? by8 : by16) * 2 * d + 2 * (size_t)T;
 }
 
 ls_status lsk_norm_bwd_scaled(int kind, const void* dh, int dhdt, const float* x, const float* mean,
@@ -743,12 +804,15 @@ ls_status lsk_norm_bwd_scaled(int kind, const void* dh, int dhdt, const float* x
   LS_REQUIRE(d % 8 == 0, "norm_bwd: d_model must be a multiple of 8");
   LS_REQUIRE(!dx16 || dx16dt == dhdt, "norm_bwd: the 16-bit copy of dx must have the type of dh");
   hipStream_t st = (hipStream_t)stream;
-  if (dhdt == LS_F32) LS_TRY(launch_norm_bwd<float>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, st));
-  else if (dhdt == LS_BF16) LS_TRY(launch_norm_bwd<bf16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, st));
-  else LS_TRY(launch_norm_bwd<f16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, st));
+  // LayerNorm's second set of column sums does not fit the register file beyond 2048 columns
+  const bool rows_ok = d <= (kind == 0 ? 2048 : 4096) && aligned16(dh) && aligned16(x) && aligned16(gamma) && aligned16(dx) &&
+                       aligned16(partial) && (!dres || aligned16(dres)) && (!dx16 || aligned16(dx16));
+  if (dhdt == LS_F32) LS_TRY(launch_norm_bwd<float>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, rows_ok, st));
+  else if (dhdt == LS_BF16) LS_TRY(launch_norm_bwd<bf16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, rows_ok, st));
+  else LS_TRY(launch_norm_bwd<f16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, rows_ok, st));
   LS_CHECK_LAUNCH();
   if (dgamma || dbeta) {
-    const int nchunk = (T + NB_ROWS - 1) / NB_ROWS;
+    const int rows = rows_ok ? norm_bwd_rows_per_wg(T, d) : NB_ROWS, nchunk = (T + rows - 1) / rows;
     norm_bwd_finish_kernel<<<(d + 31) / 32, 256, 0, st>>>(partial, nchunk, d, dgamma,
                                                             kind == 0 ? dbeta : nullptr, accumulate, alpha_dev);
     LS_CHECK_LAUNCH();

@@ -105,6 +105,33 @@ def test_fp32_products_of_few_tiles(M, N, K, offset):
             assert_close(host(out), ref, max(2e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}")
 
 
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("T,d", [(1, 8), (9, 520), (1280, 512), (1281, 1024), (2049, 1032)])
+@pytest.mark.parametrize("name,pname", [("f16", "f16"), ("bf16", "f32"), ("f32", "bf16")])
+def test_norm_backward_over_rows_of_a_workgroup(kind, T, d, name, pname):
+    """One and two rows per wavefront at the line between them, columns that end inside a wavefront's load, parameters of
+    every type beside operands of another; with and without a residual gradient.  fp32 sums over d and over T rows."""
+    x, dh, dres = S.normal(3, "x", (T, d)), q(S.normal(3, "dh", (T, d)), name), S.normal(3, "dres", (T, d))
+    g = q(1.0 + S.normal(3, "g", (d,), 0.1), pname)
+    mean, rstd = S.normal(3, "m", (T,), 0.1), 1.0 + 0.1 * np.abs(S.normal(3, "r", (T,)))
+    f = lambda a: torch.from_numpy(np.asarray(a, np.float32)).cuda().double()  # noqa: E731
+    xh = (f(x) - (f(mean)[:, None] if kind == 0 else 0.0)) * f(rstd)[:, None]
+    dxh = f(dh) * f(g)
+    ref = f(rstd)[:, None] * (dxh - (dxh.mean(1, keepdim=True) if kind == 0 else 0.0) - xh * (dxh * xh).mean(1, keepdim=True))
+    dg, db = (torch.empty(d, dtype=torch.float32, device="cuda") for _ in range(2))
+    dx, dx16 = torch.empty(T, d, dtype=torch.float32, device="cuda"), torch.empty(T, d, dtype=DT[name], device="cuda")
+    for res in (dres, None):
+        Bd.lsk_norm_bwd(kind, dev(dh, DT[name]), dev(x, torch.float32), dev(mean, torch.float32), dev(rstd, torch.float32),
+                        dev(g, DT[pname]), None if res is None else dev(res, torch.float32), dx, dx16, dg,
+                        db if kind == 0 else None, False)
+        want = (ref if res is None else ref + f(res)).cpu().numpy()
+        assert_close(host(dx), want, 1e-5, "dx", atol=1e-5)
+        assert_close(host(dx16), want, 1e-5 + out_rounding_bound(want, name), "dx in the operand type", atol=1e-5)
+        assert_close(host(dg), (f(dh) * xh).sum(0).cpu().numpy(), 1e-5, "dgamma")
+        if kind == 0:
+            assert_close(host(db), f(dh).sum(0).cpu().numpy(), 1e-5, "dbeta")
+
+
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 64, 65, 130])
 def test_fp32_attention_over_batches_of_keys(dh, L):
