@@ -105,9 +105,6 @@ __device__ __forceinline__ typename Mf<T>::V8 frag_value(const Frag<T, KMAJOR>& 
 }
 
 // MODE 0: C (16-bit) = acc + bias;  1: C (fp32) = resid + acc + bias;  2: C (fp32) = acc;  4: C (fp32) += acc;
-// MODE 3: as 0 without bias, and the half-split rotary embedding (head_dim 128) applied to the
-//         columns below rope_cols: a wavefront's 128 columns are one head, so the pair
-//         (c, c + 64) sits in accumulator tiles j and j + 2 of the same lane
 template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   typedef typename Mf<T>::V8 V8;
@@ -297,7 +294,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   // chunks of a row XOR-permuted by the row number, and writes it out as full rows; residual
   // and accumulation operands are read with the same coalesced pattern.
   typedef typename Mf<T>::V4 V4;
-  constexpr int ESZ = (MODE == 0 || MODE == 3) ? 2 : 4;
+  constexpr int ESZ = MODE == 0 ? 2 : 4;
   constexpr int REGION = (BM + BN) * 128 * 2 / 4;   // bytes of LDS per wavefront
   constexpr int ROWB = WN * ESZ;                    // bytes of a staged row
   constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
@@ -360,60 +357,26 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
       const int r = ii * 32 + row_in;
       char* srow = stg + r * ROWB;
       const int sw = r & (CPR - 1);
-      if constexpr (MODE == 3) {
-        if constexpr (TJ == 4) {
-          const int m = min(m0 + wm + i * 32 + row_in, g.M - 1);   // rows past the edge are staged, never stored
-          const bool rot = n0 + wn < g.rope_cols;   // q or k section: uniform over the wavefront
-          const float* tab = g.rope_table + (long)g.rope_pos[m] * 128 + 8 * hf;   // 64 (cos, sin) pairs
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < TJ; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              V4 lo, hi;
-              if (rot) {
-                const f32x4 cs0 = *(const f32x4*)(tab + (j * 32 + 8 * q) * 2);
-                const f32x4 cs1 = *(const f32x4*)(tab + (j * 32 + 8 * q) * 2 + 4);
+        for (int q = 0; q < 4; ++q) {
+          f32x4 v;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const float c = e < 2 ? cs0[2 * e] : cs1[2 * (e - 2)];
-                  const float sn = e < 2 ? cs0[2 * e + 1] : cs1[2 * (e - 2) + 1];
-                  const float a = acc[i][j][4 * q + e], bb = acc[i][j + 2][4 * q + e];
-                  lo[e] = from_f<T>(a * c - bb * sn);
-                  hi[e] = from_f<T>(bb * c + a * sn);
-                }
-              } else {
+          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e] * alpha;
+          if constexpr (MODE == 0 || MODE == 1) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  lo[e] = from_f<T>(acc[i][j][4 * q + e]);
-                  hi[e] = from_f<T>(acc[i][j + 2][4 * q + e]);
-                }
-              }
-              *(u32x2_a*)(srow + (((j * 4 + q) ^ sw) * 16) + hf * 8) = __builtin_bit_cast(u32x2_t, lo);
-              *(u32x2_a*)(srow + (((j * 4 + q + 8) ^ sw) * 16) + hf * 8) = __builtin_bit_cast(u32x2_t, hi);
-            }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e] * alpha;
-            if constexpr (MODE == 0 || MODE == 1) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += bv[j][q][e];
-            }
-            if constexpr (ESZ == 2) {
-              V4 o;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[e] = from_f<T>(v[e]);
-              *(u32x2_a*)(srow + (((j * 4 + q) ^ sw) * 16) + hf * 8) = __builtin_bit_cast(u32x2_t, o);
-            } else {
-              *(f32x4_a*)(srow + (((j * 8 + 2 * q + hf) ^ sw) * 16)) = v;
-            }
+            for (int e = 0; e < 4; ++e) v[e] += bv[j][q][e];
           }
-      }
+          if constexpr (ESZ == 2) {
+            V4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = from_f<T>(v[e]);
+            *(u32x2_a*)(srow + (((j * 4 + q) ^ sw) * 16) + hf * 8) = __builtin_bit_cast(u32x2_t, o);
+          } else {
+            *(f32x4_a*)(srow + (((j * 8 + 2 * q + hf) ^ sw) * 16)) = v;
+          }
+        }
     }
     // full rows out: 64 / CPR rows per instruction, 16 bytes per lane
     constexpr int NIT = ROWS_P * CPR / 64, GRP = NIT % 8 == 0 ? 8 : NIT;
@@ -499,31 +462,30 @@ ls_status launch(const DmaArgs& g, hipStream_t st, int splits = 1) {
 // gradient (k-strided x k-strided, fp32 output)
 template <class T, int BM, int BN>
 ls_status dispatch_layout(const DmaArgs& g, hipStream_t st) {
-  if (g.rope_table) {
-    if (BM == 256 && g.a_kmajor && g.b_kmajor && g.c_dtype != LS_F32 && !g.bias)
-      return launch<T, 256, 256, true, true, 3>(g, st);
-    return LS_ESTATE;
-  }
+  if (g.rope_table) return LS_ESTATE;
   const int mode = g.c_dtype != LS_F32 ? 0 : (g.resid ? 1 : (g.accumulate ? 4 : 2));
   if (mode >= 2 && g.bias) return LS_ESTATE;
   if (mode == 1 && g.accumulate) return LS_ESTATE;
-  if (g.a_kmajor && g.b_kmajor && mode == 0) return launch<T, BM, BN, true, true, 0>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 1) return launch<T, BM, BN, true, true, 1>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 2) return launch<T, BM, BN, true, true, 2>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 4) return launch<T, BM, BN, true, true, 4>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 0) return launch<T, BM, BN, true, false, 0>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 2) return launch<T, BM, BN, true, false, 2>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 4) return launch<T, BM, BN, true, false, 4>(g, st);
+  if constexpr (BM == 128) {
+    if (g.a_kmajor && g.b_kmajor && mode == 0) return launch<T, BM, BN, true, true, 0>(g, st);
+    if (g.a_kmajor && g.b_kmajor && mode == 1) return launch<T, BM, BN, true, true, 1>(g, st);
+    if (g.a_kmajor && g.b_kmajor && mode == 2) return launch<T, BM, BN, true, true, 2>(g, st);
+    if (g.a_kmajor && g.b_kmajor && mode == 4) return launch<T, BM, BN, true, true, 4>(g, st);
+    if (g.a_kmajor && !g.b_kmajor && mode == 0) return launch<T, BM, BN, true, false, 0>(g, st);
+    if (g.a_kmajor && !g.b_kmajor && mode == 2) return launch<T, BM, BN, true, false, 2>(g, st);
+    if (g.a_kmajor && !g.b_kmajor && mode == 4) return launch<T, BM, BN, true, false, 4>(g, st);
+  }
   if (!g.a_kmajor && !g.b_kmajor && mode == 2) return launch<T, BM, BN, false, false, 2>(g, st);
   if (!g.a_kmajor && !g.b_kmajor && mode == 4) return launch<T, BM, BN, false, false, 4>(g, st);
   return LS_ESTATE;
 }
 
-// 256 x 256 tiles when they still give most compute units a workgroup, else 128 x 128
+// Weight gradients: 256 x 256 tiles when they still give most compute units a workgroup, else 128 x 128.  The other
+// layouts come here where the 16x16x32 kernel leaves them to the 128 x 128 tiles.
 template <class T>
 ls_status dispatch(const DmaArgs& g, hipStream_t st) {
   const long big = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (big >= 160) return dispatch_layout<T, 256, 256>(g, st);
+  if (!g.a_kmajor && big >= 160) return dispatch_layout<T, 256, 256>(g, st);
   return dispatch_layout<T, 128, 128>(g, st);
 }
 

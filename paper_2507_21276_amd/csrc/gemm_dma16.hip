@@ -1,22 +1,22 @@
-// The 256 x 256 x 64 direct-to-LDS GEMM with the 16x16x32 MFMA.
+// The large-tile direct-to-LDS GEMM with the 16x16x32 MFMA: 256 x 256 x 64 tiles, or 192 or 128 rows by 256 (rows_per_tile).
 //
-// Same tiles, LDS layouts, loads, barrier and epilogue staging as gemm_dma_kernel (gemm_dma.hip);
+// Same LDS layouts, loads, barrier and epilogue staging as gemm_dma_kernel (gemm_dma.hip);
 // what differs is the matrix instruction.  On real (Gaussian) operands the chip holds its power limit
 // by clocking down, and a register-only loop of 16x16x32 MFMAs sustains 15 % more than one of
 // 32x32x16 MFMAs there (1730 - 1870 against 1500 - 1610 TFLOP/s; on all-zero operands both reach the
 // same 2230 - 2330): per FLOP the 16x16x32 form moves half the accumulator data.
 //
-// A wavefront owns 128 x 128 of the tile: 8 x 8 blocks of 16 x 16, 64 accumulators of 4 registers.
+// A wavefront of a 256 x 256 tile owns 128 x 128 of it: 8 x 8 blocks of 16 x 16, 64 accumulators of 4 registers.
 // Fragments: 16 rows x 32 k, lane -> row lane & 15, k 8 (lane >> 4) .. + 7: one 16-byte LDS read from
 // a k-major tile, two transposing reads (4 k x 16 rows per 16 lanes) from a k-strided one.
 // The k tile is walked in four quarters: (k 0..31, rows 0..63), (k 0..31, rows 64..127), then the
 // same for k 32..63; a quarter is 32 MFMAs and needs 4 A fragments and the 8 B fragments of its k half.
 // The quarters take the place of the four k sub-steps of gemm_dma_kernel: fragments of the next quarter
 // are read under the MFMAs of the present one, the workgroup barrier sits before the last quarter, and
-// the loads of the tile after the next are issued during the last quarter and the first of the next tile.
+// the loads of the tile after the next are issued during the last quarter and the first of the next tile.  ST: LDS buffers
+// (with more than two, the tile ST - 1 ahead in place of the next).
 #include "gemm_dma_common.h"
-#include <cstdlib>
-#include <cstring>
+#include <math.h>
 
 namespace {
 
@@ -121,11 +121,12 @@ static_assert(32 * 3 / 4 >= 12, "one read per gap");
 // MODE 3: as 0 without bias, and the half-split rotary embedding (head_dim 128) applied to the
 //         columns below rope_cols: a wavefront's 128 columns are one head, so the pair
 //         (c, c + 64) sits in accumulator blocks j and j + 4 of the same lane
-template <class T, bool AK, bool BK, int MODE>
+template <class T, int BM, int ST, bool AK, bool BK, int MODE>
 __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
   typedef typename Mf16<T>::V8 V8;
   typedef typename Mf16<T>::V4 V4;
-  constexpr int BM = 256, BN = 256;
+  constexpr int BN = 256;
+  static_assert(AK || BM == 256, "a k-strided tile has a power of two of chunks per k row");
   constexpr int WM = BM / 2, WN = BN / 2;       // wavefront tile
   constexpr int TI = WM / 16, TJ = WN / 16;     // 16 x 16 blocks per wavefront
   constexpr int HI = TI / 2;                    // row blocks per quarter
@@ -169,24 +170,32 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
     a_base += kt0 * a_step;
     b_base += kt0 * b_step;
   }
-  issue_tile<BM>(a_base, a_off, smem, wave);
-  issue_tile<BN>(b_base, b_off, smem + A_BYTES, wave);
-
   constexpr int NM = HI * TJ;            // MFMAs per quarter
   constexpr int NLD = (BM + BN) / 32;    // direct-to-LDS loads per tile and wavefront
   constexpr int LPK = NLD / 2;           // issued over two quarters
   constexpr SpreadPlan<NM, HI, LPK> plan_a{};        // quarters that read the other row half's A fragments only
   constexpr SpreadPlan<NM, HI + TJ, LPK> plan_ab{};  // quarters that also read the next k half's B fragments
+  // tiles 0 .. ST - 2, and what the last quarter of the tile before the first would have issued of the next
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t) {
+    const int tc = min(t, nk - 1);
+    issue_tile<BM>(a_base + tc * a_step, a_off, smem + t * BUF_BYTES, wave);
+    issue_tile<BN>(b_base + tc * b_step, b_off, smem + t * BUF_BYTES + A_BYTES, wave);
+  }
   {
-    // what the last quarter of the tile before the first would have issued
-    const int t1 = nk > 1 ? 1 : 0;
+    const int tc = min(ST - 1, nk - 1);
 #pragma unroll
     for (int l = 0; l < LPK; ++l)
-      issue_one<BM, BN>(l, a_base + t1 * a_step, a_off, b_base + t1 * b_step, b_off, smem + BUF_BYTES,
-                        smem + BUF_BYTES + A_BYTES, wave);
+      issue_one<BM, BN>(l, a_base + tc * a_step, a_off, b_base + tc * b_step, b_off, smem + (ST - 1) * BUF_BYTES,
+                        smem + (ST - 1) * BUF_BYTES + A_BYTES, wave);
   }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+  if constexpr (ST == 2) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  } else {
+    wait_loads<(ST - 2) * NLD + LPK>();   // tile 0 has landed
+    wait_lds_and_barrier();
+  }
   Frag16<T, AK> fa[2][HI];     // by quarter parity
   Frag16<T, BK> fb[2][TJ];     // by k half
 #pragma unroll
@@ -194,14 +203,19 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
 #pragma unroll
   for (int j = 0; j < TJ; ++j) read_frag16<T, BK, BN>(fb[0][j], smem + A_BYTES, wn + j * 16, 0, lane);
 
+  int ring = 0;   // buffer of tile kt where there are more than two
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
+    const int cur = ST == 2 ? kt & 1 : ring;
+    const int nxt = ST == 2 ? cur ^ 1 : cur + 1 == ST ? 0 : cur + 1, prv = ST == 2 ? nxt : cur == 0 ? ST - 1 : cur - 1;
+    ring = nxt;
     const char* la = smem + cur * BUF_BYTES;
     const char* lb = la + A_BYTES;
-    char* na = smem + (cur ^ 1) * BUF_BYTES;
+    char* na = smem + nxt * BUF_BYTES;   // the next tile's
     char* nb = na + A_BYTES;
+    char* pa = smem + prv * BUF_BYTES;   // the one this tile's first quarter fills up (ST = 2: the next tile's)
+    char* pb = pa + A_BYTES;
     // tiles after the last are the last again: fetched, never multiplied
-    const int t1 = min(kt + 1, nk - 1), t2 = min(kt + 2, nk - 1);
+    const int t1 = min(kt + ST - 1, nk - 1), t2 = min(kt + ST, nk - 1);
     const char* ga1 = a_base + t1 * a_step;
     const char* gb1 = b_base + t1 * b_step;
     const char* ga2 = a_base + t2 * a_step;
@@ -212,8 +226,13 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
       wait_frags16<T, AK, HI>(fa[q & 1]);
       if (half == 0) wait_frags16<T, BK, TJ>(fb[kh]);
       if (q == 3) {
-        __builtin_amdgcn_s_waitcnt(0);   // this wavefront's share of the next tile has landed
-        __syncthreads();
+        if constexpr (ST == 2) {
+          __builtin_amdgcn_s_waitcnt(0);   // this wavefront's share of the next tile has landed
+          __syncthreads();
+        } else {
+          wait_loads<(ST - 2) * NLD>();
+          wait_lds_and_barrier();
+        }
       }
       V8 va[HI], vb[TJ];
 #pragma unroll
@@ -249,7 +268,7 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
           const int l = nhalf == 1 ? plan_a.load_at[m] : plan_ab.load_at[m];
           if (l >= 0)
             issue_one<BM, BN>((ahead ? 0 : LPK) + l, ahead ? ga2 : ga1, a_off, ahead ? gb2 : gb1, b_off,
-                              ahead ? (char*)la : na, ahead ? (char*)lb : nb, wave);
+                              ahead ? (char*)la : pa, ahead ? (char*)lb : pb, wave);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -267,7 +286,7 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
   // XOR-permuted by the row number, and writes it out as full rows; residual and accumulation operands
   // are read with the same coalesced pattern.
   constexpr int ESZ = (MODE == 0 || MODE == 3 || MODE == 5) ? 2 : 4;
-  constexpr int REGION = (BM + BN) * 128 * 2 / 4;   // bytes of LDS per wavefront
+  constexpr int REGION = (BM + BN) * 128 * ST / 4 / 1024 * 1024;   // bytes of LDS per wavefront
   constexpr int ROWB = WN * ESZ;                    // bytes of a staged row
   constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
   constexpr int NPASS = (WM * ROWB + REGION - 1) / REGION;
@@ -474,43 +493,84 @@ __global__ __launch_bounds__(256) void gemm_dma16_kernel(DmaArgs g) {
   }
 }
 
-template <class T, bool AK, bool BK, int MODE>
-ls_status launch16(DmaArgs g, hipStream_t st, int splits = 1) {
+template <class T, int BM, int ST, bool AK, bool BK, int MODE>
+ls_status launch16_bm(DmaArgs g, hipStream_t st, int splits) {
   static bool attr_set = false;
-  const int lds = 2 * (256 + 256) * 128;
+  const int lds = ST * (BM + 256) * 128;
   if (!attr_set) {
-    LS_CHECK_HIP(hipFuncSetAttribute((const void*)gemm_dma16_kernel<T, AK, BK, MODE>,
+    LS_CHECK_HIP(hipFuncSetAttribute((const void*)gemm_dma16_kernel<T, BM, ST, AK, BK, MODE>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
-  g.tiles_m = (g.M + 255) / 256;
+  g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + 255) / 256;
-  gemm_dma16_kernel<T, AK, BK, MODE><<<dim3(g.tiles_m * g.tiles_n, splits), 256, lds, st>>>(g);
+  gemm_dma16_kernel<T, BM, ST, AK, BK, MODE><<<dim3(g.tiles_m * g.tiles_n, splits), 256, lds, st>>>(g);
   LS_CHECK_LAUNCH();
   return LS_OK;
 }
 
+// Rows of the tiles for an M x N result over nk k tiles, or 0 where the 128 x 128 tiles of gemm_dma.hip are the better
+// ones.  A launch takes as many rounds as its workgroups fill the 256 compute units, at so much per k tile and so much for
+// the launch, the first loads and the epilogue (us; operands from HBM, as a stage's weights are):
+//            256 x 256      192 x 256      128 x 256, three buffers      128 x 128
+//            1.40           1.18           0.90                          0.60 alone, 0.85 - 1.15 two on a unit
+// Fewer rows a tile cost more per result (a full chip: 1.28, 1.19, 1.15 and 1.2 PFLOP/s at 4096 rows), but a round that is
+// nearly empty costs a whole one.  Same process, 256 x 256 or 128 x 128 (whichever was taken) -> taken now: 22016 columns
+// over 4096: 890 rows 181 -> 170 us (192 rows a tile), 1500 rows 268 -> 237 (192), 1024 rows 182 -> 177 (128); 12288 columns:
+// 2600 rows 258 -> 228 (192), 512 rows 63 -> 61 (128); 4096 columns over 11008 with the residual: 1500 rows 251 -> 163
+// (128), 2048 rows 274 -> 181 (128), 3000 rows 249 -> 237 (192); input gradient, 11008 columns over 4096: 1500 rows 176 ->
+// 147 (192).  Three buffers for 128 x 256: 54 -> 46 us for one round over 4096 (a tile's arithmetic is too short to cover
+// its successor's latency).
+// `after`: what else the 128 x 128 tiles would need (a pass that the larger ones have in their epilogue).
+int rows_per_tile(long M, long N, int nk, bool adds, float after = 0.f) {
+  const long tn = (N + 255) / 256;
+  auto rounds = [](long wgs) { return (float)((wgs + 255) / 256); };
+  const float us256 = rounds((M + 255) / 256 * tn) * ((float)nk * 1.40f + 8.f);
+  const float us192 = rounds((M + 191) / 192 * tn) * ((float)nk * 1.18f + 6.5f);
+  const float us128w = rounds((M + 127) / 128 * tn) * ((float)nk * 0.90f + 5.f);
+  const long t128 = (M + 127) / 128 * ((N + 127) / 128);
+  float us128;
+  if (t128 <= 256) us128 = (float)nk * 0.6f + 4.f;
+  else if (adds) us128 = rounds(t128) * ((float)nk * 0.6f + 5.f);   // the old values take the registers of the second workgroup
+  else if (t128 <= 512) us128 = (float)nk * (0.85f + 0.3f * (float)(t128 - 256) / 256.f) + 4.f;
+  else us128 = (float)((t128 + 511) / 512) * ((float)nk * 0.95f + 4.f);
+  us128 += after;
+  const float best = fminf(fminf(us256, us192), us128w);
+  if (us128 <= best) return 0;
+  return best == us256 ? 256 : best == us192 ? 192 : 128;
+}
+
+// an elementwise pass over so many bytes
+float pass_us(long bytes) { return 4.f + (float)bytes / 4e6f; }
+
+template <class T, bool AK, bool BK, int MODE>
+ls_status launch16(const DmaArgs& g, int rows, hipStream_t st, int splits = 1) {
+  if (rows == 192) return launch16_bm<T, 192, 2, AK, BK, MODE>(g, st, splits);
+  if (rows == 128) return launch16_bm<T, 128, 3, AK, BK, MODE>(g, st, splits);
+  return launch16_bm<T, 256, 2, AK, BK, MODE>(g, st, splits);
+}
+
 template <class T>
-ls_status dispatch16(const DmaArgs& g, hipStream_t st) {
+ls_status dispatch16(const DmaArgs& g, int rows, hipStream_t st) {
   if (g.rope_table) {
-    if (g.a_kmajor && g.b_kmajor && g.c_dtype != LS_F32 && !g.bias) return launch16<T, true, true, 3>(g, st);
+    if (g.a_kmajor && g.b_kmajor && g.c_dtype != LS_F32 && !g.bias) return launch16<T, true, true, 3>(g, rows, st);
     return LS_ESTATE;
   }
   if (g.glu_pre) {
     if (g.a_kmajor && !g.b_kmajor && g.c_dtype != LS_F32 && !g.bias && !g.alpha && g.N % 8 == 0)
-      return launch16<T, true, false, 5>(g, st);
+      return launch16<T, true, false, 5>(g, rows, st);
     return LS_ESTATE;
   }
   const int mode = g.c_dtype != LS_F32 ? 0 : (g.resid ? 1 : (g.accumulate ? 4 : 2));
   if (mode >= 2 && g.bias) return LS_ESTATE;
   if (mode == 1 && g.accumulate) return LS_ESTATE;
-  if (g.a_kmajor && g.b_kmajor && mode == 0) return launch16<T, true, true, 0>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 1) return launch16<T, true, true, 1>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 2) return launch16<T, true, true, 2>(g, st);
-  if (g.a_kmajor && g.b_kmajor && mode == 4) return launch16<T, true, true, 4>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 0) return launch16<T, true, false, 0>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 2) return launch16<T, true, false, 2>(g, st);
-  if (g.a_kmajor && !g.b_kmajor && mode == 4) return launch16<T, true, false, 4>(g, st);
+  if (g.a_kmajor && g.b_kmajor && mode == 0) return launch16<T, true, true, 0>(g, rows, st);
+  if (g.a_kmajor && g.b_kmajor && mode == 1) return launch16<T, true, true, 1>(g, rows, st);
+  if (g.a_kmajor && g.b_kmajor && mode == 2) return launch16<T, true, true, 2>(g, rows, st);
+  if (g.a_kmajor && g.b_kmajor && mode == 4) return launch16<T, true, true, 4>(g, rows, st);
+  if (g.a_kmajor && !g.b_kmajor && mode == 0) return launch16<T, true, false, 0>(g, rows, st);
+  if (g.a_kmajor && !g.b_kmajor && mode == 2) return launch16<T, true, false, 2>(g, rows, st);
+  if (g.a_kmajor && !g.b_kmajor && mode == 4) return launch16<T, true, false, 4>(g, rows, st);
   // Both operands k-strided (weight gradients): left to the 32x32x16 kernel.  Every fragment is two
   // transposing reads there, 24 in a quarter of 32 short MFMAs, and this kernel measured 8 - 10 % slower on
   // those shapes (faster by 5 - 12 % on the other two layouts), also with the LDS reads free of bank conflicts.
@@ -519,7 +579,7 @@ ls_status dispatch16(const DmaArgs& g, hipStream_t st) {
 
 }  // namespace
 
-// The large-tile GEMM for problems with enough 256 x 256 tiles; LS_ESTATE (error text untouched) when the
+// The large-tile GEMM for problems with enough large tiles (rows_per_tile); LS_ESTATE (error text untouched) when the
 // shape or the combination of layouts is outside what this kernel covers.  Arguments as gemm_dma_try, whose
 // checks of alignment and sizes have run before this is called.
 ls_status gemm_dma16_try(int op_dtype, int M, int N, int K, const void* A, long lda, int a_kmajor, const void* B,
@@ -527,13 +587,21 @@ ls_status gemm_dma16_try(int op_dtype, int M, int N, int K, const void* A, long 
                          const float* resid, long ldr, int accumulate, const float* alpha, const int32_t* rope_pos,
                          const float* rope_table, int rope_cols, hipStream_t st) {
   if (K % TK != 0 || M < 64 || N < 64) return LS_ESTATE;
-  const long big = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (big < 160) return LS_ESTATE;
+  const int rows = rows_per_tile(M, N, K / TK, c_dtype == LS_F32 && (resid || accumulate),
+                                 rope_table ? pass_us((long)M * rope_cols * 4) : 0.f);
+  if (!rows) return LS_ESTATE;
   DmaArgs g{M, N, K, A, lda, a_kmajor, B, ldb, b_kmajor, C, ldc, c_dtype, bias, bias_dtype, resid, ldr,
             accumulate, alpha, 0, 0, 0, rope_pos, rope_table, rope_cols};
-  if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, st);
-  if (op_dtype == LS_F16) return dispatch16<f16_t>(g, st);
+  if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, rows, st);
+  if (op_dtype == LS_F16) return dispatch16<f16_t>(g, rows, st);
   return LS_ESTATE;
+}
+
+// Whether the QKV projection of T rows takes tiles that have the rotary embedding in their epilogue.  `pages`: a serving
+// call, whose page-write kernel can rotate as well, so that only its traffic is saved and no launch.
+bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim, bool pages) {
+  return head_dim == 128 && T >= 256 && (op_dtype == LS_BF16 || op_dtype == LS_F16) &&
+         rows_per_tile(T, 3L * d, d / TK, false, pages ? (float)T * d * 8.f / 4e6f : pass_us((long)T * d * 8)) != 0;
 }
 
 // Partial products [splits][M][N] (fp32) of the forward layout, whatever the number of tiles.  The caller has checked
@@ -543,8 +611,8 @@ ls_status gemm_dma16_partials(int op_dtype, int M, int N, int K, const void* A, 
   DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
             nullptr, 0};
   g.split_stride = (long)M * N;
-  if (op_dtype == LS_BF16) return launch16<bf16_t, true, true, 2>(g, st, splits);
-  if (op_dtype == LS_F16) return launch16<f16_t, true, true, 2>(g, st, splits);
+  if (op_dtype == LS_BF16) return launch16<bf16_t, true, true, 2>(g, 256, st, splits);
+  if (op_dtype == LS_F16) return launch16<f16_t, true, true, 2>(g, 256, st, splits);
   return LS_ESTATE;
 }
 
@@ -558,13 +626,13 @@ ls_status gemm_dma16_swiglu_bwd_try(int op_dtype, int M, int N, int K, const voi
   if (ldy % 8 != 0 || ldw % 8 != 0 || (uintptr_t)dY % 16 != 0 || (uintptr_t)W % 16 != 0 || (uintptr_t)pre % 16 != 0 ||
       (uintptr_t)grad % 16 != 0)
     return LS_ESTATE;
-  const long big = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (big < 160) return LS_ESTATE;
+  const int rows = rows_per_tile(M, N, K / TK, false);   // as the product alone: the two routes give the same bits
+  if (!rows) return LS_ESTATE;
   DmaArgs g{M, N, K, dY, ldy, 1, W, ldw, 0, grad, 2L * N, op_dtype, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0,
             nullptr, nullptr, 0};
   g.glu_pre = pre;
   g.glu_grad = grad;
-  if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, st);
-  if (op_dtype == LS_F16) return dispatch16<f16_t>(g, st);
+  if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, rows, st);
+  if (op_dtype == LS_F16) return dispatch16<f16_t>(g, rows, st);
   return LS_ESTATE;
 }

@@ -131,7 +131,7 @@ ls_status lsk_gemm_ws(int, int, int, int, const void*, long, const void*, long, 
 ls_status lsk_gemm_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*, void*);
 ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, const void*, void*, void*, void*);
 }
-bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim);
+bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim, bool pages);
 size_t gemm_dma_wgrad_scratch_floats(long M, long N);
 bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
 ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
@@ -424,7 +424,7 @@ ls_status block_forward(const ls_stage* s, int l, int T, const FwdBufs& f, const
   // kernel.  Serving: in the epilogue only where it is fused there; otherwise the kernel that writes K and V
   // to the pages rotates q and k in the same pass (a prompt chunk of 512 rows has too few tiles for the fused
   // epilogue, and a rotary kernel of its own before the page write cost 13 us per block).
-  const bool roped = !gpt && mt != LS_F32 && (!kv || gemm_qkv_rope_fuses(mt, T, d, c.head_dim));
+  const bool roped = !gpt && mt != LS_F32 && (!kv || gemm_qkv_rope_fuses(mt, T, d, c.head_dim, true));
   // Serving calls whose projection is split over k: one kernel sums the parts, rotates q and k and writes the pages (in
   // place of a reduce kernel and the rotary / page kernel).  LS_ESTATE from the split-K launcher means "this shape is
   // not split": the plain path runs instead.  Any other status is a failure of the launch itself and ends the call.

@@ -132,6 +132,66 @@ def test_norm_backward_over_rows_of_a_workgroup(kind, T, d, name, pname):
             assert_close(host(db), f(dh).sum(0).cpu().numpy(), 1e-5, "dbeta")
 
 
+@pytest.mark.parametrize("name", ["f16", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(3000, 3848, 192),    # 16 x 16 tiles of 192 x 256, ragged on both sides
+                                   (1915, 4104, 384),    # 15 x 17 of 128 x 256, six k tiles through three buffers
+                                   (2000, 4000, 64), (2000, 4000, 128)])   # with something to add: 128 x 256, one and two k tiles
+def test_products_of_192_and_128_row_tiles(name, M, N, K):
+    """Every epilogue and both layouts of the 16x16x32 kernel's smaller tiles, every element against float64.  fp32 sums of K
+    products of 16-bit operands; the SwiGLU epilogue bit for bit against the product followed by the element-wise kernel."""
+    dt, dev_ = DT[name], "cuda"
+    A, W, Bk = (S.normal_torch(31, n, shape, std, dtype=dt) for n, shape, std in
+                (("A", (M, K), 1.0), ("W", (N, K), 0.05), ("Bk", (K, N), 0.05)))
+    R, b = S.normal_torch(31, "R", (M, N), 1.0, dtype=torch.float32), S.normal_torch(31, "b", (N,), 1.0, dtype=torch.bfloat16)
+    fwd, dgr = A.double() @ W.double().T.contiguous(), A.double() @ Bk.double()
+    full = lambda d, v=0.0: torch.full((M, N), v, dtype=d, device=dev_)  # noqa: E731
+
+    def check(got, ref, what):
+        e = (got.double() - ref).abs().max().item() / ref.square().mean().sqrt().item()
+        lim = 1e-5 + (0.0 if got.dtype == torch.float32 else out_rounding_bound(ref.cpu().numpy(), name))
+        assert e <= lim, f"{what}: {e:.2e} > {lim:.2e}"
+    for kmajor, ref, w, ld in ((True, fwd, W, K), (False, dgr, Bk, N)):
+        kw = dict(M=M, N=N, K=K, a_kmajor=True, b_kmajor=kmajor, lda=K, ldb=ld)
+        o16, o32, acc = full(dt), full(torch.float32), full(torch.float32, 2.0)
+        Bd.lsk_gemm(A, w, o16, **kw)
+        check(o16, ref, f"operand type {kmajor}")
+        Bd.lsk_gemm(A, w, o32, **kw)
+        check(o32, ref, f"fp32 {kmajor}")
+        Bd.lsk_gemm(A, w, acc, accumulate=True, **kw)
+        check(acc, ref + 2.0, f"accumulated {kmajor}")
+        if kmajor:
+            Bd.lsk_gemm(A, w, o32, bias=b, resid=R, **kw)
+            check(o32, ref + b.double() + R.double(), "bias and residual")
+            Bd.lsk_gemm(A, w, o16, bias=b, **kw)
+            check(o16, ref + b.double(), "bias")
+    pre = S.normal_torch(31, "pre", (M, 2 * N), 1.0, dtype=dt)
+    one, two, da = torch.empty_like(pre), torch.empty_like(pre), full(dt)
+    Bd.lsk_gemm_swiglu_bwd(A, Bk, pre, one, da)
+    Bd.lsk_gemm(A, Bk, da, M=M, N=N, K=K, a_kmajor=True, b_kmajor=False, lda=K, ldb=N)
+    Bd.lsk_swiglu_bwd(da, pre, two)
+    assert torch.equal(one, two)
+
+
+@pytest.mark.parametrize("name", ["f16", "bf16"])
+@pytest.mark.parametrize("T,h", [(700, 32), (500, 32), (300, 32)])   # 192 x 256 tiles, 128 x 256, the rotary kernel
+def test_rotary_embedding_behind_192_and_128_row_tiles(name, T, h):
+    dt, d, half = DT[name], h * 128, 64
+    x, w = S.normal_torch(32, "x", (T, d), 1.0, dtype=dt), S.normal_torch(32, "w", (3 * d, d), d ** -0.5, dtype=dt)
+    pos = torch.as_tensor(S.uniform_ints(32, "pos", T, 0, 2047).astype(np.int32), device="cuda")
+    ang = torch.arange(2048, device="cuda").double()[:, None] * 1e4 ** (-torch.arange(half, device="cuda").double() / half)
+    table = torch.stack([ang.cos(), ang.sin()], -1).float().contiguous()
+    qkv = torch.empty(T, 3 * d, dtype=dt, device="cuda")
+    Bd.lsk_gemm_qkv_rope(x, w, qkv, h, 128, pos, table)
+    ref = (x.double() @ w.double().T.contiguous()).reshape(T, 3, h, 128)
+    c, s = ang.cos()[pos.long()][:, None], ang.sin()[pos.long()][:, None]
+    for part in (0, 1):
+        a, b = ref[:, part, :, :half].clone(), ref[:, part, :, half:].clone()
+        ref[:, part, :, :half], ref[:, part, :, half:] = a * c - b * s, b * c + a * s
+    ref = ref.reshape(T, 3 * d).cpu().numpy()
+    # two 16-bit roundings where the rotary kernel follows the product
+    assert_close(host(qkv), ref, 1e-5 + 2 * out_rounding_bound(ref, name), "qkv")
+
+
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 64, 65, 130])
 def test_fp32_attention_over_batches_of_keys(dh, L):
