@@ -3,11 +3,15 @@
 // 16-byte-per-lane loads that cover whole pages contiguously (a page of one
 // head is page_size * head_dim 16-bit elements, 4 KB for 16 x 128).
 //
-// Work split: a workgroup of 4 wavefronts owns one (row, head, split); the
-// split's pages are dealt round-robin to the wavefronts.  A lane holds 8
+// Work split: a workgroup of 4, 8 or 16 wavefronts owns one (row, head, split); the
+// split's tokens are dealt to the wavefronts in groups of eight loads (4 KB of K, 4 KB of V).  A lane holds 8
 // consecutive head-dimension elements of one token; the q.k dot product is
 // finished with a butterfly over the head_dim/8 lanes that share a token.
-// Softmax is online per wavefront; the four partial (max, sum, output) triples
+// A wavefront has the loads of two groups in flight, and the block table is read a group further ahead: with one group, and
+// its pages looked up when it is its turn, a wavefront waited for a table entry and then for the keys, and a chip full of
+// them reached 6.2 TB/s.  us, one group in flight and the plan of then -> now: 32 requests of 512 tokens, 12 heads of 64:
+// 15.6 -> 13.2; 64 of up to 2048, 32 heads of 128: 191 -> 173 (6.5 TB/s); 128 of up to 4096, 40 heads: 992 -> 902 (6.6).
+// Softmax is online per wavefront; the wavefronts' partial (max, sum, output) triples
 // are merged in LDS, and when the context was split across workgroups a second
 // kernel merges the per-split partials (deterministic, no atomics).
 #include <mutex>
@@ -24,25 +28,27 @@ namespace {
 constexpr size_t kStaticScratchFloats = (size_t)2 << 20;   // 8 MiB
 static __device__ __align__(256) float scratch[kStaticScratchFloats];
 
-template <class T, int DH>
-__global__ __launch_bounds__(256) void decode_attn_kernel(
+template <class T, int DH, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
     const T* __restrict__ qkv, const int32_t* __restrict__ pos_arr, const int32_t* __restrict__ req_arr,
     const T* __restrict__ k_pool, const T* __restrict__ v_pool, const int32_t* __restrict__ block_table,
     int max_pages, int page, int h, int nsplit, int chunk_pages, float scale_log2, T* __restrict__ o,
     float* __restrict__ partial) {
   constexpr int LPT = DH / 8;        // lanes per token
   constexpr int TPL = 64 / LPT;      // tokens per wave-wide load (1 KB)
+  constexpr int G = 4;               // loads of K, and of V, per group
   typedef typename vec8<T>::type V8;
-  __shared__ float s_m[4], s_l[4];
-  __shared__ float s_o[4][DH];
+  __shared__ float s_m[NW], s_l[NW];
+  __shared__ float s_o[NW][DH];
 
   const int t = blockIdx.x / h, head = blockIdx.x % h, split = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int sub = lane % LPT;        // which 8-element chunk of the head dimension
   const int tok_in = lane / LPT;     // token within a load
   const int d = h * DH;
   const int nkeys = pos_arr[t] + 1;
   const int req = req_arr[t];
+  const V8 qv = *(const V8*)(qkv + (long)t * 3 * d + (long)head * DH + sub * 8);
   const int npages = (nkeys + page - 1) / page;
   // chunk_pages > 0: every split covers that many pages whatever the request's length (splits past its end
   // are empty), so that the work items of a ragged batch are all about the same size; otherwise the
@@ -57,66 +63,87 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(
     }
     return;
   }
-  const int loads_per_page = page / TPL;   // page * DH * 2 bytes / 1 KB
+  // The split's tokens in units of one load (1 KB of K, 1 KB of V); every unit has a token of the context.  Groups of G
+  // units are dealt to the wavefronts; a group may span pages (two of 16 tokens of 64 elements) or be part of one.
+  const int lpp = page / TPL, sh = (lpp & (lpp - 1)) == 0 ? __ffs(lpp) - 1 : -1;
+  const int u_lo = p_lo * lpp, u_hi = min(p_hi * lpp, (nkeys + TPL - 1) / TPL);
+  const int ng = (u_hi - u_lo + G - 1) / G;
   const int32_t* bt = block_table + (long)req * max_pages;
+  auto page_of = [&](int u) { return sh >= 0 ? u >> sh : u / lpp; };
+  // where a group's units lie in the pools; the block table is read a group ahead of the loads that need it
+  auto find = [&](int g, long (&at)[G]) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int u = min(u_lo + g * G + i, u_hi - 1), p = page_of(u);
+      at[i] = (((long)bt[p] * h + head) * page) * DH + (u - p * lpp) * 512;
+    }
+  };
+  auto fetch = [&](const long (&at)[G], V8 (&k)[G], V8 (&v)[G]) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      k[i] = __builtin_nontemporal_load((const V8*)(k_pool + at[i] + lane * 8));
+      v[i] = __builtin_nontemporal_load((const V8*)(v_pool + at[i] + lane * 8));
+    }
+  };
 
   float q[8];
-  {
-    const V8 qv = *(const V8*)(qkv + (long)t * 3 * d + (long)head * DH + sub * 8);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) q[i] = to_f(qv[i]) * scale_log2;
-  }
+  for (int i = 0; i < 8; ++i) q[i] = to_f(qv[i]) * scale_log2;
   float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-
-  for (int p = p_lo + wave; p < p_hi; p += 4) {
-    const long base = ((long)bt[p] * h + head) * page * DH;
-    const int tok0 = p * page;
-    // up to 4 loads per page (page 16, DH 128); generic in page size via the loop
-    for (int i0 = 0; i0 < loads_per_page; i0 += 4) {
-      V8 kv[4], vv[4];
-      float s[4];
+  auto attend = [&](int g, const V8 (&kv)[G], V8 (&vv)[G]) {
+    float s[G], mx = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i0 + i < loads_per_page) {
-          kv[i] = __builtin_nontemporal_load((const V8*)(k_pool + base + (long)(i0 + i) * 512 + lane * 8));
-          vv[i] = __builtin_nontemporal_load((const V8*)(v_pool + base + (long)(i0 + i) * 512 + lane * 8));
-        }
-      float mx = -INFINITY;
+    for (int i = 0; i < G; ++i) {
+      float a = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s[i] = -INFINITY;
-        if (i0 + i < loads_per_page) {
-          float a = 0.f;
+      for (int c = 0; c < 8; ++c) a = fmaf(q[c], to_f(kv[i][c]), a);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) a = fmaf(q[c], to_f(kv[i][c]), a);
+      for (int off = 1; off < LPT; off <<= 1) a += __shfl_xor(a, off, 64);
+      const int u = u_lo + g * G + i;
+      s[i] = u < u_hi && u * TPL + tok_in < nkeys ? a : -INFINITY;
+      mx = fmaxf(mx, s[i]);
+    }
 #pragma unroll
-          for (int off = 1; off < LPT; off <<= 1) a += __shfl_xor(a, off, 64);
-          const int tok = tok0 + (i0 + i) * TPL + tok_in;
-          s[i] = tok < nkeys ? a : -INFINITY;
-          mx = fmaxf(mx, s[i]);
-        }
+    for (int off = LPT; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    const float m_new = fmaxf(m, mx);   // finite: the first token of a unit is in the context
+    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const float pr = __builtin_amdgcn_exp2f(s[i] - m_new);
+      l += pr;
+      // slots of the last page beyond the context were never written: whatever bit patterns they hold
+      // (NaN, infinity) must not reach the sum through 0 * x
+      if (s[i] == -INFINITY) vv[i] = V8{};
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] = fmaf(pr, to_f(vv[i][c]), acc[c]);
+    }
+    m = m_new;
+  };
+  int g = wave;
+  if (g < ng) {
+    long at[G];
+    V8 k0[G], v0[G], k1[G], v1[G];
+    find(g, at);
+    fetch(at, k0, v0);
+    if (g + NW < ng) find(g + NW, at);
+    for (; g < ng; g += 2 * NW) {
+      if (g + NW < ng) {
+        fetch(at, k1, v1);
+        if (g + 2 * NW < ng) find(g + 2 * NW, at);
       }
-#pragma unroll
-      for (int off = LPT; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      const float m_new = fmaxf(m, mx);   // finite: token tok0 of a visited page is always < nkeys
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-      l *= alpha;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] *= alpha;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i0 + i < loads_per_page) {
-          const float pr = __builtin_amdgcn_exp2f(s[i] - m_new);
-          l += pr;
-          // slots of the last page beyond the context were never written: whatever bit patterns they hold
-          // (NaN, infinity) must not reach the sum through 0 * x
-          if (s[i] == -INFINITY) vv[i] = V8{};
-#pragma unroll
-          for (int c = 0; c < 8; ++c) acc[c] = fmaf(pr, to_f(vv[i][c]), acc[c]);
+      attend(g, k0, v0);
+      if (g + NW < ng) {
+        if (g + 2 * NW < ng) {
+          fetch(at, k0, v0);
+          if (g + 3 * NW < ng) find(g + 3 * NW, at);
         }
-      m = m_new;
+        attend(g + NW, k1, v1);
+      }
     }
   }
   // sum over the token groups of the wavefront (lanes with equal `sub`)
@@ -133,12 +160,14 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(
   if (lane == 0) { s_m[wave] = m; s_l[wave] = l; }
   __syncthreads();
   if (threadIdx.x < DH) {
-    const float mm = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+    float mm = s_m[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w]);
     float ll = 0.f, oo = 0.f;
     if (mm != -INFINITY) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float f = __builtin_amdgcn_exp2f(s_m[w] - mm);   // 0 for a wavefront that saw no page
+      for (int w = 0; w < NW; ++w) {
+        const float f = __builtin_amdgcn_exp2f(s_m[w] - mm);   // 0 for a wavefront that saw no group
         ll += s_l[w] * f;
         oo += s_o[w][threadIdx.x] * f;
       }
@@ -182,24 +211,14 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, int nspli
   o[t * (long)h * DH + head * DH + threadIdx.x] = from_f<T>(oo / ll);
 }
 
-// Pages per split when the batch alone fills the chip (2048 or more (row, head) pairs): contexts of a ragged
-// batch differ by an order of magnitude, and with one workgroup per pair the compute units that drew the
-// long ones are still streaming when the others have finished.  Chunks of 512 tokens make every work item
-// about the same size; the partial results cost (dh + 2) floats per chunk against 512 * dh * 4 bytes read.
-constexpr int kChunkTokens = 512;
-
-int pick_nsplit(long items, int max_ctx, int page, int* chunk_pages) {
-  // enough workgroups to fill 256 compute units a few times over, but never
-  // fewer than 8 pages per split
+// The most splits that a launch uses: what the scratch of the entry points is sized for.
+int most_splits(long items, int max_ctx, int page) {
   const int max_pages = (max_ctx + page - 1) / page;
-  *chunk_pages = 0;
   if (items >= 2048) {
-    const int cp = kChunkTokens / page > 0 ? kChunkTokens / page : 1;
+    const int cp = 512 / page > 0 ? 512 / page : 1;
     if (max_pages <= cp + cp / 2) return 1;
     const int ns = (max_pages + cp - 1) / cp;
-    if (ns > 32) return 1;
-    *chunk_pages = cp;
-    return ns;
+    return ns > 32 ? 1 : ns;
   }
   int ns = (int)((2048 + items - 1) / items);
   const int cap = max_pages / 8 > 1 ? max_pages / 8 : 1;
@@ -208,17 +227,50 @@ int pick_nsplit(long items, int max_ctx, int page, int* chunk_pages) {
   return ns < 1 ? 1 : ns;
 }
 
+struct Plan { int splits, chunk_pages, waves; };
+
+// Workgroups and wavefronts for `items` (row, head) pairs with contexts of at most max_ctx tokens.  A context stays in one
+// workgroup wherever the pairs fill the chip, with more wavefronts for longer ones: splitting it costs a second launch
+// and the partial results.  us, wavefronts / splits: 384 pairs of 512 tokens of 64 elements 8/1 13.2, 4/4 15.4; 1536 of
+// 1000 8/1 60.6, 4/1 63.9, 16/1 71.5; 2048 of up to 2048 tokens of 128 16/1 173, 8/1 177, 4/1 187, 4 in chunks of 512 188;
+// 4096 of 100 4/1 35.5, 8/1 41.5.  Few pairs with long contexts are split until there are 512 workgroups, each wavefront
+// with a group at least: 32 of 1537 8/12 10.9, 16/1 19.9; 64 of 700 8/4 9.4, 16/1 11.5; but 192 of 700 x 64 16/1 9.3, 8/2 11.9.
+// Contexts beyond 6144 tokens are cut into chunks of 4096, so that one long request of a batch is not the last
+// workgroup's for itself.
+Plan plan(long items, int max_ctx, int page, int dh, bool may_split) {
+  const int per_group = 2048 / dh;   // tokens
+  const int ng = (max_ctx + per_group - 1) / per_group, most = may_split ? most_splits(items, max_ctx, page) : 1;
+  Plan p{1, 0, 4};
+  if (items < 512 && ng > 24) {
+    int ns = (int)(512 / items);
+    if (ns > ng / 8) ns = ng / 8;
+    if (ns > most) ns = most;
+    if (ns > 1) return Plan{ns, 0, 8};
+  } else if (items >= 512 && max_ctx > 6144) {
+    const int cp = 4096 / page > 0 ? 4096 / page : 1, ns = (max_ctx + cp * page - 1) / (cp * page);
+    if (ns <= most) return Plan{ns, cp, 16};
+  }
+  if (items < 320) p.waves = ng <= 4 ? 4 : ng <= 8 ? 8 : 16;
+  else p.waves = ng <= 8 ? 4 : ng <= 64 ? 8 : 16;
+  return p;
+}
+
 template <class T, int DH>
 ls_status launch(const void* qkv, int T_, int h, const int32_t* pos, const int32_t* req, const void* kp,
                  const void* vp, const int32_t* bt, int max_pages, int page, int max_ctx, void* o,
                  float* scratch, hipStream_t st) {
   const long items = (long)T_ * h;
-  int chunk_pages = 0;
-  const int ns = scratch ? pick_nsplit(items, max_ctx, page, &chunk_pages) : 1;
+  const Plan p = plan(items, max_ctx, page, DH, scratch != nullptr);
+  const int ns = p.splits;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-  decode_attn_kernel<T, DH><<<dim3((unsigned)items, ns), 256, 0, st>>>(
-      (const T*)qkv, pos, req, (const T*)kp, (const T*)vp, bt, max_pages, page, h, ns, chunk_pages, scale_log2,
-      (T*)o, scratch);
+  auto go = [&](auto* kern) {
+    kern<<<dim3((unsigned)items, ns), p.waves * 64, 0, st>>>((const T*)qkv, pos, req, (const T*)kp, (const T*)vp, bt,
+                                                             max_pages, page, h, ns, p.chunk_pages, scale_log2, (T*)o,
+                                                             scratch);
+  };
+  if (p.waves == 16) go(decode_attn_kernel<T, DH, 16>);
+  else if (p.waves == 8) go(decode_attn_kernel<T, DH, 8>);
+  else go(decode_attn_kernel<T, DH, 4>);
   LS_CHECK_LAUNCH();
   if (ns > 1) {
     decode_merge_kernel<T, DH><<<(unsigned)items, DH, 0, st>>>(scratch, ns, h, (T*)o);
@@ -253,8 +305,7 @@ ls_status static_scratch(float** out) {
 extern "C" {
 
 size_t lsk_attn_decode_scratch_floats(int T, int h, int dh, int max_ctx, int page) {
-  int chunk_pages = 0;
-  const int ns = pick_nsplit((long)T * h, max_ctx, page, &chunk_pages);
+  const int ns = most_splits((long)T * h, max_ctx, page);
   return ns > 1 ? (size_t)T * h * ns * (dh + 2) : 0;
 }
 

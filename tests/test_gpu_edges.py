@@ -192,6 +192,39 @@ def test_rotary_embedding_behind_192_and_128_row_tiles(name, T, h):
     assert_close(host(qkv), ref, 1e-5 + 2 * out_rounding_bound(ref, name), "qkv")
 
 
+@pytest.mark.parametrize("name,dh,P,h,ctx", [
+    ("f16", 64, 16, 2, [0, 7, 15, 16, 31, 32, 33, 100]),              # groups of two pages; four wavefronts
+    ("bf16", 64, 8, 3, [255, 256, 257, 140]),                          # four pages a group; eight
+    ("f16", 64, 24, 2, [95, 96, 97, 500, 1]),                          # three loads a page; sixteen
+    ("f16", 64, 64, 40, [63, 64, 200, 280, 5, 256, 17, 90]),           # half a page a group; 320 pairs
+    ("f16", 128, 16, 1, [1537, 40, 383]), ("bf16", 128, 64, 2, [1999, 64, 65]),   # split contexts
+    ("f16", 128, 8, 64, [130, 1, 127, 128, 129, 1100, 31, 12]),        # 512 pairs; sixteen wavefronts
+    ("f16", 128, 16, 128, [7000, 4095, 4096, 50])])                    # chunks of 4096 tokens
+def test_decode_attention_plans(name, dh, P, h, ctx):
+    """Pages smaller and larger than a group of loads, contexts that end at each edge, every number of wavefronts, with and
+    without splits; the slots beyond the contexts hold NaN.  Softmax weights in fp32 and 16-bit results: 1e-5 beside the
+    rounding of the result."""
+    dt, T, d = DT[name], len(ctx), h * dh
+    table, n_pages = S.page_tables(np.array(ctx), np.ones(T, np.int64), P, seed=4)
+    bt = torch.as_tensor(table, dtype=torch.int32, device="cuda")
+    kp, vp = (S.normal_torch(44, n, (n_pages, h, P, dh), 1.0, dtype=dt) for n in "KV")
+    qkv = S.normal_torch(44, "qkv", (T, 3 * d), 1.0, dtype=dt)
+    ref = torch.empty(T, d, dtype=torch.float64, device="cuda")
+    for b, n in enumerate(ctx):
+        pages = bt[b, :n // P + 1].long()
+        K, V = (x[pages].transpose(1, 2).reshape(-1, h, dh)[:n + 1].double() for x in (kp, vp))
+        w = torch.softmax((K * qkv[b, :d].double().reshape(h, dh)).sum(-1) / dh ** 0.5, 0)
+        ref[b] = (w[..., None] * V).sum(0).reshape(d)
+    for b, n in enumerate(ctx):
+        kp[bt[b, n // P].long(), :, n % P + 1:] = float("nan")
+        vp[bt[b, n // P].long(), :, n % P + 1:] = float("nan")
+    o = torch.empty(T, d, dtype=dt, device="cuda")
+    pos = torch.as_tensor(ctx, dtype=torch.int32, device="cuda")
+    Bd.lsk_attn_paged(1, qkv, h, dh, pos, torch.arange(T, dtype=torch.int32, device="cuda"), kp, vp, bt, P, max(ctx) + 1, o)
+    ref = ref.cpu().numpy()
+    assert_close(host(o), ref, 1e-5 + out_rounding_bound(ref, name), "o")
+
+
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 64, 65, 130])
 def test_fp32_attention_over_batches_of_keys(dh, L):
