@@ -292,6 +292,15 @@ ls_status lsk_gemm_wgrad(int op_dtype, int M, int N, int T, const void* dOut, co
                          const float* alpha_dev, float* scratch, size_t scratch_floats, int* parts, void* stream);
 ls_status lsk_gemm_dgrad(int op_dtype, int T, int N, int K, const void* dOut, const void* W, void* dIn, float* scratch,
                          size_t scratch_floats, int* parts, void* stream);
+/*
+ * All gradients of y = x W^T + b with K outputs and N inputs, W [K,N]: dIn [T,N], dW [K,N] (fp32) and db [K] (fp32, may be
+ * null), the latter two as (accumulate ? old : 0) + alpha * the gradient, with both products in one launch.  LS_ESTATE,
+ * and nothing launched, where separate calls are the better ones or the shape is not covered.  parts [host, two values,
+ * may be null]: parts of dW and of dIn.
+ */
+ls_status lsk_gemm_grads(int op_dtype, int T, int K, int N, const void* dOut, const void* W, const void* In, void* dIn,
+                         float* dW, float* db, int accumulate, const float* alpha_dev, float* scratch,
+                         size_t scratch_floats, int* parts, void* stream);
 
 /*
  * Decode batches (Autoregressive Generation: decoding requests extend their
@@ -351,7 +360,7 @@ ls_status lsk_finish_qkv(const float* partial, int splits, int T, int h, int dh,
  */
 enum {
   LSK_TIMED_GEMM = 0,        /* projections and gradient products of 256 rows of the result or more: lsk_gemm / lsk_gemm_scaled /
-                                lsk_gemm_qkv_rope / lsk_gemm_swiglu_bwd / lsk_gemm_ws / lsk_gemm_wgrad / lsk_gemm_dgrad, and the
+                                lsk_gemm_qkv_rope / lsk_gemm_swiglu_bwd / lsk_gemm_ws / lsk_gemm_wgrad / lsk_gemm_dgrad / lsk_gemm_grads, and the
                                 projections that a serving call splits along the contraction (the parts alone: their sum is
                                 in an lsk_finish_*) */
   LSK_TIMED_ATTN_FWD = 1,    /* matrix-core attention forward (training and prompt chunks) */

@@ -92,6 +92,7 @@ SIGNATURES = {
     "lsk_grad_scale": (_I, [_VP, _I, _SZ, _VP, _VP]),
     "lsk_gemm_scaled": (_I, [_I, _I, _I, _I, _VP, _L, _I, _VP, _L, _I, _VP, _L, _I, _VP, _I, _VP, _L, _I, _VP, _VP]),
     "lsk_gemm_wgrad": (_I, [_I, _I, _I, _I, _VP, _VP, _VP, _I, _VP, _VP, _SZ, C.POINTER(_I), _VP]),
+    "lsk_gemm_grads": (_I, [_I, _I, _I, _I, _VP, _VP, _VP, _VP, _VP, _VP, _I, _VP, _VP, _SZ, C.POINTER(_I), _VP]),
     "lsk_gemm_dgrad": (_I, [_I, _I, _I, _I, _VP, _VP, _VP, _VP, _SZ, C.POINTER(_I), _VP]),
     "lsk_convert_scaled": (_I, [_VP, _I, _VP, _I, _SZ, _VP, _VP]),
     "lsk_norm_bwd_scaled": (_I, [_I, _VP, _I, _VP, _VP, _VP, _VP, _I, _I, _I, _VP, _VP, _VP, _I, _VP, _VP, _I,
@@ -515,6 +516,19 @@ def lsk_gemm_dgrad(dout, w, dx, scratch, stream=None):
     _check(lib().lsk_gemm_dgrad(CODE_OF_TORCH[dout.dtype], dout.shape[0], w.shape[1], dout.shape[1], _p(dout), _p(w), _p(dx),
                                 _opt(scratch), scratch.numel() if scratch is not None else 0, C.byref(parts), _stream(stream)))
     return parts.value
+
+
+def lsk_gemm_grads(dout, w, x, dx, dw, db, scratch, alpha=None, accumulate=False, stream=None):
+    """dx = dout w, dw (+)= alpha dout^T x, db (+)= alpha column sums of dout (or None): returns (parts of dw, parts of dx), or
+    None where separate calls are to be made."""
+    parts = (C.c_int * 2)()
+    st = lib().lsk_gemm_grads(CODE_OF_TORCH[dout.dtype], dout.shape[0], dout.shape[1], x.shape[1], _p(dout), _p(w), _p(x), _p(dx),
+                              _p(dw), _opt(db), int(accumulate), _opt(alpha), _opt(scratch),
+                              scratch.numel() if scratch is not None else 0, parts, _stream(stream))
+    if st == LS_ESTATE:
+        return None
+    _check(st)
+    return parts[0], parts[1]
 
 
 def lsk_gemm_partials(x, w, partial, stream=None):

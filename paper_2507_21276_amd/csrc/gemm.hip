@@ -447,6 +447,19 @@ extern "C" ls_status lsk_gemm_dgrad(int op_dtype, int T, int N, int K, const voi
   return r;
 }
 
+ls_status gemm_dma_grads(int, int, int, int, const void*, const void*, const void*, void*, float*, float*, int, const float*,
+                         float*, size_t, int*, hipStream_t);
+
+// All gradients of a linear map, in one launch of products where that is better than two
+extern "C" ls_status lsk_gemm_grads(int op_dtype, int T, int K, int N, const void* dOut, const void* W, const void* In,
+                                    void* dIn, float* dW, float* db, int accumulate, const float* alpha_dev, float* scratch,
+                                    size_t scratch_floats, int* parts, void* stream) {
+  LS_REQUIRE(T > 0 && K > 0 && N > 0 && dOut && W && In && dIn && dW, "gemm_grads: bad argument");
+  LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, stream);
+  return gemm_dma_grads(op_dtype, T, K, N, dOut, W, In, dIn, dW, db, accumulate, alpha_dev, scratch, scratch_floats,
+                        parts, (hipStream_t)stream);
+}
+
 ls_status gemm_dma16_swiglu_bwd_try(int, int, int, int, const void*, long, const void*, long, const void*, void*,
                                     hipStream_t);
 

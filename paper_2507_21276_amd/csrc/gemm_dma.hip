@@ -24,6 +24,10 @@
 // workgroup barrier per tile sits before the last quarter of the MFMAs.
 #include "gemm_dma_common.h"
 
+#include <math.h>
+
+#include <type_traits>
+
 namespace {
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -105,15 +109,15 @@ __device__ __forceinline__ typename Mf<T>::V8 frag_value(const Frag<T, KMAJOR>& 
 }
 
 // MODE 0: C (16-bit) = acc + bias;  1: C (fp32) = resid + acc + bias;  2: C (fp32) = acc;  4: C (fp32) += acc;
+// The tile `bid` of the launch's order, over part `part` of `parts` of the contraction.
 template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
-__global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
+__device__ __forceinline__ void gemm_dma_tile(const DmaArgs& g, char* smem, int bid, int part, int parts) {
   typedef typename Mf<T>::V8 V8;
   static_assert(!KTAIL || (!AK && !BK), "only a k-strided operand has a row per k to clear");
   constexpr int TM = BM, TN = BN;
   constexpr int WM = BM / 2, WN = BN / 2;       // wavefront tile
   constexpr int TI = WM / 32, TJ = WN / 32;     // 32x32 MFMA tiles per wavefront
   constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, BUF_BYTES = A_BYTES + B_BYTES;
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
   // buffer b: A tile at smem + b BUF_BYTES, B tile A_BYTES after it
 
   // workgroups that run at the same time share operand tiles through L2:
@@ -121,7 +125,6 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   // (consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its
   // own L2: give every XCD a contiguous run of the tile order instead)
   const int total = g.tiles_m * g.tiles_n, per_xcd = total / 8;
-  int bid = blockIdx.x;
   if (bid < per_xcd * 8) bid = (bid % 8) * per_xcd + bid / 8;
   const int band = 8;
   const int per_band = band * g.tiles_m;
@@ -149,10 +152,10 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // gridDim.y > 1: split-K, this workgroup contracts over its share of the k tiles
+  // parts > 1: split-K, this workgroup contracts over its share of the k tiles
   const int nk_all = KTAIL ? (g.K + TK - 1) / TK : g.K / TK;
-  const int kt0 = (int)((long)blockIdx.y * nk_all / gridDim.y);
-  const int nk = (int)((long)(blockIdx.y + 1) * nk_all / gridDim.y) - kt0;
+  const int kt0 = (int)((long)part * nk_all / parts);
+  const int nk = (int)((long)(part + 1) * nk_all / parts) - kt0;
   a_base += kt0 * a_step;
   b_base += kt0 * b_step;
   // A contraction length that is not a multiple of TK (weight gradients: any number of tokens): the last tile
@@ -215,6 +218,18 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
 #pragma unroll
   for (int j = 0; j < TJ; ++j) read_frag<T, BK, BN>(fb[0][j], smem + A_BYTES, wn + j * 32, 0, lane);
 
+  // Sums of A over k (the bias gradient beside a weight gradient): the first column of tiles has all of A in its
+  // fragments, so the wavefronts on its left add them up under the matrix instructions.  One sum per k sub-step and row
+  // block keeps the chains short.
+  constexpr bool SUMS = !AK && !BK && BM == 128;
+  const bool sums = SUMS && g.row_sums && n0 == 0 && wn == 0;
+  float rs[SUMS ? TI : 1][4];
+  if constexpr (SUMS)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) rs[i][ks] = 0.f;
+
   int cur = 0;   // buffer of tile kt
   for (int kt = 0; kt < nk; ++kt) {
     const int nxt = cur + 1 == ST ? 0 : cur + 1, prv = cur == 0 ? ST - 1 : cur - 1;
@@ -276,6 +291,15 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (SUMS)
+        if (sums)
+#pragma unroll
+          for (int i = 0; i < TI; ++i) {
+            float t[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[e] = to_f(va[i][e]);
+            rs[i][ks] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+          }
     }
   }
   // The last iteration read the fragments of a tile that does not exist.  Their registers must
@@ -305,6 +329,18 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
   const float alpha = g.alpha ? *g.alpha : 1.f;
   __syncthreads();   // every wavefront is done with the operand tiles
   char* stg = smem + wave * REGION;
+  if constexpr (SUMS)
+    if (sums)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        float v = (rs[i][0] + rs[i][1]) + (rs[i][2] + rs[i][3]);
+        v = (v + __shfl_xor(v, 32, 64)) * alpha;   // the other eight k of every sixteen
+        const int m = m0 + wm + i * 32 + row_in;
+        if (hf == 0 && m < g.M) {
+          float* out = g.row_sums + (long)part * g.M + m;
+          *out = MODE == 4 ? *out + v : v;
+        }
+      }
   // A lane's columns are the same for all of its rows: its bias values are fetched once, outside the
   // staging loops (a fetch with a type switch inside them, once per element, made the epilogue some
   // thousands of instructions long and cost 3 - 6 us per launch even without a bias).
@@ -341,7 +377,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
     constexpr bool ADDS = MODE == 1 || MODE == 4;
     f32x4 c_old[ADDS ? NOUT : 1];
     if constexpr (ADDS) {
-      const float* src = MODE == 1 ? g.resid : (const float*)g.C + blockIdx.y * g.split_stride;
+      const float* src = MODE == 1 ? g.resid : (const float*)g.C + part * g.split_stride;
       const long ld_src = MODE == 1 ? g.ldr : g.ldc;
 #pragma unroll
       for (int it = 0; it < NOUT; ++it) {
@@ -386,7 +422,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
       } else if constexpr (MODE == 1) {
         *(f32x4*)((float*)g.C + (long)m * g.ldc + n) = v + c_old[it];
       } else {
-        *(f32x4*)((float*)g.C + blockIdx.y * g.split_stride + (long)m * g.ldc + n) = MODE == 4 ? c_old[it] + v : v;
+        *(f32x4*)((float*)g.C + part * g.split_stride + (long)m * g.ldc + n) = MODE == 4 ? c_old[it] + v : v;
       }
     };
     if (m0 + wm + pass * ROWS_P + ROWS_P <= g.M && n0 + wn + WN <= g.N) {
@@ -420,6 +456,12 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
       }
     }
   }
+}
+
+template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
+__global__ __launch_bounds__(256) void gemm_dma_kernel(DmaArgs g) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_dma_tile<T, BM, BN, AK, BK, MODE, ST, KTAIL>(g, smem, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
 template <class T, int BM, int BN, bool AK, bool BK, int MODE, int ST, bool KTAIL>
@@ -651,6 +693,175 @@ size_t gemm_dma_wgrad_scratch_floats(long M, long N) {
   if (tiles > 128) return 0;
   const long most = 256 / tiles < 8 ? 256 / tiles : 8;
   return (size_t)(most * M * N);
+}
+
+namespace {
+
+// The two gradients of a linear map as one launch of 128 x 128 tiles: the weight gradient's workgroups (w, WMODE 2 or 4)
+// and the input gradient's (d, DMODE 0 or 2), the longer ones first.  Either alone leaves part of the chip without work
+// in a task of a few thousand tokens on a small stage (192 and 144 tiles on 256 compute units), and its ramp and drain
+// are a third of it.
+template <class T, int WMODE, int DMODE, bool KTAIL>
+__global__ __launch_bounds__(256) void gemm_grads_kernel(DmaArgs w, int wparts, DmaArgs d, int dparts, int d_first) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tw = w.tiles_m * w.tiles_n, td = d.tiles_m * d.tiles_n;
+  const int id = blockIdx.x - (d_first ? td * dparts : 0);
+  if (d_first ? id >= 0 : id < tw * wparts) {
+    gemm_dma_tile<T, 128, 128, false, false, WMODE, 4, KTAIL>(w, smem, id % tw, id / tw, wparts);
+  } else {
+    const int i = d_first ? blockIdx.x : id - tw * wparts;
+    gemm_dma_tile<T, 128, 128, true, false, DMODE, 4, false>(d, smem, i % td, i / td, dparts);
+  }
+}
+
+// The sums over the parts of both, and of the bias gradient's, in order
+struct GradSums {
+  const float* wp; int wparts; long wMN; float* dW; int accumulate; const float* alpha; unsigned w_blocks;
+  const float* bp; int bM; float* db; unsigned b_blocks;
+  const float* dp; int dparts; long dMN; void* dIn;
+};
+__device__ __forceinline__ f32x4 sum_parts(const float* p, int parts, long stride) {
+  f32x4 v[8], s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (i < parts) v[i] = *(const f32x4*)(p + i * stride);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (i < parts) s += v[i];
+  return s;
+}
+template <class T>
+__global__ __launch_bounds__(256) void grad_sums_kernel(GradSums g) {
+  unsigned b = blockIdx.x;
+  if (b < g.w_blocks) {
+    const long i4 = ((long)b * 256 + threadIdx.x) * 4;
+    if (i4 >= g.wMN) return;
+    const f32x4 old = g.accumulate ? *(const f32x4*)(g.dW + i4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    const float a = g.alpha ? *g.alpha : 1.f;
+    const f32x4 v = sum_parts(g.wp + i4, g.wparts, g.wMN) * a;
+    *(f32x4*)(g.dW + i4) = g.accumulate ? old + v : v;
+    return;
+  }
+  b -= g.w_blocks;
+  if (b < g.b_blocks) {
+    const int i4 = (b * 256 + threadIdx.x) * 4;
+    if (i4 >= g.bM) return;
+    const float a = g.alpha ? *g.alpha : 1.f;
+    const f32x4 v = sum_parts(g.bp + i4, g.wparts, g.bM) * a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g.db[i4 + e] = g.accumulate ? g.db[i4 + e] + v[e] : v[e];   // any alignment
+    return;
+  }
+  b -= g.b_blocks;
+  const long i4 = ((long)b * 256 + threadIdx.x) * 4;
+  if (i4 >= g.dMN) return;
+  const f32x4 v = sum_parts(g.dp + i4, g.dparts, g.dMN);
+  typename Mf<T>::V4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = from_f<T>(v[e]);
+  *(typename Mf<T>::V4*)((T*)g.dIn + i4) = o;
+}
+
+template <class T, int WMODE, int DMODE, bool KTAIL>
+ls_status launch_grads(const DmaArgs& w, int wparts, const DmaArgs& d, int dparts, bool d_first, hipStream_t st) {
+  static bool attr_set = false;
+  constexpr int lds = 4 * 256 * 128;
+  if (!attr_set) {
+    LS_CHECK_HIP(hipFuncSetAttribute((const void*)gemm_grads_kernel<T, WMODE, DMODE, KTAIL>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    attr_set = true;
+  }
+  const unsigned wgs = (unsigned)(w.tiles_m * w.tiles_n * wparts + d.tiles_m * d.tiles_n * dparts);
+  gemm_grads_kernel<T, WMODE, DMODE, KTAIL><<<dim3(wgs), 256, lds, st>>>(w, wparts, d, dparts, d_first);
+  LS_CHECK_LAUNCH();
+  return LS_OK;
+}
+
+// Time until n1 workgroups of l1 us and then n2 of l2 <= l1 us have run on 256 compute units, one at a time on each.
+float makespan(int n1, float l1, int n2, float l2) {
+  const int q = n1 / 256, r = n1 % 256;
+  const float busy = (float)q * l1, more = (float)(q + 1) * l1;   // of 256 - r units and of r
+  float t = fmaxf(r ? more : busy, ((float)n1 * l1 + (float)n2 * l2) / 256.f);
+  for (;; t += l2 * 0.125f) {
+    const float a = r ? floorf((t - more) / l2) : 0.f, b = floorf((t - busy) / l2);
+    if ((float)r * fmaxf(a, 0.f) + (float)(256 - r) * fmaxf(b, 0.f) >= (float)n2) return t;
+  }
+}
+
+}  // namespace
+
+float gemm_dma_whole_us(int M, int N, int K);
+
+// Both gradients of a linear map y = x W^T (+ b) over T rows: dIn [T, N] = dOut [T, K] W [K, N] in the operand type, dW [K, N]
+// (+)= alpha dOut^T In, db [K] (+)= alpha column sums of dOut (null: none).  LS_ESTATE where two launches are better or the
+// shape is not covered (nothing has been launched then).
+// Parts of each contraction by the same estimate as splits_to_fill, 0.6 us per k tile and 3 us a workgroup, over the
+// order in which the workgroups run; a sum of parts is a launch of 4 us and its traffic.  Two launches, the column sums and
+// their reductions -> here, in a task of 999 tokens on d 768: FFN-down 12.5 + 17 + 4 -> 22 us, FFN-up 18 + 17 + 4 -> 22 + 5,
+// output projection 10.6 + 20 + 4 -> 19, QKV 16 + 20 + 4 -> 21 + 5; six such blocks, two micro-batches: 3404 -> 2872 us; 4 x
+// 1024 tokens 3177 -> 2957.
+ls_status gemm_dma_grads(int op_dtype, int T, int K, int N, const void* dOut, const void* W, const void* In, void* dIn,
+                         float* dW, float* db, int accumulate, const float* alpha, float* scratch, size_t scratch_floats,
+                         int* parts, hipStream_t st) {
+  if (!scratch || (uintptr_t)scratch % 16 != 0 || T < TK || N < 64 || K < 64 || K % TK != 0 || N % 8 != 0) return LS_ESTATE;
+  if (((uintptr_t)dOut | (uintptr_t)W | (uintptr_t)In | (uintptr_t)dIn | (uintptr_t)dW) % 16 != 0) return LS_ESTATE;
+  if (op_dtype != LS_BF16 && op_dtype != LS_F16) return LS_ESTATE;
+  const long MNw = (long)K * N, MNd = (long)T * N;
+  const long tw = (long)((K + 127) / 128) * ((N + 127) / 128), td = (long)((T + 127) / 128) * ((N + 127) / 128);
+  if (tw > 256 || td > 4096) return LS_ESTATE;
+  const int nkw = (T + TK - 1) / TK, nkd = K / TK;
+  int wparts = 0, dparts = 0;
+  bool d_first = false;
+  float best = 1e30f;
+  for (int a = 1; a <= 8 && (a == 1 || nkw / a >= 4); ++a)
+    for (int b = 1; b <= 4 && (b == 1 || nkd / b >= 4); ++b) {
+      if ((a > 1 ? (size_t)a * (MNw + K) : 0) + (b > 1 ? (size_t)b * MNd : 0) > scratch_floats) continue;
+      if (a * tw > 512 || (b > 1 && b * td > 512)) continue;
+      const float lw = (float)((nkw + a - 1) / a) * 0.6f + 3.f, ld = (float)((nkd + b - 1) / b) * 0.6f + 3.f;
+      float us = 2.f + (ld > lw ? makespan((int)(b * td), ld, (int)(a * tw), lw) : makespan((int)(a * tw), lw, (int)(b * td), ld));
+      if (a > 1 || b > 1)
+        us += 4.f + (float)((a > 1 ? MNw * (a + 1) : 0) + (b > 1 ? MNd * (b + 1) : 0)) / 1e6f;
+      if (us < 0.97f * best) { best = us; wparts = a; dparts = b; d_first = ld > lw; }
+    }
+  // launches apart
+  const int ws = splits_to_fill(tw, nkw, MNw), ds = splits_to_fill(td, nkd, MNd);
+  const float w_us = (float)((nkw + ws - 1) / ws) * 0.65f + 5.f + (ws > 1 ? 4.f + (float)MNw * (ws + 1) / 1e6f : 0.f);
+  const float d_us = fminf(gemm_dma_whole_us(T, N, K),
+                           (float)((nkd + ds - 1) / ds) * 0.65f + 5.f + (ds > 1 ? 4.f + (float)MNd * (ds + 1) / 1e6f
+                                                                               : td > 256 ? 1e30f : 0.f));
+  if (best >= w_us + d_us) return LS_ESTATE;
+  if (parts) { parts[0] = wparts; parts[1] = dparts; }
+
+  float *wp = scratch, *bp = wp + wparts * MNw, *dp = wparts > 1 ? bp + (long)wparts * K : scratch;
+  const bool ws_parts = wparts > 1, ds_parts = dparts > 1;
+  DmaArgs w{K, N, T, dOut, K, 0, In, N, 0, ws_parts ? wp : dW, N, LS_F32, nullptr, 0, nullptr, 0, !ws_parts && accumulate,
+            ws_parts ? nullptr : alpha, 0, 0, MNw, nullptr, nullptr, 0};
+  w.row_sums = !db ? nullptr : ws_parts ? bp : db;
+  w.tiles_m = (K + 127) / 128; w.tiles_n = (N + 127) / 128;
+  DmaArgs d{T, N, K, dOut, K, 1, W, N, 0, ds_parts ? (void*)dp : dIn, N, ds_parts ? LS_F32 : op_dtype, nullptr, 0, nullptr, 0, 0,
+            nullptr, 0, 0, MNd, nullptr, nullptr, 0};
+  d.tiles_m = (T + 127) / 128; d.tiles_n = (N + 127) / 128;
+  auto run = [&](auto t) -> ls_status {
+    typedef decltype(t) E;
+    auto tail = [&](auto wm, auto dm) {
+      constexpr int WM = decltype(wm)::value, DM = decltype(dm)::value;
+      return T % TK ? launch_grads<E, WM, DM, true>(w, wparts, d, dparts, d_first, st)
+                    : launch_grads<E, WM, DM, false>(w, wparts, d, dparts, d_first, st);
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 2> I2;
+    typedef std::integral_constant<int, 4> I4;
+    const bool add = w.accumulate;
+    LS_TRY(add ? (ds_parts ? tail(I4{}, I2{}) : tail(I4{}, I0{})) : (ds_parts ? tail(I2{}, I2{}) : tail(I2{}, I0{})));
+    if (!ws_parts && !ds_parts) return LS_OK;
+    auto blocks = [](long n) { return (unsigned)((n / 4 + 255) / 256); };
+    GradSums g{wp, wparts, MNw, dW, accumulate, alpha, ws_parts ? blocks(MNw) : 0, bp, K, db,
+               ws_parts && db ? blocks(K + 3) : 0, dp, dparts, MNd, dIn};
+    grad_sums_kernel<E><<<g.w_blocks + g.b_blocks + (ds_parts ? blocks(MNd) : 0), 256, 0, st>>>(g);
+    LS_CHECK_LAUNCH();
+    return LS_OK;
+  };
+  return op_dtype == LS_BF16 ? run(bf16_t{}) : run(f16_t{});
 }
 
 // Weight gradient C[M, N] (fp32) = (C +) alpha A^T B over K rows of A [K][M] and B [K][N], split along K into partial

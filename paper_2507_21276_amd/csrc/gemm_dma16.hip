@@ -521,8 +521,9 @@ ls_status launch16_bm(DmaArgs g, hipStream_t st, int splits) {
 // (128), 2048 rows 274 -> 181 (128), 3000 rows 249 -> 237 (192); input gradient, 11008 columns over 4096: 1500 rows 176 ->
 // 147 (192).  Three buffers for 128 x 256: 54 -> 46 us for one round over 4096 (a tile's arithmetic is too short to cover
 // its successor's latency).
-// `after`: what else the 128 x 128 tiles would need (a pass that the larger ones have in their epilogue).
-int rows_per_tile(long M, long N, int nk, bool adds, float after = 0.f) {
+// `after`: what else the 128 x 128 tiles would need (a pass that the larger ones have in their epilogue).  us: the time of
+// the tiles taken.
+int rows_per_tile(long M, long N, int nk, bool adds, float after = 0.f, float* us = nullptr) {
   const long tn = (N + 255) / 256;
   auto rounds = [](long wgs) { return (float)((wgs + 255) / 256); };
   const float us256 = rounds((M + 255) / 256 * tn) * ((float)nk * 1.40f + 8.f);
@@ -536,6 +537,7 @@ int rows_per_tile(long M, long N, int nk, bool adds, float after = 0.f) {
   else us128 = (float)((t128 + 511) / 512) * ((float)nk * 0.95f + 4.f);
   us128 += after;
   const float best = fminf(fminf(us256, us192), us128w);
+  if (us) *us = fminf(us128, best);
   if (us128 <= best) return 0;
   return best == us256 ? 256 : best == us192 ? 192 : 128;
 }
@@ -595,6 +597,13 @@ ls_status gemm_dma16_try(int op_dtype, int M, int N, int K, const void* A, long 
   if (op_dtype == LS_BF16) return dispatch16<bf16_t>(g, rows, st);
   if (op_dtype == LS_F16) return dispatch16<f16_t>(g, rows, st);
   return LS_ESTATE;
+}
+
+// us that a product takes in one piece
+float gemm_dma_whole_us(int M, int N, int K) {
+  float us = 0.f;
+  (void)rows_per_tile(M, N, K / TK, false, 0.f, &us);
+  return us;
 }
 
 // Whether the QKV projection of T rows takes tiles that have the rotary embedding in their epilogue.  `pages`: a serving

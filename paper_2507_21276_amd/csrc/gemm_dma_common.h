@@ -24,6 +24,8 @@ struct DmaArgs {
   // MODE 5 only (16x16x32 kernel): the product is the gradient of a SwiGLU output; the saved (gate | up)
   // pre-activations [M, 2 N] and the gradient buffer of the same shape that the epilogue fills
   const void* glu_pre = nullptr; void* glu_grad = nullptr;
+  // weight gradients (both operands k-strided): where the sums of A over k go as well ([M] per part; null: not wanted)
+  float* row_sums = nullptr;
 };
 
 constexpr int TK = 64;  // k extent of a tile; a tile of ROWS rows is ROWS * 128 bytes = ROWS / 8 wave loads

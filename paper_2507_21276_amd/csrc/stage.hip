@@ -130,6 +130,8 @@ ls_status lsk_gemm_ws(int, int, int, int, const void*, long, const void*, long, 
                       const float*, long, float*, size_t, void*);
 ls_status lsk_gemm_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*, void*);
 ls_status lsk_gemm_swiglu_bwd(int, int, int, int, const void*, const void*, const void*, void*, void*, void*);
+ls_status lsk_gemm_grads(int, int, int, int, const void*, const void*, const void*, void*, float*, float*, int, const float*,
+                         float*, size_t, int*, void*);
 }
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim, bool pages);
 size_t gemm_dma_wgrad_scratch_floats(long M, long N);
@@ -345,6 +347,7 @@ size_t carve_bwd(const ls_stage* s, void* base, int T, BwdWs* w) {
       const size_t f = gemm_dma_wgrad_scratch_floats((long)n, (long)d);
       if (f > v.wsplit_floats) v.wsplit_floats = f;
     }
+    v.wsplit_floats += tiles;   // both gradients of a map at a time
   }
   v.wsplit = (float*)b.take(v.wsplit_floats * 4);
   if (w) *w = v;
@@ -855,35 +858,41 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
   auto input_grad = [&](int N, int K, const void* dOut, const void* W, void* dIn) {
     return lsk_gemm_dgrad(mt, T, N, K, dOut, W, dIn, w.wsplit, w.wsplit_floats, nullptr, st);
   };
+  // all gradients of a linear map with K outputs and N inputs; db null: no bias
+  auto map_grads = [&](int K, int N, const void* dOut, const void* W, const void* In, void* dIn, float* dW,
+                       float* db) -> ls_status {
+    if (mt != LS_F32) {
+      const ls_status r = lsk_gemm_grads(mt, T, K, N, dOut, W, In, dIn, dW, db, acc, inv, w.wsplit, w.wsplit_floats,
+                                         nullptr, st);
+      if (r != LS_ESTATE) return r;
+    }
+    LS_TRY(input_grad(N, K, dOut, W, dIn));
+    LS_TRY(weight_grad(K, N, dOut, In, dW));
+    return db ? bias_grad(dOut, K, db) : LS_OK;
+  };
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerOff& o = s->off[l];
     const Saved& v = sv[l];
     // y = x1 + act W_dn^T (+ b_dn)
     if (gpt) {
-      LS_TRY(input_grad(F, d, w.g16, wptr(s, o.w_dn), w.dact));
+      LS_TRY(map_grads(d, F, w.g16, wptr(s, o.w_dn), v.act, w.dact, dParams + o.w_dn, dParams + o.b_dn));
+      LS_TRY(lsk_gelu_bwd(w.dact, v.up, w.dup, mt, (size_t)T * F, c.act, st));
     } else if (mt == LS_F32) {
       LS_TRY(input_grad(F, d, w.g16, wptr(s, o.w_dn), w.dact));
       LS_TRY(lsk_swiglu_bwd(w.dact, v.up, w.dup, mt, T, F, st));
+      LS_TRY(weight_grad(d, F, w.g16, v.act, dParams + o.w_dn));
     } else {
       // the activation's backward in the epilogue of the product that feeds it (no dact round trip)
       LS_TRY(lsk_gemm_swiglu_bwd(mt, T, F, d, w.g16, wptr(s, o.w_dn), v.up, w.dup, w.dact, st));
-    }
-    LS_TRY(weight_grad(d, F, w.g16, v.act, dParams + o.w_dn));
-    if (gpt) {
-      LS_TRY(bias_grad(w.g16, d, dParams + o.b_dn));
-      LS_TRY(lsk_gelu_bwd(w.dact, v.up, w.dup, mt, (size_t)T * F, c.act, st));
+      LS_TRY(weight_grad(d, F, w.g16, v.act, dParams + o.w_dn));
     }
     // up = h2 W_up^T (+ b_up)
-    LS_TRY(input_grad(d, U, w.dup, wptr(s, o.w_up), w.dh));
-    LS_TRY(weight_grad(U, d, w.dup, v.h2, dParams + o.w_up));
-    if (gpt) LS_TRY(bias_grad(w.dup, U, dParams + o.b_up));
+    LS_TRY(map_grads(U, d, w.dup, wptr(s, o.w_up), v.h2, w.dh, dParams + o.w_up, gpt ? dParams + o.b_up : nullptr));
     // h2 = norm2(x1);  g1 = g + norm2_bwd(dh)
     LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x1, v.mean2, v.rstd2, pptr(s, o.n2_g), pt, T, d, w.g, w.g1, w.g16, mt,
                         dParams + o.n2_g, gpt ? dParams + o.n2_b : nullptr, acc, w.partial, inv, st));
     // x1 = x + o W_o^T (+ b_o)
-    LS_TRY(input_grad(d, d, w.g16, wptr(s, o.w_o), w.d_o));
-    LS_TRY(weight_grad(d, d, w.g16, v.o, dParams + o.w_o));
-    if (gpt) LS_TRY(bias_grad(w.g16, d, dParams + o.b_o));
+    LS_TRY(map_grads(d, d, w.g16, wptr(s, o.w_o), v.o, w.d_o, dParams + o.w_o, gpt ? dParams + o.b_o : nullptr));
     if (gpt)
       LS_TRY(lsk_attn_bwd(mt == LS_F32 ? 0 : 1, v.qkv, v.o, w.d_o, v.lse, mt, B, L, c.n_heads, c.head_dim, w.dqkv,
                           w.dvec, st));
@@ -891,10 +900,8 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
       LS_TRY(lsk_attn_bwd_rope(mt == LS_F32 ? 0 : 1, v.qkv, v.o, w.d_o, v.lse, mt, B, L, c.n_heads, c.head_dim,
                                w.dqkv, w.dvec, w.pos, s->rope_table, st));
     // qkv = h1 W_qkv^T (+ b_qkv)
-    LS_TRY(input_grad(d, 3 * d, w.dqkv, wptr(s, o.w_qkv), w.dh));
-    LS_TRY(weight_grad(3 * d, d, w.dqkv, v.h1, dParams + o.w_qkv));
-    if (gpt) LS_TRY(bias_grad(w.dqkv, 3 * d, dParams + o.b_qkv));
-    if (gpt) {
+    LS_TRY(map_grads(3 * d, d, w.dqkv, wptr(s, o.w_qkv), v.h1, w.dh, dParams + o.w_qkv, gpt ? dParams + o.b_qkv : nullptr));
+    if (n_sums > 0) {
       LS_TRY(lsk_colsum_finish(n_sums, sums, T, acc, inv, st));
       n_sums = 0;
       sums_at = w.bias_partial;

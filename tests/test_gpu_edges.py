@@ -306,6 +306,39 @@ def test_input_gradient_in_parts(name, T, N, K, parts):
         assert_close(host(dX), ref, 1e-5 + out_rounding_bound(ref, name), f"{T}x{N}x{K} in {want}")
 
 
+@pytest.mark.parametrize("name", ["bf16", "f16"])
+@pytest.mark.parametrize("T,K,N,parts", [
+    (999, 768, 3072, (1, 1)), (999, 3072, 768, (1, 2)), (333, 768, 768, (1, 1)), (65, 128, 72, (1, 1)), (64, 64, 64, (1, 1)),
+    (1025, 256, 264, (4, 1)), (2049, 1728, 256, (4, 3)), (2049, 320, 200, (7, 1)), (129, 4096, 256, (1, 4)),
+    (1000, 128, 1024, (4, 1)), (63, 768, 768, None), (300, 4096, 4096, None)])
+def test_gradients_of_a_linear_map_in_one_launch(name, T, K, N, parts):
+    """Either product first and in parts, a last k tile of 1, 39 and 64 tokens, ragged tiles, with and without a bias, added to
+    what is there and scaled; a workspace that holds no parts.  Exact operands: 1e-5 of the RMS for fp32 sums of T or K
+    products, the rounding of the input gradient beside it; sums of T values for the bias: 2e-6."""
+    dt = DT[name]
+    dO, x, w = (S.normal_torch(12, n, shape, std, dtype=dt) for n, shape, std in
+                (("dO", (T, K), 1.0), ("x", (T, N), 1.0), ("w", (K, N), 0.05)))
+    rx = (dO.double() @ w.double()).cpu().numpy()
+    rw, rb = (dO.double().T.contiguous() @ x.double() / 8).cpu().numpy(), (dO.double().sum(0) / 8).cpu().numpy()
+    alpha = torch.full((1,), 0.125, dtype=torch.float32, device="cuda")
+    ws = torch.full((8 * (K * N + K) + 4 * T * N,), float("nan"), dtype=torch.float32, device="cuda")
+    for scratch, want in ((ws, parts), (ws[:4], (1, 1))):
+        for bias in (True, False):
+            dx, dw = torch.full((T, N), 7.0, dtype=dt, device="cuda"), torch.full((K, N), 7.0, device="cuda")
+            db = torch.full((K + 1,), 7.0, device="cuda")[1:] if bias else None   # not 16-byte aligned
+            for acc in (False, True):
+                got = Bd.lsk_gemm_grads(dO, w, x, dx, dw, db, scratch, alpha=alpha, accumulate=acc)
+                if got is None:   # not covered, or better apart if each has to stay whole: nothing has been written
+                    assert parts is None or want != parts
+                    assert (dx == 7.0).all() and (dw == 7.0).all()
+                    break
+                assert got == want
+                assert_close(host(dw), (1 + acc) * rw, 1e-5, "dW")
+                assert_close(host(dx), rx, 1e-5 + out_rounding_bound(rx, name), "dIn")
+                if bias:
+                    assert_close(host(db), (1 + acc) * rb, 2e-6, "db")
+
+
 @pytest.mark.parametrize("mma", ["f16", "bf16"])
 @pytest.mark.parametrize("which", ["gpt", "llama"])
 @pytest.mark.parametrize("B,L", [(5, 205), (3, 333), (1, 1024), (2, 255)])
