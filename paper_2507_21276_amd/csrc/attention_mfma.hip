@@ -308,9 +308,9 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(const T* __restrict__ qk
 }
 
 // ---------------------------------------------------------------------------------
-// Backward.  Two kernels, no atomics (deterministic):
-//   flash_bwd_dq_kernel : a workgroup owns 128 query rows, walks key tiles j <= i
-//   flash_bwd_dkv_kernel: a workgroup owns 128 keys, walks query tiles i >= j
+// Backward.  Two parts, no atomics (deterministic):
+//   dQ:      a workgroup owns 128 query rows, walks key tiles j <= i
+//   dK, dV:  a workgroup owns 128 keys, walks query tiles i >= j
 // Both recompute P from the saved log-sum-exp.  An MFMA result has its row index
 // in registers and its column index in lanes, which is the B-operand layout of a
 // following product that contracts over the rows; so each kernel forms its first
@@ -874,28 +874,45 @@ ls_status launch_prefill(const void* qkv, int h, void* o, const PagedGeom& pg, i
   return LS_OK;
 }
 
+// HV = 2: two wavefronts share 32 rows (queries of dq, keys of dkv) and take half of each tile; the second one's sums go to
+// the first through LDS (DT x 4 KB a pair, over the ring, whose loads have all landed).  False in the second.
+template <int HV, int DT>
+__device__ __forceinline__ bool add_halves(f32x16 (&acc)[DT], char* smem, int wave, int lane) {
+  if constexpr (HV == 1) return true;
+  float* at = (float*)smem + (wave & 3) * DT * 1024 + lane;
+  __syncthreads();
+  if (wave >= 4)
+#pragma unroll
+    for (int j = 0; j < DT; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) at[(j * 16 + e) * 64] = acc[j][e];
+  __syncthreads();
+  if (wave >= 4) return false;
+#pragma unroll
+  for (int j = 0; j < DT; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[j][e] += at[(j * 16 + e) * 64];
+  return true;
+}
+
 // dQ.  A workgroup owns 128 queries (32 per wavefront, Q and dO fragments in registers) and
 // walks the key tiles of 64 keys below its diagonal.  K and V tiles arrive by direct-to-LDS
 // loads through a ring of NS stages; K^T for the second product is read from the K tile with
 // the transposing LDS load.  Both first products are formed transposed (S^T, dP^T: rows =
 // keys, lane column = query), so the softmax statistics are per-lane scalars.
-template <class T, int DH>
-__global__ __launch_bounds__(256) void flash_bwd_dq_kernel(const T* __restrict__ qkv,
-                                                           const T* __restrict__ dO,
-                                                           const float* __restrict__ lse,
-                                                           const float* __restrict__ dvec,
-                                                           T* __restrict__ dqkv, int L, int h,
-                                                           float scale, const float* __restrict__ rope) {
+template <class T, int DH, int HV>
+__device__ __forceinline__ void bwd_dq(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
+                                       const float* __restrict__ dvec, T* __restrict__ dqkv, int L, int h, float scale,
+                                       const float* __restrict__ rope, char* smem, int y) {
   typedef typename Mma<T>::V8 V8;
   constexpr int BQ = 128, NS = 4, KS = DH / 16, DT = DH / 32;
   constexpr int TILE_B = KT * DH * 2;            // bytes of a K or V tile
   constexpr int STAGE_B = 2 * TILE_B;
-  constexpr int NLT = TILE_B / 1024 / 4;         // wave loads per wavefront and tile
+  constexpr int NLT = TILE_B / 1024 / (4 * HV);  // wave loads per wavefront and tile
   constexpr int NLD = 2 * NLT;                   // loads per wavefront and stage
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   const int n_qt = (L + BQ - 1) / BQ;
-  const int qtile = n_qt - 1 - blockIdx.y;   // heaviest tiles of all heads first
+  const int qtile = n_qt - 1 - y;   // heaviest tiles of all heads first
   const int b = blockIdx.x / h, head = blockIdx.x % h;
   const int d = h * DH;
   const long ld = 3L * d;
@@ -905,7 +922,7 @@ __global__ __launch_bounds__(256) void flash_bwd_dq_kernel(const T* __restrict__
   const T* dob = dO + (long)b * L * d + (long)head * DH;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 31, hf = lane >> 5;
-  const int wq0 = qtile * BQ + wave * 32;
+  const int wq0 = qtile * BQ + (wave & 3) * 32;
   const int q = wq0 + col;
   const float scale_log2 = scale * 1.4426950408889634f;
   const float gsc = do_scale(dvec + (long)gridDim.x * L + ((long)gridDim.x * L + 3) / 4);   // after D and the per-workgroup maxima
@@ -956,9 +973,10 @@ __global__ __launch_bounds__(256) void flash_bwd_dq_kernel(const T* __restrict__
     const int key0 = t * KT;
     const char* ks = smem + (t % NS) * STAGE_B;
     const char* vs = ks + TILE_B;
-    // the tile's 64 keys in two blocks of 32
+    // the tile's 64 keys in two blocks of 32, or the one of this wavefront
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    for (int ci = 0; ci < 2 / HV; ++ci) {
+      const int c = HV == 2 ? wave >> 2 : ci;
       f32x16 sacc, pacc;
 #pragma unroll
       for (int e = 0; e < 16; ++e) sacc[e] = pacc[e] = 0.f;
@@ -1005,6 +1023,7 @@ __global__ __launch_bounds__(256) void flash_bwd_dq_kernel(const T* __restrict__
     issue(t + NS);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no direct-to-LDS write may outlive the workgroup
+  if (!add_halves<HV, DT>(acc, smem, wave, lane)) return;
   if (q < L) {
     T* row = dqkv + ((long)b * L + q) * ld + (long)head * DH;
     store_grad_row<T, DH>(row, acc, scale / gsc, hf, rope ? rope + (long)q * DH : nullptr);
@@ -1016,23 +1035,18 @@ __global__ __launch_bounds__(256) void flash_bwd_dq_kernel(const T* __restrict__
 // direct-to-LDS loads through a ring of NS stages (three tiles in flight); the transposed
 // operands dO^T and Q^T of the second pair of products are read from the same tiles with the
 // transposing LDS load.  dS is scaled by a power of two before it is rounded to 16 bits.
-template <class T, int DH>
-__global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const T* __restrict__ qkv,
-                                                            const T* __restrict__ dO,
-                                                            const float* __restrict__ lse,
-                                                            const float* __restrict__ dvec,
-                                                            T* __restrict__ dqkv, int L, int h,
-                                                            float scale, const float* __restrict__ rope) {
+template <class T, int DH, int HV>
+__device__ __forceinline__ void bwd_dkv(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
+                                        const float* __restrict__ dvec, T* __restrict__ dqkv, int L, int h, float scale,
+                                        const float* __restrict__ rope, char* smem, int y) {
   typedef typename Mma<T>::V8 V8;
   constexpr int BKEY = 128, QR = 64, NS = 4, KS = DH / 16, DT = DH / 32;
   constexpr int TILE_B = QR * DH * 2;            // bytes of a Q or dO tile
   constexpr int STAGE_B = 2 * TILE_B + 512;      // Q, dO, 64 log-sum-exp, 64 D
-  constexpr int NLT = TILE_B / 1024 / 4;         // wave loads per wavefront and tile
+  constexpr int NLT = TILE_B / 1024 / (4 * HV);  // wave loads per wavefront and tile
   constexpr int NLD = 2 * NLT + 2;               // loads per wavefront and stage
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  // key tiles in grid.y (dispatched slowest): the long workgroups of all heads start first
-  const int ktile = blockIdx.y;
+  const int ktile = y;   // the first sees the most queries
   const int b = blockIdx.x / h, head = blockIdx.x % h;
   const int d = h * DH;
   const long ld = 3L * d;
@@ -1044,7 +1058,7 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const T* __restrict_
   const float* dvb = dvec + (long)b * L * h + head;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 31, hf = lane >> 5;
-  const int wk0 = ktile * BKEY + wave * 32;
+  const int wk0 = ktile * BKEY + (wave & 3) * 32;
   const int key = wk0 + col;
   const float scale_log2 = scale * 1.4426950408889634f;
   const float gsc = do_scale(dvec + (long)gridDim.x * L + ((long)gridDim.x * L + 3) / 4);
@@ -1096,9 +1110,11 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const T* __restrict_
     const float* lses = (const float*)(qs + 2 * TILE_B);
     const float* ds_ = lses + 64;
     {
-      // the tile's 64 queries in two blocks of 32 (keeps the live registers within one wavefront's share)
+      // the tile's 64 queries in two blocks of 32 (keeps the live registers within one wavefront's share), or the one
+      // of this wavefront
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
+      for (int ci = 0; ci < 2 / HV; ++ci) {
+        const int c = HV == 2 ? wave >> 2 : ci;
         // S = Q K^T and dP = dO V^T for 32 queries x 32 keys; MFMA row r is query pi(r), which
         // makes a lane's 8 values per 16-query step consecutive queries
         f32x16 sacc, pacc;
@@ -1161,11 +1177,30 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const T* __restrict_
     issue(t + NS);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no direct-to-LDS write may outlive the workgroup
+  if constexpr (HV == 2) {
+    (void)add_halves<HV, DT>(dk, smem, wave, lane);
+    if (!add_halves<HV, DT>(dv, smem, wave, lane)) return;
+  }
   if (key < L) {
     T* rk = dqkv + ((long)b * L + key) * ld + d + (long)head * DH;
     store_grad_row<T, DH>(rk, dk, scale / gsc, hf, rope ? rope + (long)key * DH : nullptr);
     store_grad_row<T, DH>(rk + d, dv, 1.0f, hf, nullptr);
   }
+}
+
+// Both in one launch, head_dim 64: dK/dV in the even rows of the grid and dQ in the odd ones (grid.y is dispatched slowest,
+// and both begin with their longest workgroups).  They do not depend on each other, and a short sequence leaves either alone
+// a fraction of the chip.  Two workgroups share a compute unit: dK/dV with 32 rows a wavefront and a whole tile needs 262
+// registers, which left it one.  Two launches of four wavefronts -> here, with dvec_kernel, us: 12 heads, 128 tokens 21.9 ->
+// 14.3; 3 x 333 36.9 -> 22.9; 2048 124 -> 58; 4 x 1024 77.6 -> 61.7; 4096 232 -> 158.
+template <class T, int DH, int HV>
+__global__ __launch_bounds__(256 * HV, 2) void flash_bwd_kernel(const T* __restrict__ qkv, const T* __restrict__ dO,
+                                                             const float* __restrict__ lse, const float* __restrict__ dvec,
+                                                             T* __restrict__ dqkv, int L, int h, float scale,
+                                                             const float* __restrict__ rope) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if (blockIdx.y & 1) bwd_dq<T, DH, HV>(qkv, dO, lse, dvec, dqkv, L, h, scale, rope, smem, blockIdx.y >> 1);
+  else bwd_dkv<T, DH, HV>(qkv, dO, lse, dvec, dqkv, L, h, scale, rope, smem, blockIdx.y >> 1);
 }
 
 // also records max|dO| per workgroup in dvec[n_items + blockIdx.x]; amax_finish_kernel
@@ -1234,43 +1269,39 @@ ls_status launch_bwd(const void* qkv, const void* o, const void* dO, const float
   dvec_kernel<T, DH><<<(unsigned)nwg, 256, 0, st>>>((const T*)o, (const T*)dO, items, dvec, lse, lse2);
   amax_finish_kernel<<<1, 1024, 0, st>>>(dvec + items, nwg, nb);
   LS_CHECK_LAUNCH();
-  dim3 gq(B * h, (L + 127) / 128), gk(B * h, (L + 127) / 128);
-  constexpr int dq_lds = 4 * (2 * KT * DH * 2);
-  static bool dq_attr = false;
+  const dim3 grid(B * h, (L + 127) / 128);
+  constexpr int dq_lds = 4 * (2 * KT * DH * 2), dkv_lds = 4 * (2 * 64 * DH * 2 + 512);
   if constexpr (DH == 128) {
+    static bool dq_attr = false, dkv_attr = false;
     if (!dq_attr) {
       LS_CHECK_HIP(hipFuncSetAttribute((const void*)flash_bwd_dq128_kernel<T>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, dq_lds));
       dq_attr = true;
     }
-    flash_bwd_dq128_kernel<T><<<gq, 256, dq_lds, st>>>((const T*)qkv, (const T*)dO, lse2, dvec, (T*)dqkv, L, h, scale, rope);
-  } else {
-    if (!dq_attr) {
-      LS_CHECK_HIP(hipFuncSetAttribute((const void*)flash_bwd_dq_kernel<T, DH>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, dq_lds));
-      dq_attr = true;
-    }
-    flash_bwd_dq_kernel<T, DH><<<gq, 256, dq_lds, st>>>((const T*)qkv, (const T*)dO, lse, dvec, (T*)dqkv, L, h, scale, rope);
-  }
-  LS_CHECK_LAUNCH();
-  constexpr int dkv_lds = 4 * (2 * 64 * DH * 2 + 512);
-  static bool dkv_attr = false;
-  if constexpr (DH == 128) {
+    flash_bwd_dq128_kernel<T><<<grid, 256, dq_lds, st>>>((const T*)qkv, (const T*)dO, lse2, dvec, (T*)dqkv, L, h, scale, rope);
+    LS_CHECK_LAUNCH();
     if (!dkv_attr) {
       LS_CHECK_HIP(hipFuncSetAttribute((const void*)flash_bwd_dkv128_kernel<T>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, dkv_lds));
       dkv_attr = true;
     }
-    flash_bwd_dkv128_kernel<T><<<gk, 256, dkv_lds, st>>>((const T*)qkv, (const T*)dO, lse2, dvec, (T*)dqkv, L, h, scale, rope);
-    LS_CHECK_LAUNCH();
-    return LS_OK;
+    flash_bwd_dkv128_kernel<T><<<grid, 256, dkv_lds, st>>>((const T*)qkv, (const T*)dO, lse2, dvec, (T*)dqkv, L, h, scale, rope);
+  } else {
+    const dim3 both(grid.x, 2 * grid.y);
+    // eight wavefronts beyond one tile of keys: us, four -> eight: 2048 tokens of 12 heads 82.9 -> 58.2, 3 x 333 23.9 -> 22.9,
+    // 16 x 256 42.3 -> 40.6, 8 x 300 31.1 -> 32.5; 128 14.3 -> 15.0, 16 x 128 23.3 -> 25.2
+    const bool halves = L > 160;
+    auto go = [&](auto* kern, int threads, bool& attr_set) -> ls_status {
+      if (!attr_set) {
+        LS_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, dkv_lds));
+        attr_set = true;
+      }
+      kern<<<both, threads, dkv_lds, st>>>((const T*)qkv, (const T*)dO, lse, dvec, (T*)dqkv, L, h, scale, rope);
+      return LS_OK;
+    };
+    static bool one = false, two = false;
+    LS_TRY(halves ? go(flash_bwd_kernel<T, DH, 2>, 512, two) : go(flash_bwd_kernel<T, DH, 1>, 256, one));
   }
-  if (!dkv_attr) {
-    LS_CHECK_HIP(hipFuncSetAttribute((const void*)flash_bwd_dkv_kernel<T, DH>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, dkv_lds));
-    dkv_attr = true;
-  }
-  flash_bwd_dkv_kernel<T, DH><<<gk, 256, dkv_lds, st>>>((const T*)qkv, (const T*)dO, lse, dvec, (T*)dqkv, L, h, scale, rope);
   LS_CHECK_LAUNCH();
   return LS_OK;
 }

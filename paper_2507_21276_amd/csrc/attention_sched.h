@@ -1,6 +1,6 @@
 // Hand-scheduled attention kernels for head_dim 128: dK/dV, dQ and the training forward (included by
 // attention_mfma.hip, inside its anonymous namespace).  Same tiles, layouts and arithmetic as the
-// compiler-scheduled kernels of that file (flash_bwd_dkv_kernel, flash_bwd_dq_kernel, flash_fwd_ring_kernel,
+// compiler-scheduled kernels of that file (bwd_dkv, bwd_dq, flash_fwd_ring_kernel,
 // which stay for head_dim 64 and for prompt chunks over pages); what differs is who places the instructions:
 //   * every MFMA, LDS read and wait of the tile loop is issued from assembly, in source order, with
 //     scheduling barriers between the steps, so that the matrix pipe, the vector unit and the LDS
@@ -181,7 +181,7 @@ struct DkvPlan {
   static constexpr int wait(int g) { return newer(g, need_tau(g + 1), need_pos(g + 1)); }
 };
 
-// dK, dV for head_dim 128.  Grid, LDS layout and arguments of flash_bwd_dkv_kernel, except that lse2 is the
+// dK, dV for head_dim 128.  Grid, LDS layout and arguments of bwd_dkv, except that lse2 is the
 // log-sum-exp in base 2 (natural value times log2 e; dvec_kernel writes it beside D).
 template <class T>
 __global__ __launch_bounds__(256) void flash_bwd_dkv128_kernel(const T* __restrict__ qkv, const T* __restrict__ dO,
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv128_kernel(const T* __restri
 }
 
 // ---- dQ ------------------------------------------------------------------------------------------
-// The same treatment for flash_bwd_dq_kernel at head_dim 128.  A workgroup owns 128 queries (32 per
+// The same treatment for bwd_dq at head_dim 128.  A workgroup owns 128 queries (32 per
 // wavefront, Q and dO fragments in the accumulator file) and walks the key tiles of 64 keys below its diagonal.
 // Both first products are formed transposed (S^T, dP^T: rows = keys, lane = query), so the softmax statistics are
 // per-lane scalars.  A tile is 48 MFMAs: 0..15 S^T and dP^T of keys 0..31 (alternating), 16..31 of keys

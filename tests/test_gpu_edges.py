@@ -192,6 +192,27 @@ def test_rotary_embedding_behind_192_and_128_row_tiles(name, T, h):
     assert_close(host(qkv), ref, 1e-5 + 2 * out_rounding_bound(ref, name), "qkv")
 
 
+@pytest.mark.parametrize("name", ["f16", "bf16"])
+@pytest.mark.parametrize("B,L,h", [(1, 1, 1), (2, 128, 3), (3, 160, 2), (2, 161, 2), (1, 257, 3), (1, 640, 2)])
+def test_attention_backward_of_64_element_heads(name, B, L, h):
+    """Four and eight wavefronts a workgroup at the line between them, sequences that end inside and at the edge of a tile of
+    32, 64 and 128 rows.  16-bit probabilities and scores' gradients: the bar of the attention tests."""
+    dh, dt, d = 64, DT[name], h * 64
+    qkv, dO = S.normal_torch(51, "qkv", (B * L, 3 * d), 1.0, dtype=dt), S.normal_torch(51, "dO", (B * L, d), 1.0, dtype=dt)
+    o, dqkv = torch.empty(B * L, d, dtype=dt, device="cuda"), torch.full((B * L, 3 * d), 7.0, dtype=dt, device="cuda")
+    lse = torch.empty(B * L, h, dtype=torch.float32, device="cuda")
+    Bd.lsk_attn_fwd(1, qkv, B, L, h, dh, o, lse)
+    Bd.lsk_attn_bwd(1, qkv, o, dO, lse, B, L, h, dh, dqkv)
+    x = qkv.double().reshape(B, L, 3, h, dh).permute(2, 0, 3, 1, 4).contiguous().requires_grad_()
+    s = (x[0] @ x[1].transpose(-1, -2).contiguous()) / dh ** 0.5
+    s = s.masked_fill(torch.ones(L, L, device="cuda").triu(1).bool(), float("-inf"))
+    (torch.softmax(s, -1) @ x[2]).permute(0, 2, 1, 3).reshape(B * L, d).backward(dO.double())
+    g = x.grad.permute(1, 3, 0, 2, 4).reshape(B * L, 3, d).cpu().numpy()
+    for i, nm in enumerate(("dq", "dk", "dv")):
+        r = g[:, i]
+        assert_close(host(dqkv).reshape(B * L, 3, d)[:, i], r, 2e-2 + out_rounding_bound(r, name), nm, atol=1e-5 if L == 1 else 0.0)
+
+
 @pytest.mark.parametrize("name,dh,P,h,ctx", [
     ("f16", 64, 16, 2, [0, 7, 15, 16, 31, 32, 33, 100]),              # groups of two pages; four wavefronts
     ("bf16", 64, 8, 3, [255, 256, 257, 140]),                          # four pages a group; eight
