@@ -136,6 +136,7 @@ ls_status lsk_gemm_grads(int, int, int, int, const void*, const void*, const voi
 bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim, bool pages);
 size_t gemm_dma_wgrad_scratch_floats(long M, long N);
 bool decode_gemv_covers(int dt, int param_dtype, int T, int d, int F, int dh);
+bool decode_rows_covers(int dt, int param_dtype, int T, int d, int F, int dh);
 ls_status gemm_dma_splitk_partials(int, int, int, int, const void*, long, const void*, long, float*, size_t, int*,
                                    hipStream_t);
 extern "C" {
@@ -150,6 +151,12 @@ ls_status lsk_gemv_norm_qkv(int, int, int, int, const float*, int, const void*, 
 ls_status lsk_gemv_norm_act(int, int, int, int, int, const float*, int, const void*, const void*, float, const void*,
                             const void*, void*, void*);
 ls_status lsk_gemv_resid(int, int, int, int, const void*, const void*, const void*, const float*, float*, void*);
+ls_status lsk_rows_norm_qkv(int, int, int, int, const float*, int, const void*, const void*, float, const void*,
+                            const void*, const int32_t*, const int32_t*, const float*, void*, void*, void*,
+                            const int32_t*, int, int, void*);
+ls_status lsk_rows_norm_act(int, int, int, int, int, const float*, int, const void*, const void*, float, const void*,
+                            const void*, void*, void*);
+ls_status lsk_rows_resid(int, int, int, int, const void*, const void*, const void*, const float*, float*, void*);
 ls_status lsk_optimizer_layers(int, float, float, float, float, float, float, float, int, int, size_t, int, const size_t*,
                                const size_t*, const float*, float*, float*, float*, void*, int, void*, int, void*);
 ls_status lsk_attn_bwd_rope(int, const void*, const void*, const void*, const float*, int, int, int, int, int,
@@ -544,10 +551,11 @@ ls_status block_forward_fused(const ls_stage* s, int l, int T, const FwdBufs& f,
                                pptr(s, nx.n1_g), gpt ? pptr(s, nx.n1_b) : nullptr, pt, c.norm_eps, f.h1, mt, st);
 }
 
-// Serving calls of one to four rows: matrix-vector kernels that take the steps around each projection with them
-ls_status block_forward_gemv(const ls_stage* s, int l, int T, const FwdBufs& f, const int32_t* pos, const int32_t* req,
-                             int B, const ls_kv* kv, int max_ctx, const int32_t* chunk_start, int n_decode,
-                             hipStream_t st) {
+// Serving calls of few rows (matrix-vector kernels), and of up to 64 on a small stage (`rows`): kernels that take the steps
+// around each projection with them
+ls_status block_forward_few(const ls_stage* s, int l, int T, const FwdBufs& f, const int32_t* pos, const int32_t* req,
+                            int B, const ls_kv* kv, int max_ctx, const int32_t* chunk_start, int n_decode, bool rows,
+                            hipStream_t st) {
   const ls_config& c = s->cfg;
   const LayerOff& o = s->off[l];
   const int d = c.d_model, F = c.d_ff, mt = c.mma_dtype;
@@ -556,15 +564,26 @@ ls_status block_forward_gemv(const ls_stage* s, int l, int T, const FwdBufs& f, 
   const size_t slab = (size_t)kv->n_pages * c.n_heads * c.page_size * c.head_dim * osz(s);
   void* kp = (char*)kv->k_pool + (size_t)l * slab;
   void* vp = (char*)kv->v_pool + (size_t)l * slab;
-  LS_TRY(lsk_gemv_norm_qkv(mt, T, c.n_heads, c.head_dim, f.x, nk, pptr(s, o.n1_g), gpt ? pptr(s, o.n1_b) : nullptr,
-                           c.norm_eps, wptr(s, o.w_qkv), gpt ? pptr(s, o.b_qkv) : nullptr, pos, req,
-                           gpt ? nullptr : s->rope_table, f.qkv, kp, vp, kv->block_table, kv->max_pages_per_req,
-                           c.page_size, st));
+  auto* norm_qkv = rows ? lsk_rows_norm_qkv : lsk_gemv_norm_qkv;
+  auto* norm_act = rows ? lsk_rows_norm_act : lsk_gemv_norm_act;
+  auto* resid = rows ? lsk_rows_resid : lsk_gemv_resid;
+  LS_TRY(norm_qkv(mt, T, c.n_heads, c.head_dim, f.x, nk, pptr(s, o.n1_g), gpt ? pptr(s, o.n1_b) : nullptr,
+                  c.norm_eps, wptr(s, o.w_qkv), gpt ? pptr(s, o.b_qkv) : nullptr, pos, req,
+                  gpt ? nullptr : s->rope_table, f.qkv, kp, vp, kv->block_table, kv->max_pages_per_req,
+                  c.page_size, st));
   LS_TRY(serve_attention(s, T, f, pos, req, B, kv, kp, vp, max_ctx, chunk_start, n_decode, st));
-  LS_TRY(lsk_gemv_resid(mt, T, d, d, f.o, wptr(s, o.w_o), gpt ? pptr(s, o.b_o) : nullptr, f.x, f.x1, st));
-  LS_TRY(lsk_gemv_norm_act(mt, T, d, F, c.act, f.x1, nk, pptr(s, o.n2_g), gpt ? pptr(s, o.n2_b) : nullptr, c.norm_eps,
-                           wptr(s, o.w_up), gpt ? pptr(s, o.b_up) : nullptr, f.act, st));
-  return lsk_gemv_resid(mt, T, d, F, f.act, wptr(s, o.w_dn), gpt ? pptr(s, o.b_dn) : nullptr, f.x1, f.y, st);
+  LS_TRY(resid(mt, T, d, d, f.o, wptr(s, o.w_o), gpt ? pptr(s, o.b_o) : nullptr, f.x, f.x1, st));
+  LS_TRY(norm_act(mt, T, d, F, c.act, f.x1, nk, pptr(s, o.n2_g), gpt ? pptr(s, o.n2_b) : nullptr, c.norm_eps,
+                  wptr(s, o.w_up), gpt ? pptr(s, o.b_up) : nullptr, f.act, st));
+  if (rows && T > 16 && fused_decode_ok(s, T)) {
+    // 48 workgroups over 3072 columns of 32 rows take longer than the same split over k and a sum: 11.8 us, 5.7 + 3.5 (16
+    // rows: 8.9)
+    int splits = 0;
+    LS_TRY(lsk_gemm_partials(mt, T, d, F, f.act, F, wptr(s, o.w_dn), F, f.scratch, serve_scratch_floats(s), &splits, st));
+    return lsk_finish_resid_norm(f.scratch, splits, T, d, gpt ? pptr(s, o.b_dn) : nullptr, f.x1, f.y, -1, nullptr, nullptr,
+                                 c.dtype, c.norm_eps, nullptr, mt, st);
+  }
+  return resid(mt, T, d, F, f.act, wptr(s, o.w_dn), gpt ? pptr(s, o.b_dn) : nullptr, f.x1, f.y, st);
 }
 
 ls_status check_kv(const ls_stage* s, const ls_kv* kv, int B, const int32_t* new_tokens, int* max_ctx) {
@@ -596,12 +615,13 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
   const ls_config& c = s->cfg;
   LS_TRY(lsk_convert(X, c.io_dtype, w.xa, LS_F32, (size_t)T * c.d_model, st));
   const bool gemv = decode_gemv_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
+  const bool rows = !gemv && decode_rows_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
   const bool fused = fused_decode_ok(s, T);
   bool h1_ready = false;
   for (int l = 0; l < c.n_layers; ++l) {
     FwdBufs f{w.xa, w.xb, w.xa, nullptr, nullptr, nullptr, nullptr, nullptr,
               w.h, w.qkv, w.o, w.h, w.up, w.act, w.scratch};
-    if (gemv) LS_TRY(block_forward_gemv(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, st));
+    if (gemv || rows) LS_TRY(block_forward_few(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, rows, st));
     else if (fused) LS_TRY(block_forward_fused(s, l, T, f, w.pos, w.req, B, kv, max_ctx, chunk_start, n_decode, st));
     else LS_TRY(block_forward(s, l, T, f, w.pos, w.req, B, 0, kv, max_ctx, chunk_start, n_decode, st, &h1_ready));
   }

@@ -267,6 +267,41 @@ def test_decode_of_few_rows(mma, rows, shape):
 
 
 @pytest.mark.parametrize("mma", ["f16", "bf16"])
+@pytest.mark.parametrize("rows", [6, 16, 17, 32, 33])
+@pytest.mark.parametrize("shape", ["gpt", "gpt_narrow", "llama", "llama_heads_of_32"])
+def test_decode_of_up_to_32_rows_on_a_small_stage(mma, rows, shape):
+    """Projections with the norm before and the epilogue behind them: one and two blocks of 16 rows, full and not, and the
+    first batch above them; contractions of fewer chunks than wavefronts and of several per wavefront, the widest norm, both
+    blocks and their row orders, the FFN-down product split and whole.  Bar: that of the stage tests."""
+    cfg = {"gpt": S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=2, d_model=1024, n_heads=16, d_ff=1056),
+           "gpt_narrow": S.scaled(S.CONFIGS["gpt2s_bf16"], n_layers=2, d_model=96, n_heads=3, head_dim=32, d_ff=224),
+           "llama": S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=2, d_model=256, n_heads=2, d_ff=1088),
+           "llama_heads_of_32": S.scaled(S.CONFIGS["llama7b_bf16"], n_layers=1, d_model=160, n_heads=5, head_dim=32, d_ff=352)}[shape]
+    old = [(0, 15, 16, 130, 7, 40)[b % 6] + b // 6 for b in range(rows)]
+    st, flat, _ = make_stage(cfg, mma=mma, io="f32")
+    table, n_pages = S.page_tables(np.array(old), np.ones(rows, np.int64), cfg["page_size"])
+    cache = O.new_cache(cfg, rows)
+    for l in range(cfg["n_layers"]):
+        for b, n in enumerate(old):
+            cache[l][b] = [q(S.normal(11, f"{w}{l}{b}", (n, cfg["n_heads"], cfg["head_dim"])), mma) for w in "KV"]
+    kp, vp = pool_from_oracle_cache(cache, table, n_pages, cfg)
+    kv = Bd.KV(st, n_pages, table, old)
+    kv.k_pool.copy_(dev(kp, DT[mma]).view_as(kv.k_pool))
+    kv.v_pool.copy_(dev(vp, DT[mma]).view_as(kv.v_pool))
+    X = S.make_activations(cfg, "X", (rows, cfg["d_model"]))
+    Y = torch.empty(rows, cfg["d_model"], dtype=torch.float32, device="cuda")
+    st.stage_decode(dev(X, torch.float32), rows, kv, Y, st.new_workspace(rows))
+    ref = O.stage_decode(cfg, flat.astype(np.float64), X.astype(np.float64), cache)
+    assert_close(host(Y), ref, TOL["bf16"], shape)
+    for pool, i in ((kv.k_pool, 0), (kv.v_pool, 1)):
+        got = host(pool).reshape(kp.shape)
+        for b, n in enumerate(old):
+            row = gather_rows_from_pool(got, table, b, n, n + 1)
+            assert_close(row, np.stack([cache[l][b][i][n:n + 1] for l in range(cfg["n_layers"])]), TOL["bf16"], f"row {b}")
+    st.close()
+
+
+@pytest.mark.parametrize("mma", ["f16", "bf16"])
 @pytest.mark.parametrize("rows", [(129,), (48, 152), (100, 157)])
 def test_prompt_chunks_with_split_projections(mma, rows):
     """Projections of 129, 200 and 257 rows left as partial products (128 x 128 tiles; 256 x 256 for QKV at 257) of the
