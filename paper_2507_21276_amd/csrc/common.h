@@ -66,7 +66,7 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // block-wide sum for blockDim.x a multiple of 64, up to 1024; `red` has >= 16 floats
 __device__ __forceinline__ float block_sum(float v, float* red) {
-  v = wave_sum(v);
+  v = wave_total(v);
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[w] = v;

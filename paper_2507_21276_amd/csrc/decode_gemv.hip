@@ -111,7 +111,7 @@ __global__ __launch_bounds__(NT) void gemv_kernel(GemvArgs g) {
     // sums over the workgroup, of all rows between one pair of barriers
     auto sums = [&](float (&t)[M]) {
 #pragma unroll
-      for (int m = 0; m < M; ++m) t[m] = wave_sum(t[m]);
+      for (int m = 0; m < M; ++m) t[m] = wave_total(t[m]);
       __syncthreads();
       if (lane == 0)
 #pragma unroll

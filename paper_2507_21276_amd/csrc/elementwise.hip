@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(int kind, const floa
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += v[it][i];
   }
-  const float mu = kind == 0 ? wave_sum(s) / d : 0.f;
+  const float mu = kind == 0 ? wave_total(s) / d : 0.f;
   float q = 0.f;
 #pragma unroll
   for (int it = 0; it < NIT; ++it)
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(int kind, const floa
         const float t = v[it][i] - mu;
         q += t * t;
       }
-  const float r = 1.0f / sqrtf(wave_sum(q) / d + eps);
+  const float r = 1.0f / sqrtf(wave_total(q) / d + eps);
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int c = lane * 8 + it * 512;
@@ -321,8 +321,8 @@ __global__ __launch_bounds__(512) void norm_bwd_rows_kernel(const TD* dh, const 
         }
       }
     }
-    const float m1 = KIND == 0 ? wave_sum(s1) / d : 0.f;
-    const float m2 = wave_sum(s2) / d;
+    const float m1 = KIND == 0 ? wave_total(s1) / d : 0.f;
+    const float m2 = wave_total(s2) / d;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int c = lane * 8 + it * 512;
