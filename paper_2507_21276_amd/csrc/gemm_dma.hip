@@ -605,7 +605,25 @@ ls_status gemm_dma_splitk_try(int op_dtype, int M, int N, int K, const void* A, 
   return LS_ESTATE;
 }
 
-ls_status gemm_dma16_partials(int, int, int, int, const void*, long, const void*, long, float*, int, hipStream_t);
+ls_status gemm_dma16_partials(int, int, int, int, const void*, long, const void*, long, float*, int, int, hipStream_t);
+
+namespace {
+// Parts in which 128 x 256 tiles (three LDS buffers, one workgroup a compute unit) take a product of up to 256 rows, or 0
+// where they leave too much of the chip without one.  A workgroup has twice the weights in flight of two that share a unit
+// with two buffers each, and fewer parts are to be written and summed.  More workgroups than about 200 gain nothing while a
+// part is short.  us (parts), weights from HBM, smaller tiles -> these: 128 rows, 12288 columns over 4096 29.4 (5) -> 26.9 (4),
+// 22016 over 4096 55.3 (2) -> 50.6 (2), 27648 over 5120 77.0 (2) -> 67.8 (2), 5120 over 13824 38.5 (12) -> 34.5 (10); 64
+// rows, 12288 over 4096 26.8 (8) -> 24.9 (4); 248 rows, 4096 over 4096 25.0 (8) -> 20.0 (6), 4096 over 11008 42.7 (8) -> 39.3 (8),
+// 5120 over 13824 59.2 (6) -> 54.9 (6).  Where half of the chip has no workgroup it is the other way round: 64 rows, 22016 over
+// 4096 41.1 (4), 47.4 (2).
+int parts_of_128x256(int M, int N, int nk) {
+  const int tiles = (M + 127) / 128 * ((N + 255) / 256);
+  int s = 256 / tiles < 16 ? 256 / tiles : 16;
+  while (s > 4 && s * tiles > 208 && nk / s < 16) --s;
+  while (s > 1 && nk / s < 6) --s;
+  return s * tiles >= (M <= 64 ? 190 : 160) ? s : 0;
+}
+}  // namespace
 
 // The first half of gemm_dma_splitk_try: the partial products stay in `scratch` as [splits][M][N] for a
 // caller that sums them together with its next step.  LS_ESTATE when the shape does not call for a split.
@@ -632,7 +650,7 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   const int kind = M >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM;
   if (wide) {
     LsTimed timed(kind, st);
-    LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, s256, st));
+    LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, s256, 256, st));
     *splits_out = s256;
     return LS_OK;
   }
@@ -642,10 +660,16 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   while (splits > 1 && nk / splits < 8) --splits;
   while (splits > 1 && (size_t)splits * M * N > scratch_floats) --splits;
   if (splits < 2) return LS_ESTATE;
+  LsTimed timed(kind, st);
+  const int fewer = M <= 256 ? parts_of_128x256(M, N, nk) : 0;
+  if (fewer >= 2 && fewer <= splits) {
+    LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, fewer, 128, st));
+    *splits_out = fewer;
+    return LS_OK;
+  }
   DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
             nullptr, 0};
   g.split_stride = (long)M * N;
-  LsTimed timed(kind, st);
   if (op_dtype == LS_BF16) LS_TRY((launch<bf16_t, 128, 128, true, true, 2>(g, st, splits)));
   else if (op_dtype == LS_F16) LS_TRY((launch<f16_t, 128, 128, true, true, 2>(g, st, splits)));
   else return LS_ESTATE;
@@ -932,6 +956,14 @@ ls_status gemm_dma_skinny_partials(int op_dtype, int M, int N, int K, const void
   while (splits > 1 && nk / splits < 6) --splits;
   while (splits > 1 && (size_t)splits * M * N > scratch_floats) --splits;
   if ((size_t)splits * M * N > scratch_floats) return LS_ESTATE;
+  // (fewer rows than 48 would be a small part of such a tile: 16 rows of 12288 columns over 4096 22.7 us, 23.9; up to 64
+  // rows the parts saved have to pay for half of it: 64 rows of 4096 columns over 11008 24.3 us (16), 25.2 (13))
+  const int fewer = M >= 48 && N >= 256 ? parts_of_128x256(M, N, nk) : 0;
+  if (fewer > 0 && (M > 64 ? fewer <= splits : 10 * fewer <= 8 * splits)) {
+    LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, fewer, 128, st));
+    *splits_out = fewer;
+    return LS_OK;
+  }
   DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
             nullptr, 0};
   g.split_stride = (long)M * N;

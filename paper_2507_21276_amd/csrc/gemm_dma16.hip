@@ -616,12 +616,12 @@ bool gemm_qkv_rope_fuses(int op_dtype, int T, int d, int head_dim, bool pages) {
 // Partial products [splits][M][N] (fp32) of the forward layout, whatever the number of tiles.  The caller has checked
 // sizes (K a multiple of 64, at least one k tile per part, N % 4 == 0) and alignment (16 bytes, ld % 8 == 0).
 ls_status gemm_dma16_partials(int op_dtype, int M, int N, int K, const void* A, long lda, const void* B, long ldb,
-                              float* scratch, int splits, hipStream_t st) {
+                              float* scratch, int splits, int rows, hipStream_t st) {
   DmaArgs g{M, N, K, A, lda, 1, B, ldb, 1, scratch, N, LS_F32, nullptr, 0, nullptr, 0, 0, nullptr, 0, 0, 0, nullptr,
             nullptr, 0};
   g.split_stride = (long)M * N;
-  if (op_dtype == LS_BF16) return launch16<bf16_t, true, true, 2>(g, 256, st, splits);
-  if (op_dtype == LS_F16) return launch16<f16_t, true, true, 2>(g, 256, st, splits);
+  if (op_dtype == LS_BF16) return launch16<bf16_t, true, true, 2>(g, rows, st, splits);
+  if (op_dtype == LS_F16) return launch16<f16_t, true, true, 2>(g, rows, st, splits);
   return LS_ESTATE;
 }
 

@@ -56,6 +56,19 @@ def test_partials_sum_to_the_product(name, M, N, K):
         partials_of(name, M, N, K, 41, floats=M * N - 4)
 
 
+@pytest.mark.parametrize("name", ["f16", "bf16"])
+@pytest.mark.parametrize("M,N,K,parts", [(47, 12288, 4096, 8), (48, 12288, 4096, 4), (127, 12296, 4160, 4), (128, 15368, 5184, 4),
+                                         (64, 27648, 1088, 2), (65, 27648, 320, 1)])
+def test_partials_from_tiles_of_256_columns(name, M, N, K, parts):
+    """The first batch that takes them and the last that does not, columns that end inside a tile, parts of unequal k tiles
+    and of two short ones, a contraction too short to split."""
+    x, w, part, splits = partials_of(name, M, N, K, 42)
+    assert splits == parts
+    got = part[:splits * M * N].view(splits, M, N).double().sum(0)
+    ref = x.double() @ w.double().T.contiguous()
+    assert_close(host(got), host(ref), 1e-5, "sum of partials")
+
+
 @pytest.mark.parametrize("splits", range(1, 19))
 def test_parts_are_summed_in_ascending_order(splits):
     """Every count of a group of eight parts and its rest: bit-equal to the parts added one after the other in fp32."""
