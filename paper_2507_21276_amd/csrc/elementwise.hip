@@ -436,18 +436,28 @@ __global__ __launch_bounds__(256) void norm_bwd_apply_kernel(int kind, const TD*
   Ld8<float>::store(p + d, db);
 }
 
+// The column sums of several norm backwards over the same rows: set i = blockIdx.y has its partial sums at
+// partial + i * stride and its results in block i / 2 of the gradient vector, at first (i even) or second.
+struct NormSums {
+  const float* partial; size_t stride;
+  float* grad; size_t per_block;   // elements of a block
+  size_t gamma[2], beta[2];        // offsets in a block
+  int has_gamma, has_beta;
+};
+
 // 32 columns (eight float4 lanes) x 32 row groups per workgroup; the 32 partial sums of a
 // column are combined in a fixed order through LDS.  d % 4 == 0.
-__global__ __launch_bounds__(256) void norm_bwd_finish_kernel(const float* partial, int nwg, int d, float* dgamma,
-                                                              float* dbeta, int accumulate, const float* alpha) {
+__global__ __launch_bounds__(256) void norm_bwd_finish_kernel(NormSums s, int nwg, int d, int accumulate, const float* alpha) {
   __shared__ float sg[32][32], sb[32][32];
+  const float* partial = s.partial + blockIdx.y * s.stride;
+  float* grad = s.grad + (blockIdx.y >> 1) * s.per_block;
   const int cg = threadIdx.x & 7, rg = threadIdx.x >> 3;
   const int i = blockIdx.x * 32 + cg * 4;
   f32x4 g = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
   if (i < d)
     for (int w = rg; w < nwg; w += 32) {
       g += *(const f32x4*)(partial + (size_t)w * 2 * d + i);
-      if (dbeta) b += *(const f32x4*)(partial + (size_t)w * 2 * d + d + i);
+      if (s.has_beta) b += *(const f32x4*)(partial + (size_t)w * 2 * d + d + i);
     }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -464,8 +474,9 @@ __global__ __launch_bounds__(256) void norm_bwd_finish_kernel(const float* parti
     tb += sb[k][threadIdx.x];
   }
   if (alpha) { tg *= *alpha; tb *= *alpha; }
-  if (dgamma) dgamma[col] = accumulate ? dgamma[col] + tg : tg;
-  if (dbeta) dbeta[col] = accumulate ? dbeta[col] + tb : tb;
+  float *dgamma = grad + s.gamma[blockIdx.y & 1] + col, *dbeta = grad + s.beta[blockIdx.y & 1] + col;
+  if (s.has_gamma) *dgamma = accumulate ? *dgamma + tg : tg;
+  if (s.has_beta) *dbeta = accumulate ? *dbeta + tb : tb;
 }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -794,11 +805,10 @@ size_t lsk_norm_bwd_partial_floats(int T, int d) {
   return (size_t)(by8 > by16 ? by8 : by16) * 2 * d + 2 * (size_t)T;
 }
 
-ls_status lsk_norm_bwd_scaled(int kind, const void* dh, int dhdt, const float* x, const float* mean,
-                              const float* rstd, const void* gamma, int pdt, int T, int d,
-                              const float* dres, float* dx, void* dx16, int dx16dt, float* dgamma,
-                              float* dbeta, int accumulate, float* partial, const float* alpha_dev,
-                              void* stream) {
+// dx, and the column sums of `chunks` runs of rows in partial, for lsk_norm_bwd_sums
+ls_status lsk_norm_bwd_partials(int kind, const void* dh, int dhdt, const float* x, const float* mean, const float* rstd,
+                                const void* gamma, int pdt, int T, int d, const float* dres, float* dx, void* dx16,
+                                int dx16dt, float* partial, int* chunks, void* stream) {
   LS_REQUIRE(dh && x && rstd && gamma && dx && partial && T > 0 && d > 0, "norm_bwd: bad argument");
   LS_REQUIRE(kind == 1 || mean, "norm_bwd: LayerNorm needs the saved mean");
   LS_REQUIRE(d % 8 == 0, "norm_bwd: d_model must be a multiple of 8");
@@ -811,10 +821,35 @@ ls_status lsk_norm_bwd_scaled(int kind, const void* dh, int dhdt, const float* x
   else if (dhdt == LS_BF16) LS_TRY(launch_norm_bwd<bf16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, rows_ok, st));
   else LS_TRY(launch_norm_bwd<f16_t>(kind, dh, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, partial, rows_ok, st));
   LS_CHECK_LAUNCH();
-  if (dgamma || dbeta) {
-    const int rows = rows_ok ? norm_bwd_rows_per_wg(T, d) : NB_ROWS, nchunk = (T + rows - 1) / rows;
-    norm_bwd_finish_kernel<<<(d + 31) / 32, 256, 0, st>>>(partial, nchunk, d, dgamma,
-                                                            kind == 0 ? dbeta : nullptr, accumulate, alpha_dev);
+  const int rows = rows_ok ? norm_bwd_rows_per_wg(T, d) : NB_ROWS;
+  *chunks = (T + rows - 1) / rows;
+  return LS_OK;
+}
+// The gradients of both norms of n blocks from the partial sums of 2 n calls, in one launch: the sets `stride` floats apart,
+// two a block (gamma[0] / beta[0], then gamma[1] / beta[1], elements into a block's part of grad); beta null: none.
+ls_status lsk_norm_bwd_sums(const float* partial, size_t stride, int chunks, int d, int n, float* grad, size_t per_block,
+                            const size_t* gamma, const size_t* beta, int accumulate, const float* alpha_dev, void* stream) {
+  LS_REQUIRE(partial && grad && gamma && chunks > 0 && d > 0 && n > 0, "norm_bwd_sums: bad argument");
+  const NormSums s{partial, stride, grad, per_block, {gamma[0], gamma[1]}, {beta ? beta[0] : 0, beta ? beta[1] : 0}, 1,
+                   beta != nullptr};
+  norm_bwd_finish_kernel<<<dim3((d + 31) / 32, 2 * n), 256, 0, (hipStream_t)stream>>>(s, chunks, d, accumulate, alpha_dev);
+  LS_CHECK_LAUNCH();
+  return LS_OK;
+}
+ls_status lsk_norm_bwd_scaled(int kind, const void* dh, int dhdt, const float* x, const float* mean,
+                              const float* rstd, const void* gamma, int pdt, int T, int d,
+                              const float* dres, float* dx, void* dx16, int dx16dt, float* dgamma,
+                              float* dbeta, int accumulate, float* partial, const float* alpha_dev,
+                              void* stream) {
+  int chunks = 0;
+  LS_TRY(lsk_norm_bwd_partials(kind, dh, dhdt, x, mean, rstd, gamma, pdt, T, d, dres, dx, dx16, dx16dt, partial, &chunks,
+                               stream));
+  if (dgamma || (dbeta && kind == 0)) {
+    // offsets from one address, which may be either
+    float* base = dgamma ? dgamma : dbeta;
+    const size_t off = dgamma && dbeta ? (size_t)(dbeta - dgamma) : 0;
+    const NormSums s{partial, 0, base, 0, {0, 0}, {off, off}, dgamma != nullptr, dbeta && kind == 0};
+    norm_bwd_finish_kernel<<<(d + 31) / 32, 256, 0, (hipStream_t)stream>>>(s, chunks, d, accumulate, alpha_dev);
     LS_CHECK_LAUNCH();
   }
   return LS_OK;

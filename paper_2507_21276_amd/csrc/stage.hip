@@ -120,6 +120,10 @@ ls_status lsk_grad_scale(const void*, int, size_t, float*, void*);
 ls_status lsk_norm_bwd_scaled(int, const void*, int, const float*, const float*, const float*, const void*, int,
                               int, int, const float*, float*, void*, int, float*, float*, int, float*,
                               const float*, void*);
+ls_status lsk_norm_bwd_partials(int, const void*, int, const float*, const float*, const float*, const void*, int, int, int,
+                                const float*, float*, void*, int, float*, int*, void*);
+ls_status lsk_norm_bwd_sums(const float*, size_t, int, int, int, float*, size_t, const size_t*, const size_t*, int,
+                            const float*, void*);
 ls_status lsk_colsum_partials(const void*, int, int, int, long, float*, void*);
 ls_status lsk_colsum_finish(int, const LsColsum*, int, int, const float*, void*);
 ls_status lsk_attn_prefill_mfma(const void*, int, int, const int32_t*, int, int, const void*, const void*,
@@ -317,8 +321,15 @@ size_t carve_fwd(const ls_stage* s, void* base, int T, FwdWs* w) {
   return b.used;
 }
 
+// Whether the column sums of all norms of a backward pass are kept and finished by one launch (in place of one of 3 - 5 us
+// each: six blocks of d 768, 2 x 3 x 333 tokens 2684 -> 2615 us) or each at once: 64 MB of them are 8192 rows of those blocks, and more
+// rows than that are worth the launches.
+constexpr size_t kNormSumsBytes = (size_t)64 << 20;
+bool norm_sums_together(size_t floats, int n_layers) { return floats * 4 * 2 * (size_t)n_layers <= kNormSumsBytes; }
+
 // backward scratch
 struct BwdWs {
+  size_t norm_floats;   // of one norm's column sums
   int32_t* pos;
   float *g, *g1, *dvec, *partial, *gscale, *wsplit, *bias_partial;
   size_t wsplit_floats;
@@ -340,8 +351,11 @@ size_t carve_bwd(const ls_stage* s, void* base, int T, BwdWs* w) {
   v.dqkv = b.take(T * 3 * d * e);
   v.d_o = b.take(T * d * e);
   v.dvec = (float*)b.take(lsk_attn_bwd_scratch_floats(1, T, c.n_heads) * 4);
-  const size_t pf = lsk_norm_bwd_partial_floats(T, c.d_model);
-  v.partial = (float*)b.take(pf * 4);
+  // the column sums of every norm's backward, finished together; up to 64 MB of them (see norm_sums_together)
+  v.norm_floats = align_up(lsk_norm_bwd_partial_floats(T, c.d_model), 64);
+  const size_t one = v.norm_floats * 4;
+  v.partial = (float*)b.take(norm_sums_together(v.norm_floats, c.n_layers) ? one * 2 * c.n_layers
+                             : one > kNormSumsBytes ? one : kNormSumsBytes);   // never less for more rows
   // column sums of the four bias gradients of a block, finished together
   v.bias_partial = c.block == LS_BLOCK_GPT_PRELN
                        ? (float*)b.take(lsk_colsum_partial_floats(T, 5 * c.d_model + s->up_cols) * 4) : nullptr;
@@ -890,6 +904,19 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     LS_TRY(weight_grad(K, N, dOut, In, dW));
     return db ? bias_grad(dOut, K, db) : LS_OK;
   };
+  const bool together = norm_sums_together(w.norm_floats, c.n_layers);
+  int chunks = 0;
+  // dx of norm `second` of block l, and its gains' gradients now or with all others
+  auto norm_grads = [&](int l, bool second, const float* x, const float* mean, const float* rstd, const float* dres,
+                        float* dx) -> ls_status {
+    const LayerOff& o = s->off[l];
+    const size_t g = second ? o.n2_g : o.n1_g, b = second ? o.n2_b : o.n1_b;
+    if (together)
+      return lsk_norm_bwd_partials(nk, w.dh, mt, x, mean, rstd, pptr(s, g), pt, T, d, dres, dx, w.g16, mt,
+                                   w.partial + (2 * (size_t)l + second) * w.norm_floats, &chunks, st);
+    return lsk_norm_bwd_scaled(nk, w.dh, mt, x, mean, rstd, pptr(s, g), pt, T, d, dres, dx, w.g16, mt, dParams + g,
+                               gpt ? dParams + b : nullptr, acc, w.partial, inv, st);
+  };
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerOff& o = s->off[l];
     const Saved& v = sv[l];
@@ -909,8 +936,7 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
     // up = h2 W_up^T (+ b_up)
     LS_TRY(map_grads(U, d, w.dup, wptr(s, o.w_up), v.h2, w.dh, dParams + o.w_up, gpt ? dParams + o.b_up : nullptr));
     // h2 = norm2(x1);  g1 = g + norm2_bwd(dh)
-    LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x1, v.mean2, v.rstd2, pptr(s, o.n2_g), pt, T, d, w.g, w.g1, w.g16, mt,
-                        dParams + o.n2_g, gpt ? dParams + o.n2_b : nullptr, acc, w.partial, inv, st));
+    LS_TRY(norm_grads(l, true, v.x1, v.mean2, v.rstd2, w.g, w.g1));
     // x1 = x + o W_o^T (+ b_o)
     LS_TRY(map_grads(d, d, w.g16, wptr(s, o.w_o), v.o, w.d_o, dParams + o.w_o, gpt ? dParams + o.b_o : nullptr));
     if (gpt)
@@ -927,8 +953,13 @@ ls_status stage_train_bwd(ls_stage* s, const void* dY, int B, int L, const void*
       sums_at = w.bias_partial;
     }
     // h1 = norm1(x);  g = g1 + norm1_bwd(dh)
-    LS_TRY(lsk_norm_bwd_scaled(nk, w.dh, mt, v.x_in, v.mean1, v.rstd1, pptr(s, o.n1_g), pt, T, d, w.g1, w.g, w.g16, mt,
-                        dParams + o.n1_g, gpt ? dParams + o.n1_b : nullptr, acc, w.partial, inv, st));
+    LS_TRY(norm_grads(l, false, v.x_in, v.mean1, v.rstd1, w.g1, w.g));
+  }
+  if (together) {   // the blocks follow each other in the parameter vector and are laid out alike
+    const LayerOff& o = s->off[0];
+    const size_t gamma[2] = {o.n1_g, o.n2_g}, beta[2] = {o.n1_b, o.n2_b};
+    LS_TRY(lsk_norm_bwd_sums(w.partial, w.norm_floats, chunks, d, c.n_layers, dParams, s->n_params / c.n_layers, gamma,
+                             gpt ? beta : nullptr, acc, inv, st));
   }
   return lsk_convert_scaled(w.g, LS_F32, dX, c.io_dtype, (size_t)T * d, inv, st);
 }
