@@ -565,7 +565,7 @@ ls_status block_forward_fused(const ls_stage* s, int l, int T, const FwdBufs& f,
                                pptr(s, nx.n1_g), gpt ? pptr(s, nx.n1_b) : nullptr, pt, c.norm_eps, f.h1, mt, st);
 }
 
-// Serving calls of few rows (matrix-vector kernels), and of up to 64 on a small stage (`rows`): kernels that take the steps
+// Serving calls of few rows (matrix-vector kernels), and of up to 32 on a small stage (`rows`): kernels that take the steps
 // around each projection with them
 ls_status block_forward_few(const ls_stage* s, int l, int T, const FwdBufs& f, const int32_t* pos, const int32_t* req,
                             int B, const ls_kv* kv, int max_ctx, const int32_t* chunk_start, int n_decode, bool rows,
