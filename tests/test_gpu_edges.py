@@ -377,3 +377,30 @@ def test_training_with_gradients_split_along_the_contraction(which, B, L, mma):
     _, _, twice = run_train(st, cfg, X, dY, B, L, accumulate_twice=True)
     assert_close(twice, 2 * once, 1e-6, "accumulated gradients")
     st.close()
+
+
+def test_norm_gradients_finished_together_or_one_by_one():
+    """52 norms' pairs of column sums over 16384 rows are more than the 64 MB that are kept for one launch, so every norm is
+    finished by itself; two micro-batches of half the rows are finished together, the second one accumulating.  The
+    same gradients either way, within the fp32 stage's bar (sums of 16384 terms in another order)."""
+    cfg = S.scaled(S.CONFIGS["tiny_gpt_f32"], n_layers=52, d_model=64, n_heads=2, d_ff=64)
+    B, L, d = 32, 512, 64
+    st = Bd.Stage(cfg, io_dtype="f32", mma_dtype="f32")
+    st.ls_bind_params(S.make_params_torch(cfg, 3))
+    X, dY = (S.normal_torch(3, n, (B, L, d), 1.0, dtype=torch.float32) for n in ("X", "dY"))
+
+    def gradients(pieces):
+        b = B // pieces
+        grads = torch.full((st.ls_param_count(),), 7.0, dtype=torch.float32, device="cuda")
+        saved, ws = st.new_saved(b, L), st.new_workspace(b * L)
+        dX = torch.empty_like(X)
+        for i in range(pieces):
+            x, dy, dx = (t[i * b:(i + 1) * b] for t in (X, dY, dX))
+            st.stage_train_fwd(x, b, L, torch.empty_like(x), saved, ws)
+            st.stage_train_bwd(dy, b, L, saved, dx, grads, int(i > 0), ws)
+        return host(grads), host(dX)
+
+    (one, dx1), (two, dx2) = gradients(1), gradients(2)
+    assert_close(two, one, 1e-4, "dParams")
+    assert_close(dx2, dx1, 1e-4, "dX")
+    st.close()
