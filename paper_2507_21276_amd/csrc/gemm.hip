@@ -455,7 +455,6 @@ extern "C" ls_status lsk_gemm_grads(int op_dtype, int T, int K, int N, const voi
                                     void* dIn, float* dW, float* db, int accumulate, const float* alpha_dev, float* scratch,
                                     size_t scratch_floats, int* parts, void* stream) {
   LS_REQUIRE(T > 0 && K > 0 && N > 0 && dOut && W && In && dIn && dW, "gemm_grads: bad argument");
-  LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, stream);
   return gemm_dma_grads(op_dtype, T, K, N, dOut, W, In, dIn, dW, db, accumulate, alpha_dev, scratch, scratch_floats,
                         parts, (hipStream_t)stream);
 }

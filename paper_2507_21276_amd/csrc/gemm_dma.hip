@@ -854,6 +854,7 @@ ls_status gemm_dma_grads(int op_dtype, int T, int K, int N, const void* dOut, co
                            (float)((nkd + ds - 1) / ds) * 0.65f + 5.f + (ds > 1 ? 4.f + (float)MNd * (ds + 1) / 1e6f
                                                                                : td > 256 ? 1e30f : 0.f));
   if (best >= w_us + d_us) return LS_ESTATE;
+  LsTimed timed(T >= 256 ? LSK_TIMED_GEMM : LSK_TIMED_DECODE_GEMM, st);   // a refusal launches nothing and is not recorded
   if (parts) { parts[0] = wparts; parts[1] = dparts; }
 
   float *wp = scratch, *bp = wp + wparts * MNw, *dp = wparts > 1 ? bp + (long)wparts * K : scratch;

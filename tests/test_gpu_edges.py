@@ -404,3 +404,15 @@ def test_norm_gradients_finished_together_or_one_by_one():
     assert_close(two, one, 1e-4, "dParams")
     assert_close(dx2, dx1, 1e-4, "dX")
     st.close()
+
+
+@pytest.mark.parametrize("T,K,N,calls", [(999, 768, 768, 1), (300, 4096, 4096, 0)])
+def test_refused_gradient_launches_are_not_recorded(T, K, N, calls):
+    """A shape that is left to separate launches adds nothing to the recording."""
+    dO, x, w = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((T, K), (T, N), (K, N)))
+    dx, dw = torch.empty_like(x), torch.empty(K, N, device="cuda")
+    scratch = torch.empty(2 * (K * N + K) + T * N, dtype=torch.float32, device="cuda")
+    Bd.lsk_timing_begin()
+    got = Bd.lsk_gemm_grads(dO, w, x, dx, dw, None, scratch)
+    assert (got is not None) == (calls == 1)
+    assert Bd.lsk_timing_end()["gemm"][1] == calls
