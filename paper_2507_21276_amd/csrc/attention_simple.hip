@@ -243,12 +243,14 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(KvView kv, int L, con
     }
 #pragma unroll
     for (int off = LPT; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float m_new = fmaxf(m, mx), alpha = expf(m - m_new);
+    const float m_new = fmaxf(m, mx);
+    // a batch whose scores have all overflowed to -inf counts for nothing beside a finite score, before it or after it
+    const float ref = m_new == -INFINITY ? 0.f : m_new, alpha = expf(m - ref);
     l *= alpha;
     acc *= alpha;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const float p = j0 + u * TPL + tg < nkeys ? expf(s[u] - m_new) : 0.f;
+      const float p = j0 + u * TPL + tg < nkeys ? expf(s[u] - ref) : 0.f;
       l += p;
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, vx[u][e], acc[e]);

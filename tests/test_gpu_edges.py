@@ -270,6 +270,38 @@ def test_fp32_attention_over_batches_of_keys(dh, L):
         assert_close(host(dqkv).reshape(B * L, 3, d)[:, i], g[:, i], 1e-5, nm, atol=1e-5 if L == 1 else 0.0)
 
 
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("dead", [(16, 32), (0, 16), (48, 80), (17, 130)])
+def test_fp32_attention_where_scores_overflow(dh, dead):
+    """Finite queries and keys whose product overflows to -inf, over a wavefront's first batch of 16 keys, its later ones and
+    all of it: weight 0 for these keys, as in float64, where they are -1e40.  Contiguous and paged keys; rows that see no
+    other key are left out.  Bar: that of the attention over batches of keys."""
+    L, h, P = 130, 2, 16
+    d = h * dh
+    qkv = torch.from_numpy(S.normal(15, "qkv", (L, 3 * d)).astype(np.float32)).cuda()
+    x = qkv.view(L, 3, h, dh)
+    x[:, 0, :, 0], x[:, 1, :, 0] = 1e20, 0.0
+    x[dead[0]:dead[1], 1, :, 0] = -1e20
+    Q, K, V = x.double().permute(1, 2, 0, 3).contiguous()
+    s = (Q @ K.transpose(-1, -2).contiguous()) / dh ** 0.5
+    s = s.masked_fill(torch.ones(L, L, device="cuda").triu(1).bool(), float("-inf"))
+    ref = host((torch.softmax(s, -1) @ V).permute(1, 0, 2).reshape(L, d))
+    rows = slice(dead[1] if dead[0] == 0 else 0, L)
+    o, lse = torch.empty(L, d, device="cuda"), torch.empty(L, h, device="cuda")
+    Bd.lsk_attn_fwd(0, qkv, 1, L, h, dh, o, lse)
+    assert_close(host(o)[rows], ref[rows], 1e-5, "o")
+    assert_close(host(lse)[rows], host(torch.logsumexp(s, -1).T.contiguous())[rows], 1e-5, "lse")
+    table, n_pages = S.page_tables(np.array([L]), np.ones(1, np.int64), P, seed=2)
+    bt = torch.as_tensor(table, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.zeros(n_pages, h, P, dh, device="cuda") for _ in range(2))
+    for j in range(L):
+        kp[table[0, j // P], :, j % P], vp[table[0, j // P], :, j % P] = x[j, 1], x[j, 2]
+    o.zero_()
+    Bd.lsk_attn_paged(0, qkv, h, dh, torch.arange(L, dtype=torch.int32, device="cuda"),
+                      torch.zeros(L, dtype=torch.int32, device="cuda"), kp, vp, bt, P, L, o)
+    assert_close(host(o)[rows], ref[rows], 1e-5, "o over pages")
+
+
 @pytest.mark.parametrize("name", ["bf16", "f16"])
 @pytest.mark.parametrize("kind", [Bd.LS_ACT_GELU_TANH, Bd.LS_ACT_GELU_ERF])
 @pytest.mark.parametrize("n", [8, 1000, 1003])
