@@ -107,14 +107,15 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
     }
 #pragma unroll
     for (int off = LPT; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float m_new = fmaxf(m, mx);   // finite: the first token of a unit is in the context
-    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+    const float m_new = fmaxf(m, mx);
+    // a group whose scores have all overflowed to -inf (bf16 operands reach that) counts for nothing beside a finite score
+    const float ref = m_new == -INFINITY ? 0.f : m_new, alpha = __builtin_amdgcn_exp2f(m - ref);
     l *= alpha;
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] *= alpha;
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const float pr = __builtin_amdgcn_exp2f(s[i] - m_new);
+      const float pr = __builtin_amdgcn_exp2f(s[i] - ref);
       l += pr;
       // slots of the last page beyond the context were never written: whatever bit patterns they hold
       // (NaN, infinity) must not reach the sum through 0 * x

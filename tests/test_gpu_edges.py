@@ -246,6 +246,35 @@ def test_decode_attention_plans(name, dh, P, h, ctx):
     assert_close(host(o), ref, 1e-5 + out_rounding_bound(ref, name), "o")
 
 
+@pytest.mark.parametrize("dh,h,ctx", [(64, 1, 511), (64, 40, 300), (128, 1, 1100), (128, 64, 700)])
+def test_decode_attention_where_scores_overflow(dh, h, ctx):
+    """bf16 queries and keys whose product overflows to -inf, one run of tokens after the other, so that every wavefront and
+    every split has groups of nothing else first, later and throughout: weight 0, as in float64, where they are -1e40.
+    Bar: that of the plans above."""
+    P, d, T = 16, h * dh, 5
+    table, n_pages = S.page_tables(np.full(T, ctx), np.ones(T, np.int64), P, seed=6)
+    bt = torch.as_tensor(table, dtype=torch.int32, device="cuda")
+    kp, vp = (S.normal_torch(45, n, (n_pages, h, P, dh), 1.0, dtype=torch.bfloat16) for n in "KV")
+    qkv = S.normal_torch(45, "qkv", (T, 3 * d), 1.0, dtype=torch.bfloat16)
+    qkv[:, :d].view(T, h, dh)[:, :, 0] = 1e20
+    kp[..., 0] = 0.0
+    ref = torch.empty(T, d, dtype=torch.float64, device="cuda")
+    # a run of 64 tokens, every second one, the first half, the second half, all but one token
+    n_pg = ctx // P + 1
+    runs = [range(10, 14), [p for p in range(n_pg) if p // 4 % 2 == 0], range(n_pg // 2), range(n_pg // 2, n_pg), range(n_pg - 1)]
+    for b, run in enumerate(runs):
+        pages = bt[b, :n_pg].long()
+        kp[pages[torch.as_tensor(list(run), device="cuda")], ..., 0] = -1e20
+        K, V = (x[pages].transpose(1, 2).reshape(-1, h, dh)[:ctx + 1].double() for x in (kp, vp))
+        w = torch.softmax((K * qkv[b, :d].double().reshape(h, dh)).sum(-1) / dh ** 0.5, 0)
+        ref[b] = (w[..., None] * V).sum(0).reshape(d)
+    o = torch.empty(T, d, dtype=torch.bfloat16, device="cuda")
+    Bd.lsk_attn_paged(1, qkv, h, dh, torch.full((T,), ctx, dtype=torch.int32, device="cuda"),
+                      torch.arange(T, dtype=torch.int32, device="cuda"), kp, vp, bt, P, ctx + 1, o)
+    ref = ref.cpu().numpy()
+    assert_close(host(o), ref, 1e-5 + out_rounding_bound(ref, "bf16"), "o")
+
+
 @pytest.mark.parametrize("dh", [32, 64, 128])
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 64, 65, 130])
 def test_fp32_attention_over_batches_of_keys(dh, L):
