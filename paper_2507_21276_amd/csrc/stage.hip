@@ -629,7 +629,10 @@ ls_status serve_forward(ls_stage* s, const void* X, int T, int B, const ls_kv* k
   const ls_config& c = s->cfg;
   LS_TRY(lsk_convert(X, c.io_dtype, w.xa, LS_F32, (size_t)T * c.d_model, st));
   const bool gemv = decode_gemv_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
-  const bool rows = !gemv && decode_rows_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
+  // pools that are not 8-byte aligned go where they went without these kernels: a page write that takes any alignment, or
+  // one that refuses them
+  const bool rows = !gemv && (((uintptr_t)kv->k_pool | (uintptr_t)kv->v_pool) & 7) == 0 &&
+                    decode_rows_covers(c.mma_dtype, c.dtype, T, c.d_model, c.d_ff, c.head_dim);
   const bool fused = fused_decode_ok(s, T);
   bool h1_ready = false;
   for (int l = 0; l < c.n_layers; ++l) {

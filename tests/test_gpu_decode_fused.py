@@ -314,6 +314,40 @@ def test_decode_of_up_to_32_rows_on_a_small_stage(mma, rows, shape):
     st.close()
 
 
+@pytest.mark.parametrize("rows", [4, 5, 32, 33])
+@pytest.mark.parametrize("shape", ["gpt", "llama"])
+def test_decode_over_pools_of_any_alignment(rows, shape):
+    """Pools that begin four bytes behind an aligned address, around the rows at which the kernels change: the same results
+    as over aligned ones, within the stage's bar; widths that are multiples of 64 are refused from five rows on."""
+    over = dict(n_layers=2, d_model=96, n_heads=3, head_dim=32, d_ff=224)
+    cfg = S.scaled(S.CONFIGS["gpt2s_bf16" if shape == "gpt" else "llama7b_bf16"], **over)
+    old = [(0, 15, 16, 40)[b % 4] + b for b in range(rows)]
+
+    def decode(cfg, offset):
+        st, _, _ = make_stage(cfg, mma="f16", io="f32")
+        table, n_pages = S.page_tables(np.array(old), np.ones(rows, np.int64), cfg["page_size"])
+        kv = Bd.KV(st, n_pages, table, old)
+        for name in ("k_pool", "v_pool"):
+            pool = getattr(kv, name)
+            buf = torch.zeros(pool.numel() + offset, dtype=pool.dtype, device="cuda")
+            buf[offset:] = S.normal_torch(14, name, (pool.numel(),), 1.0, dtype=pool.dtype)
+            setattr(kv, name, buf[offset:].view(pool.shape))
+        X = dev(S.make_activations(cfg, "X", (rows, cfg["d_model"])), torch.float32)
+        Y = torch.empty_like(X)
+        try:
+            st.stage_decode(X, rows, kv, Y, st.new_workspace(rows))
+            return host(Y), host(kv.k_pool), host(kv.v_pool)
+        finally:
+            st.close()
+
+    for a, b, what in zip(decode(cfg, 2), decode(cfg, 0), ("Y", "K", "V")):
+        assert_close(a, b, TOL["bf16"], what)
+    if rows > 4:
+        with pytest.raises(Bd.LsError) as e:
+            decode(S.scaled(cfg, d_model=128, n_heads=4, d_ff=256), 2)
+        assert e.value.status == Bd.LS_EINVAL
+
+
 @pytest.mark.parametrize("mma", ["f16", "bf16"])
 @pytest.mark.parametrize("rows", [(129,), (48, 152), (100, 157)])
 def test_prompt_chunks_with_split_projections(mma, rows):
