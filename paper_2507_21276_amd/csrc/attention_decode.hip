@@ -230,30 +230,37 @@ int most_splits(long items, int max_ctx, int page) {
 
 struct Plan { int splits, chunk_pages, waves; };
 
-// Workgroups and wavefronts for `items` (row, head) pairs with contexts of at most max_ctx tokens.  A context stays in one
-// workgroup wherever the pairs fill the chip, with more wavefronts for longer ones: splitting it costs a second launch
-// and the partial results.  us, wavefronts / splits: 384 pairs of 512 tokens of 64 elements 8/1 13.2, 4/4 15.4; 1536 of
-// 1000 8/1 60.6, 4/1 63.9, 16/1 71.5; 2048 of up to 2048 tokens of 128 16/1 173, 8/1 177, 4/1 187, 4 in chunks of 512 188;
-// 4096 of 100 4/1 35.5, 8/1 41.5.  Few pairs with long contexts are split until there are 512 workgroups, each wavefront
-// with a group at least: 32 of 1537 8/12 10.9, 16/1 19.9; 64 of 700 8/4 9.4, 16/1 11.5; but 192 of 700 x 64 16/1 9.3, 8/2 11.9.
-// Contexts beyond 6144 tokens are cut into chunks of 4096, so that one long request of a batch is not the last
-// workgroup's for itself.
+// Workgroups and wavefronts for `items` (row, head) pairs with contexts of at most max_ctx tokens.  How far the others fall
+// short of the longest is not known here, so a rule has to hold for equal contexts and for one long one among short ones.
+// ng: groups of loads in the longest context.  us, splits / wavefronts: equal contexts | 64 tokens to the longest | one of the
+// longest and the others up to a sixteenth of it; 128 elements unless said:
+//   Fewer than 1024 pairs: contexts of few groups whole (64 pairs of 512 1/16 9.0 | 7.5 | 7.9, 2/8 10.3 | 9.9 | 10.2), longer
+//   ones split into about 2048 workgroups in all, which shares out the one long context as well (288 of 2048 1/16 64 | 29 |
+//   24, 8/8 50 | 28 | 17; 480 of 16384 1/16 603 | 363 | 170, 5/16 602 | 324 | 84; 512 of 4096 1/16 166 | 85 | 45, 4/8 163 |
+//   73 | 31), with more wavefronts for more groups (192 of 8192 in 11 or 12, 4: 125 | 47 | 35, 8: 126 | 44 | 33).
+//   From 1024 pairs on whole contexts, as a split costs a launch and the partial results, with more wavefronts for longer
+//   ones (1536 of 1000 x 64 elements 1/8 60.6, 1/4 63.9, 1/16 71.5; 2048 of 2048 1/16 326 | 163 | 33, 1/4 324 | 180 | 42), but
+//   four where the pairs are many and the longest context short: a short one leaves the others without a group (5120 of
+//   300 1/4 121 | 78 | 21, 1/8 120 | 74 | 34).
+//   Beyond 6144 tokens chunks, so that one long request is not the last workgroup's for itself: of 4096, or more where the
+//   scratch holds no more parts (1024 of 16384 whole 1271 | 668 | 177, chunks 1252 | 636 | 130), from 2048 pairs on of an eighth
+//   (2048 of 8192 chunks of 4096 1278 | 687 | 102, of 1024 1302 | 692 | 85).
 Plan plan(long items, int max_ctx, int page, int dh, bool may_split) {
   const int per_group = 2048 / dh;   // tokens
   const int ng = (max_ctx + per_group - 1) / per_group, most = may_split ? most_splits(items, max_ctx, page) : 1;
-  Plan p{1, 0, 4};
-  if (items < 512 && ng > 24) {
-    int ns = (int)(512 / items);
-    if (ns > ng / 8) ns = ng / 8;
-    if (ns > most) ns = most;
-    if (ns > 1) return Plan{ns, 0, 8};
-  } else if (items >= 512 && max_ctx > 6144) {
-    const int cp = 4096 / page > 0 ? 4096 / page : 1, ns = (max_ctx + cp * page - 1) / (cp * page);
-    if (ns <= most) return Plan{ns, cp, 16};
+  if (items < 1024) {
+    const int ns = most < ng / 8 ? most : ng / 8;   // a group for each wavefront
+    if (ns > 1 && ng > (items < 384 ? 32 : 64))
+      return Plan{ns, 0, ng / ns >= 128 ? 16 : ng / ns >= 32 || items * ns < 1024 ? 8 : 4};
+    if (items < 512) return Plan{1, 0, ng <= 8 ? 4 : items <= 256 ? 16 : 8};
+  } else if (max_ctx > 6144 && most > 1) {
+    const bool many = items >= 2048;
+    const int max_pages = (max_ctx + page - 1) / page, parts = many ? 8 : most, floor = (many ? 1024 : 4096) / page;
+    const int even = (max_pages + parts - 1) / parts, cp = even > floor ? even : floor;
+    return Plan{(max_pages + cp - 1) / cp, cp, many ? 8 : 16};
   }
-  if (items < 320) p.waves = ng <= 4 ? 4 : ng <= 8 ? 8 : 16;
-  else p.waves = ng <= 8 ? 4 : ng <= 64 ? 8 : 16;
-  return p;
+  if (ng <= 8 || (items >= 2048 && ng <= 24) || (items >= 4096 && ng <= 48)) return Plan{1, 0, 4};
+  return Plan{1, 0, ng <= 64 || (items > 2048 && ng <= 128) ? 8 : 16};
 }
 
 template <class T, int DH>

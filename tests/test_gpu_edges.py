@@ -215,12 +215,17 @@ def test_attention_backward_of_64_element_heads(name, B, L, h):
 
 @pytest.mark.parametrize("name,dh,P,h,ctx", [
     ("f16", 64, 16, 2, [0, 7, 15, 16, 31, 32, 33, 100]),              # groups of two pages; four wavefronts
-    ("bf16", 64, 8, 3, [255, 256, 257, 140]),                          # four pages a group; eight
+    ("bf16", 64, 8, 3, [255, 256, 257, 140]),                          # four pages a group; sixteen
     ("f16", 64, 24, 2, [95, 96, 97, 500, 1]),                          # three loads a page; sixteen
-    ("f16", 64, 64, 40, [63, 64, 200, 280, 5, 256, 17, 90]),           # half a page a group; 320 pairs
-    ("f16", 128, 16, 1, [1537, 40, 383]), ("bf16", 128, 64, 2, [1999, 64, 65]),   # split contexts
-    ("f16", 128, 8, 64, [130, 1, 127, 128, 129, 1100, 31, 12]),        # 512 pairs; sixteen wavefronts
-    ("f16", 128, 16, 128, [7000, 4095, 4096, 50])])                    # chunks of 4096 tokens
+    ("f16", 64, 64, 40, [63, 64, 200, 280, 5, 256, 17, 90]),           # half a page a group; 320 pairs: eight
+    ("f16", 128, 16, 1, [1537, 40, 383]), ("bf16", 128, 64, 2, [1999, 64, 65]),   # split contexts, eight wavefronts
+    ("f16", 128, 8, 64, [130, 1, 127, 128, 129, 1100, 31, 12]),        # 512 pairs in four parts; four
+    ("f16", 128, 16, 128, [7000, 4095, 4096, 50]),                     # 512 pairs in four parts; eight
+    ("f16", 128, 16, 128, [6200, 17, 4000, 90, 1, 333]),               # 768 pairs in three parts; sixteen
+    ("bf16", 128, 16, 128, [1100, 1, 16, 900, 64, 5, 1023, 300]),      # 1024 pairs, whole contexts; sixteen
+    ("f16", 128, 16, 128, [8193, 4095, 4096, 50, 8191, 1, 900, 64]),   # 1024 pairs, the chunks that the scratch holds
+    ("bf16", 128, 16, 256, [300, 1, 16, 170, 64, 5, 299, 33]),         # 2048 pairs, short contexts; four
+    ("f16", 64, 16, 256, [6200, 1023, 1024, 1025, 40, 2047, 2048, 12])])   # 2048 pairs in chunks of 1024 tokens
 def test_decode_attention_plans(name, dh, P, h, ctx):
     """Pages smaller and larger than a group of loads, contexts that end at each edge, every number of wavefronts, with and
     without splits; the slots beyond the contexts hold NaN.  Softmax weights in fp32 and 16-bit results: 1e-5 beside the
@@ -244,6 +249,26 @@ def test_decode_attention_plans(name, dh, P, h, ctx):
     Bd.lsk_attn_paged(1, qkv, h, dh, pos, torch.arange(T, dtype=torch.int32, device="cuda"), kp, vp, bt, P, max(ctx) + 1, o)
     ref = ref.cpu().numpy()
     assert_close(host(o), ref, 1e-5 + out_rounding_bound(ref, name), "o")
+
+
+@pytest.mark.parametrize("rows,h,n,parts", [
+    (2, 32, 512, 1), (9, 32, 512, 1), (9, 32, 2048, 8), (12, 32, 4096, 6), (15, 32, 16384, 5), (31, 33, 1024, 1), (31, 33, 1040, 3),
+    (32, 32, 6144, 1), (32, 32, 16384, 2), (64, 32, 6144, 1), (64, 32, 8192, 8), (64, 32, 9000, 8)])
+def test_decode_attention_parts_of_long_contexts(rows, h, n, parts):
+    """How many parts contexts of n tokens are cut into, and that no more of the scratch is written than was asked for.  The
+    requests share their pages."""
+    dh, P = 128, 16
+    pool = torch.zeros(64, h, P, dh, dtype=torch.float16, device="cuda")
+    bt = (torch.arange(rows * -(-n // P), device="cuda") % 64).to(torch.int32).view(rows, -1)
+    qkv, o = torch.zeros(rows, 3 * h * dh, dtype=torch.float16, device="cuda"), torch.empty(rows, h * dh, dtype=torch.float16, device="cuda")
+    pos, req = torch.full((rows,), n - 1, dtype=torch.int32, device="cuda"), torch.arange(rows, dtype=torch.int32, device="cuda")
+    size = Bd.lib().lsk_attn_paged_scratch_floats(rows, h, dh, n, P)
+    scratch = torch.full((size + 4096,), float("nan"), device="cuda")
+    Bd._check(Bd.lib().lsk_attn_paged(1, qkv.data_ptr(), Bd.LS_F16, rows, h, dh, pos.data_ptr(), req.data_ptr(), pool.data_ptr(),
+                                      pool.data_ptr(), bt.data_ptr(), bt.shape[1], P, n, o.data_ptr(), scratch.data_ptr(), None))
+    written = int(scratch.isfinite().sum())
+    assert written == (rows * h * parts * (dh + 2) if parts > 1 else 0)
+    assert scratch[size:].isnan().all() and (o == 0).all()
 
 
 @pytest.mark.parametrize("dh,h,ctx", [(64, 1, 511), (64, 40, 300), (128, 1, 1100), (128, 64, 700)])
