@@ -250,10 +250,12 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(KvView kv, int L, con
     acc *= alpha;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const float p = j0 + u * TPL + tg < nkeys ? expf(s[u] - ref) : 0.f;
+      const bool in = j0 + u * TPL + tg < nkeys;
+      const float p = in ? expf(s[u] - ref) : 0.f;
       l += p;
+      // what stands in for a token past the end may be infinite: 0 times it must not reach the sum
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, vx[u][e], acc[e]);
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, in ? vx[u][e] : 0.f, acc[e]);
     }
     m = m_new;
   }
@@ -331,8 +333,8 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float* qkv, con
         const float p = in ? expf(s * scale - ls[u]) : 0.f, ds = in ? p * (dp - dv) : 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          a[e] = fmaf(ds, qx[u][e], a[e]);
-          b[e] = fmaf(p, gx[u][e], b[e]);
+          a[e] = fmaf(ds, in ? qx[u][e] : 0.f, a[e]);
+          b[e] = fmaf(p, in ? gx[u][e] : 0.f, b[e]);
         }
       }
     }

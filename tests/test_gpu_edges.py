@@ -356,6 +356,48 @@ def test_fp32_attention_where_scores_overflow(dh, dead):
     assert_close(host(o)[rows], ref[rows], 1e-5, "o over pages")
 
 
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("at", [0, 15, 16, 77])
+def test_fp32_attention_where_the_last_row_is_infinite(dh, at):
+    """An infinite element in a row of V is infinite in every output that sees the row, and one in a row of dO in dV of every
+    key that the row sees: no NaN, and nothing else changes.  Contiguous and paged keys.  Bar: that of the attention over
+    batches of keys."""
+    L, h, P = at + 1, 2, 16
+    d, inf = h * dh, float("inf")
+    n = L + 5   # rows behind the infinite one, forward
+    qkv = torch.from_numpy(S.normal(16, "qkv", (n, 3 * d)).astype(np.float32)).cuda()
+    x = qkv.view(n, 3, h, dh)
+    o, lse, plain = torch.empty(n, d, device="cuda"), torch.empty(n, h, device="cuda"), torch.empty(n, d, device="cuda")
+    Bd.lsk_attn_fwd(0, qkv, 1, n, h, dh, plain, lse)
+    v = x[at, 2, 1, 3].item()
+    x[at, 2, 1, 3] = inf
+
+    def check(got, ref, rows, what):
+        assert (got[rows, dh + 3] == inf).all(), what
+        got[rows, dh + 3] = ref[rows, dh + 3]
+        assert_close(host(got), host(ref), 1e-5, what)
+
+    Bd.lsk_attn_fwd(0, qkv, 1, n, h, dh, o, lse)
+    check(o, plain, slice(at, n), "o")
+    table, n_pages = S.page_tables(np.array([n]), np.ones(1, np.int64), P, seed=2)
+    bt = torch.as_tensor(table, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.zeros(n_pages, h, P, dh, device="cuda") for _ in range(2))
+    for j in range(n):
+        kp[table[0, j // P], :, j % P], vp[table[0, j // P], :, j % P] = x[j, 1], x[j, 2]
+    o.zero_()
+    Bd.lsk_attn_paged(0, qkv, h, dh, torch.arange(n, dtype=torch.int32, device="cuda"),
+                      torch.zeros(n, dtype=torch.int32, device="cuda"), kp, vp, bt, P, n, o)
+    check(o, plain, slice(at, n), "o over pages")
+    x[at, 2, 1, 3] = v
+    part = qkv[:L].contiguous()
+    dO = torch.from_numpy(S.normal(16, "dO", (L, d)).astype(np.float32)).cuda()
+    ref, got = torch.empty_like(part), torch.empty_like(part)
+    Bd.lsk_attn_bwd(0, part, plain[:L].contiguous(), dO, lse[:L].contiguous(), 1, L, h, dh, ref)
+    dO[at, dh + 3] = inf
+    Bd.lsk_attn_bwd(0, part, plain[:L].contiguous(), dO, lse[:L].contiguous(), 1, L, h, dh, got)
+    check(got[:, 2 * d:], ref[:, 2 * d:], slice(0, L), "dV")
+
+
 @pytest.mark.parametrize("name", ["bf16", "f16"])
 @pytest.mark.parametrize("kind", [Bd.LS_ACT_GELU_TANH, Bd.LS_ACT_GELU_ERF])
 @pytest.mark.parametrize("n", [8, 1000, 1003])
