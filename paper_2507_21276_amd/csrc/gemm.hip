@@ -338,14 +338,15 @@ extern "C" ls_status lsk_gemm_scaled(int op_dtype, int M, int N, int K, const vo
   if (op_dtype == LS_F32) {
     LS_REQUIRE(c_dtype == LS_F32, "gemm: fp32 operands need an fp32 output");
     // 64 x 64 tiles where they give every compute unit one; fewer go to the matrix instruction (gemm_f32.hip), except for
-    // short contractions over many results, which are bound by their stores (960 x 1024 over 16 5.6 us here, 6.0 there;
-    // over 48 7.7 and 8.2; over 80 11.1 and 8.8).  64 x 64 tiles take k tiles of 16: workgroups that share a unit hide each
-    // other's loads, and the padding of a short contraction is less (k tiles of 32 -> 16: 6144 x 2048 over 16 30.8 -> 23.6
-    // us, over 80 57 -> 47, 4096 x 2048 over 1024 358 -> 350)
+    // short contractions over many results, which are bound by their stores: up to 48, and up to 64 (one k tile here) where
+    // the tiles nearly fill the chip and A is k-major (us here, there: 960 x 1024 over 16 5.6, 6.0; over 48 7.7, 8.2; over 64
+    // 8.3, 10.6, B k-strided 8.3, 9.3, both 8.3, 7.6; over 80 11.1, 8.8; 768 x 768 over 64 7.1, 7.0).  64 x 64 tiles take k
+    // tiles of 16: workgroups that share a unit hide each other's loads, and the padding of a short contraction is less (k
+    // tiles of 32 -> 16: 6144 x 2048 over 16 30.8 -> 23.6 us, over 80 57 -> 47, 4096 x 2048 over 1024 358 -> 350)
     const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
     if (tiles >= 256) {
       gemm_f32_kernel<64, 16><<<dim3(tiles), dim3(256), 0, st>>>(g);
-    } else if (tiles > 64 && K <= 48) {
+    } else if (tiles > 64 && K <= (tiles > 200 && a_kmajor ? 64 : 48)) {
       gemm_f32_kernel<32, 64><<<dim3(((M + 31) / 32) * ((N + 31) / 32)), dim3(256), 0, st>>>(g);
     } else {
       return gemm_f32_few_tiles(M, N, K, A, lda, a_kmajor, B, ldb, b_kmajor, C, ldc, bias, bias_dtype, resid, ldr,

@@ -105,6 +105,13 @@ def test_fp32_products_of_few_tiles(M, N, K, offset):
             assert_close(host(out), ref, max(2e-6, K * 2.0 ** -24), f"{M}x{N}x{K} {ak} {bk}")
 
 
+@pytest.mark.parametrize("M,N", [(640, 1280), (800, 1000), (1000, 900)])   # 200, 208 and 240 tiles of 64 x 64
+@pytest.mark.parametrize("K", [64, 65])
+def test_fp32_products_of_short_contractions(M, N, K):
+    """Both sides of the line between the kernels at contractions of one and two k tiles.  Bar and inputs as above."""
+    test_fp32_products_of_few_tiles(M, N, K, 0)
+
+
 @pytest.mark.parametrize("kind", [0, 1])
 @pytest.mark.parametrize("T,d", [(1, 8), (9, 520), (1280, 512), (1281, 1024), (2049, 1032)])
 @pytest.mark.parametrize("name,pname", [("f16", "f16"), ("bf16", "f32"), ("f32", "bf16")])
