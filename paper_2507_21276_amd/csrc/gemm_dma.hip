@@ -609,19 +609,35 @@ ls_status gemm_dma16_partials(int, int, int, int, const void*, long, const void*
 
 namespace {
 // Parts in which 128 x 256 tiles (three LDS buffers, one workgroup a compute unit) take a product of up to 256 rows, or 0
-// where they leave too much of the chip without one.  A workgroup has twice the weights in flight of two that share a unit
-// with two buffers each, and fewer parts are to be written and summed.  More workgroups than about 200 gain nothing while a
-// part is short.  us (parts), weights from HBM, smaller tiles -> these: 128 rows, 12288 columns over 4096 29.4 (5) -> 26.9 (4),
-// 22016 over 4096 55.3 (2) -> 50.6 (2), 27648 over 5120 77.0 (2) -> 67.8 (2), 5120 over 13824 38.5 (12) -> 34.5 (10); 64
-// rows, 12288 over 4096 26.8 (8) -> 24.9 (4); 248 rows, 4096 over 4096 25.0 (8) -> 20.0 (6), 4096 over 11008 42.7 (8) -> 39.3 (8),
-// 5120 over 13824 59.2 (6) -> 54.9 (6).  Where half of the chip has no workgroup it is the other way round: 64 rows, 22016 over
-// 4096 41.1 (4), 47.4 (2).
-int parts_of_128x256(int M, int N, int nk) {
+// where the smaller tiles in `parts` parts are the better way.  A workgroup has twice the weights in flight of two that share
+// a unit with two buffers each, and fewer parts are to be written and summed.  More workgroups than about 200 gain nothing
+// while a part is short.  us with the sum (parts), weights from HBM, smaller tiles -> these: 128 rows, 12288 columns over
+// 4096 35.6 (5) -> 32.0 (4), 22016 over 4096 59.7 (2) -> 55.8 (2); 64 rows, 12288 over 4096 32.3 (8) -> 28.6 (4); 256 rows,
+// 4096 over 4096 30.0 (8) -> 28.0 (6).
+// Where half of the chip has no workgroup it is the other way round (64 rows, 22016 over 4096 without the sum 41.1 (4), 47.4
+// (2)), and also:
+//   up to 64 rows, where half of a tile is empty, unless a fifth of the parts is saved (4096 over 11008 29.0 (16), 29.8 (13)),
+//     and with more than 216 workgroups of long parts (28672 over 4096 55.1 (3), 62.2 (2); 8192 over 32768 122 (12), 136 (8); but
+//     20480 over 5120 53.2 (4) -> 47.5 (3)); at 48 rows with more than 240 of any (16384 over 3072 29.2 (6), 30.6 (4));
+//   up to 128 rows, where no part is saved that matters: sixteen are the most of either (96 rows, 3072 over 8192 22.6, 23.3), and
+//     parts of less than eight k tiles gain nothing when there are as many (128 rows, 7680 over 2560 24.7, 23.8, but in cached
+//     weights 21.3, 22.0);
+//   beyond, where parts are short or the chip is full (130 rows, 8192 over 2048 22.9 (4), 26.7 (4), 10240 over 2560 27.7 (3), 32.4
+//     (3), 8192 over 22016 125 (4), 141 (4); 200 rows, 6144 over 2048 22.2 (4), 23.2 (4)); but a full chip is the better one
+//     with many parts and nearly all rows of the second tile (248 rows, 5120 over 13824 66.2 (6) -> 60.3 (6), 4096 over 11008 48.6
+//     (8) -> 47.4 (8); 200 rows 43.5 (8), 44.9 (8); 248 rows, 8192 over 22016 148 (4), 154 (4)).
+int parts_of_128x256(int M, int N, int nk, int parts) {
   const int tiles = (M + 127) / 128 * ((N + 255) / 256);
   int s = 256 / tiles < 16 ? 256 / tiles : 16;
   while (s > 4 && s * tiles > 208 && nk / s < 16) --s;
   while (s > 1 && nk / s < 6) --s;
-  return s * tiles >= (M <= 64 ? 190 : 160) ? s : 0;
+  const int wgs = s * tiles, per = s > 0 ? nk / s : 0;
+  if (wgs < (M <= 64 ? 190 : 160) || s > parts) return 0;
+  bool better;
+  if (M <= 64) better = 10 * s <= 8 * parts && (wgs <= 216 || (per < 32 && wgs <= (M < 56 ? 240 : 256)));
+  else if (M <= 128) better = s < parts || (s < 16 && per >= 8);
+  else better = wgs <= 216 ? per >= 10 : M > 224 && s >= 6;
+  return better ? s : 0;
 }
 }  // namespace
 
@@ -661,8 +677,8 @@ ls_status gemm_dma_splitk_partials(int op_dtype, int M, int N, int K, const void
   while (splits > 1 && (size_t)splits * M * N > scratch_floats) --splits;
   if (splits < 2) return LS_ESTATE;
   LsTimed timed(kind, st);
-  const int fewer = M <= 256 ? parts_of_128x256(M, N, nk) : 0;
-  if (fewer >= 2 && fewer <= splits) {
+  const int fewer = M <= 256 ? parts_of_128x256(M, N, nk, splits) : 0;
+  if (fewer >= 2) {
     LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, fewer, 128, st));
     *splits_out = fewer;
     return LS_OK;
@@ -957,10 +973,9 @@ ls_status gemm_dma_skinny_partials(int op_dtype, int M, int N, int K, const void
   while (splits > 1 && nk / splits < 6) --splits;
   while (splits > 1 && (size_t)splits * M * N > scratch_floats) --splits;
   if ((size_t)splits * M * N > scratch_floats) return LS_ESTATE;
-  // (fewer rows than 48 would be a small part of such a tile: 16 rows of 12288 columns over 4096 22.7 us, 23.9; up to 64
-  // rows the parts saved have to pay for half of it: 64 rows of 4096 columns over 11008 24.3 us (16), 25.2 (13))
-  const int fewer = M >= 48 && N >= 256 ? parts_of_128x256(M, N, nk) : 0;
-  if (fewer > 0 && (M > 64 ? fewer <= splits : 10 * fewer <= 8 * splits)) {
+  // (fewer rows than 48 would be a small part of such a tile: 16 rows of 12288 columns over 4096 22.7 us, 23.9)
+  const int fewer = M >= 48 && N >= 256 ? parts_of_128x256(M, N, nk, splits) : 0;
+  if (fewer > 0) {
     LS_TRY(gemm_dma16_partials(op_dtype, M, N, K, A, lda, B, ldb, scratch, fewer, 128, st));
     *splits_out = fewer;
     return LS_OK;

@@ -69,6 +69,17 @@ def test_partials_from_tiles_of_256_columns(name, M, N, K, parts):
     assert_close(host(got), host(ref), 1e-5, "sum of partials")
 
 
+@pytest.mark.parametrize("M,N,K,parts", [(48, 16384, 3072, 6), (56, 16384, 3072, 4), (64, 28672, 4096, 3), (64, 20480, 5120, 3),
+                                         (96, 8192, 2048, 5)])
+def test_parts_where_tiles_of_256_columns_are_the_slower_ones(M, N, K, parts):
+    """Full chips of half-empty tiles with short and with long parts, and parts of six k tiles: how many parts, and their sum."""
+    x, w, part, splits = partials_of("f16", M, N, K, 43)
+    assert splits == parts
+    got = part[:splits * M * N].view(splits, M, N).double().sum(0)
+    ref = x.double() @ w.double().T.contiguous()
+    assert_close(host(got), host(ref), 1e-5, "sum of partials")
+
+
 @pytest.mark.parametrize("splits", range(1, 19))
 def test_parts_are_summed_in_ascending_order(splits):
     """Every count of a group of eight parts and its rest: bit-equal to the parts added one after the other in fp32."""
