@@ -479,8 +479,13 @@ __global__ void rope_kv_vec_kernel(TH* qkv, int T, int h, int dh, const int32_t*
   }
 }
 
-ls_status set_lds(const void* fn, size_t bytes) {
+// The longest context that the entry points take: one whose scores the kernels of any type and head_dim hold in LDS
+ls_status context_fits(size_t bytes) {
   LS_REQUIRE(bytes <= 160 * 1024, "attention: context too long for the plain kernel (%zu bytes of LDS)", bytes);
+  return LS_OK;
+}
+ls_status set_lds(const void* fn, size_t bytes) {
+  LS_TRY(context_fits(bytes));
   if (bytes > 48 * 1024)
     LS_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
   return LS_OK;
@@ -496,10 +501,11 @@ ls_status lsk_attn_fwd_simple(const void* qkv, int dt, int B, int L, int h, int 
   KvView kv{qkv, nullptr, nullptr, nullptr, 0, dt, h, dh, h * dh, 0, 1};
   const int T = B * L;
   const size_t lds = 4 * (size_t)(L + dh) * sizeof(float);
-  LS_TRY(set_lds((const void*)attn_fwd_simple_kernel, lds));
+  LS_TRY(context_fits(lds));
   const long items = (long)T * h;
   if (f32_covers(dt, dh, items, {qkv}))
     return launch_fwd_f32<false>(kv, T, L, nullptr, nullptr, (float*)o, lse, (hipStream_t)stream);
+  LS_TRY(set_lds((const void*)attn_fwd_simple_kernel, lds));
   attn_fwd_simple_kernel<<<(unsigned)((items + 3) / 4), 256, lds, (hipStream_t)stream>>>(
       kv, T, L, nullptr, nullptr, L, o, lse);
   LS_CHECK_LAUNCH();
@@ -514,8 +520,7 @@ ls_status lsk_attn_bwd_simple(const void* qkv, const void* o, const void* dO, co
   const long items = (long)T * h;
   hipStream_t st = (hipStream_t)stream;
   if (f32_covers(dt, dh, items, {qkv, o, dO})) {
-    const size_t bytes = 4 * (size_t)(2 * L + 2 * dh) * sizeof(float);   // the limit of the kernels below
-    LS_REQUIRE(bytes <= 160 * 1024, "attention: context too long for the plain kernel (%zu bytes of LDS)", bytes);
+    LS_TRY(context_fits(4 * (size_t)(2 * L + 2 * dh) * sizeof(float)));
     const dim3 grid((unsigned)items, 2);
     if (dh == 32) attn_bwd_f32_kernel<32><<<grid, 256, 0, st>>>((const float*)qkv, (const float*)o, (const float*)dO, lse, L, h, (float*)dqkv);
     else if (dh == 64) attn_bwd_f32_kernel<64><<<grid, 256, 0, st>>>((const float*)qkv, (const float*)o, (const float*)dO, lse, L, h, (float*)dqkv);
@@ -587,10 +592,11 @@ ls_status lsk_attn_paged_simple(const void* qkv, int dt, int T, int h, int dh, c
              "attn_paged: bad argument");
   KvView kv{qkv, k_pool, v_pool, block_table, 1, dt, h, dh, h * dh, max_pages, page};
   const size_t lds = 4 * (size_t)(max_ctx + dh) * sizeof(float);
-  LS_TRY(set_lds((const void*)attn_fwd_simple_kernel, lds));
+  LS_TRY(context_fits(lds));
   const long items = (long)T * h;
   if (f32_covers(dt, dh, items, {qkv, k_pool, v_pool}))
     return launch_fwd_f32<true>(kv, T, 0, pos, req, (float*)o, nullptr, (hipStream_t)stream);
+  LS_TRY(set_lds((const void*)attn_fwd_simple_kernel, lds));
   attn_fwd_simple_kernel<<<(unsigned)((items + 3) / 4), 256, lds, (hipStream_t)stream>>>(
       kv, T, 0, pos, req, max_ctx, o, nullptr);
   LS_CHECK_LAUNCH();
