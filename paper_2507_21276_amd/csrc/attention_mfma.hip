@@ -1190,8 +1190,9 @@ __device__ __forceinline__ void bwd_dkv(const T* __restrict__ qkv, const T* __re
 
 // Both in one launch, head_dim 64: dK/dV in the even rows of the grid and dQ in the odd ones (grid.y is dispatched slowest,
 // and both begin with their longest workgroups).  They do not depend on each other, and a short sequence leaves either alone
-// a fraction of the chip.  Two workgroups share a compute unit: dK/dV with 32 rows a wavefront and a whole tile needs 262
-// registers, which left it one.  Two launches of four wavefronts -> here, with dvec_kernel, us: 12 heads, 128 tokens 21.9 ->
+// a fraction of the chip.  Eight wavefronts take 187 registers: two wavefronts a SIMD, one workgroup a compute unit.  Two
+// workgroups of four share a unit, for which dK/dV with 32 rows a wavefront and a whole tile (262 registers) keeps 16 of its
+// registers in scratch.  Two launches of four wavefronts -> here, with dvec_kernel, us: 12 heads, 128 tokens 21.9 ->
 // 14.3; 3 x 333 36.9 -> 22.9; 2048 124 -> 58; 4 x 1024 77.6 -> 61.7; 4096 232 -> 158.
 template <class T, int DH, int HV>
 __global__ __launch_bounds__(256 * HV, 2) void flash_bwd_kernel(const T* __restrict__ qkv, const T* __restrict__ dO,

@@ -185,7 +185,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(const void* qk
 // scores and the weighted sums (the kernels above read a row of K four bytes a lane, one lane per key, and walk the
 // keys one after the other for the sums: a chain of up to 2 L load latencies).  Parts are merged in the order of the
 // wavefronts: deterministic.  2 x 64 tokens, 4 heads of 32: forward 26.8 -> 4.0 us, backward 45.2 + a launch for
-// rowsum(dO * O) -> 4.6.
+// rowsum(dO * O) -> 4.6; 2048 tokens, 12 heads of 64: 4508 -> 485, 29992 -> 1490; 64 requests of 4000 over pages, 16 heads of 128:
+// 6002 -> 701.
 template <int DH> struct F32Lanes {
   static constexpr int LPT = DH / 4, TPL = 64 / LPT, UN = 16 / TPL;   // lanes per token, tokens per load, loads per batch
   static __device__ __forceinline__ float dot(f32x4 a, f32x4 b) {

@@ -3,11 +3,12 @@
 //
 // The weights of such a projection (1 - 5 MB) are a microsecond of HBM traffic; what a block takes is the number of its
 // launches and of the round trips in each.  So nothing is split across workgroups: a workgroup owns 16 weight rows, its
-// eight wavefronts share the contraction (all loads of a wavefront's share in flight at once, straight into the
-// fragments), and their partial results are summed in LDS, in the order of the wavefronts.  A workgroup that needs the
-// normalised rows normalises them for itself, into LDS, while its weights are on their way.  Five launches a block in
-// place of nine: QKV (norm, bias, rotary embedding, page write), attention, output projection (bias, residual), FFN-up
-// (norm, bias, activation), FFN-down (bias, residual).
+// eight wavefronts share the contraction (straight into the fragments, up to 256 elements of a wavefront's share in flight at
+// once: all of it up to a contraction of 2048), and their partial results are summed in LDS, in the order of the
+// wavefronts.  A workgroup that needs the normalised rows normalises them for itself, into LDS, while its weights are on
+// their way.  Five launches a block in place of nine: QKV (norm, bias, rotary embedding, page write), attention, output
+// projection (bias, residual), FFN-up (norm, bias, activation), FFN-down (bias, residual).  Six where a call of 17 rows or
+// more leaves FFN-down to the split products and their sum (block_forward_few).
 //
 // The 16 weight rows are two runs of eight: a rotary pair's halves, gate and up columns of the same units, or 16 in a row.
 // Six blocks of d 768, nine launches a block -> these: 5 rows 262 -> 203 us, 16 rows 278 -> 219, 32 rows 289 -> 260.
@@ -285,7 +286,8 @@ bool norm_ok(int K, const float* x, const void* gamma, const void* beta) {
 
 // Whether the kernels below cover a block's projections and are the better ones for it: while a workgroup's rows are few
 // (QKV of d 768: 5.6 us at 5 rows, 8.0 at 32, 14.9 at 64 against 5.7 + 3.6 for a split product and its sum) and the weights
-// few enough to be latency
+// few enough to be latency.  Four blocks over short contexts, nine launches a block -> these, us at 5 and 32 rows: d 256 143 ->
+// 81, 149 -> 114; d 512 161 -> 98, 165 -> 124; d 1024 172 -> 125, 181 -> 157; gated, d 1024 over 4096 166 -> 127, 176 -> 175.
 bool decode_rows_covers(int dt, int param_dtype, int T, int d, int F, int dh) {
   return (dt == LS_BF16 || dt == LS_F16) && param_dtype == LS_BF16 && T >= 1 && T <= 32 && d % 32 == 0 && d <= MAX_D &&
          F % 32 == 0 && F <= 4 * MAX_D && dh % 16 == 0;

@@ -1033,7 +1033,7 @@ ls_status gemm_dma_try(int op_dtype, int M, int N, int K, const void* A, long ld
   const int per16 = c_dtype == LS_F32 ? 4 : 8;
   if (N % per16 != 0 || ldc % per16 != 0 || (uintptr_t)C % 16 != 0) return LS_ESTATE;
   if (resid && (ldr % 4 != 0 || (uintptr_t)resid % 16 != 0)) return LS_ESTATE;
-  // problems with enough 256 x 256 tiles run the 16x16x32 kernel
+  // problems with enough tiles of 128 to 256 rows by 256 run the 16x16x32 kernel (rows_per_tile)
   const ls_status r16 = gemm_dma16_try(op_dtype, M, N, K, A, lda, a_kmajor, B, ldb, b_kmajor, C, ldc, c_dtype, bias,
                                        bias_dtype, resid, ldr, accumulate, alpha, rope_pos, rope_table, rope_cols, st);
   if (r16 != LS_ESTATE) return r16;

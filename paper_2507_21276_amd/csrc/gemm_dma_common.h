@@ -30,7 +30,7 @@ struct DmaArgs {
 
 constexpr int TK = 64;  // k extent of a tile; a tile of ROWS rows is ROWS * 128 bytes = ROWS / 8 wave loads
 
-// Direct-to-LDS loads of one operand tile of ROWS rows (256 or 128): ROWS / 32
+// Direct-to-LDS loads of one operand tile of ROWS rows (64, 128, 192 or 256; 192 of a k-major operand only): ROWS / 32
 // wave loads per wavefront.  The per-lane byte offsets inside the tile are fixed
 // for the whole k loop (`off`, computed once); only the uniform tile base moves.
 // K8: the chunk index of a k-strided tile is also XOR-permuted with 2 * ((k >> 3) & 1) (the 16x16x32 kernel,

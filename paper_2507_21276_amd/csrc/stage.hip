@@ -322,8 +322,9 @@ size_t carve_fwd(const ls_stage* s, void* base, int T, FwdWs* w) {
 }
 
 // Whether the column sums of all norms of a backward pass are kept and finished by one launch (in place of one of 3 - 5 us
-// each: six blocks of d 768, 2 x 3 x 333 tokens 2684 -> 2615 us) or each at once: 64 MB of them are 8192 rows of those blocks, and more
-// rows than that are worth the launches.
+// each: six blocks of d 768, 2 x 3 x 333 tokens 2684 -> 2615 us) or each at once: up to 64 MB of them, which
+// six blocks of d 768 reach at 14,000 rows and twelve at 7,100: beyond, the launches are less than a
+// hundredth of the pass.
 constexpr size_t kNormSumsBytes = (size_t)64 << 20;
 bool norm_sums_together(size_t floats, int n_layers) { return floats * 4 * 2 * (size_t)n_layers <= kNormSumsBytes; }
 
@@ -446,8 +447,8 @@ ls_status block_forward(const ls_stage* s, int l, int T, const FwdBufs& f, const
   if (h1_ready) *h1_ready = false;
   // training: rotary embedding in the projection's epilogue where the tile shape allows, else by the rotary
   // kernel.  Serving: in the epilogue only where it is fused there; otherwise the kernel that writes K and V
-  // to the pages rotates q and k in the same pass (a prompt chunk of 512 rows has too few tiles for the fused
-  // epilogue, and a rotary kernel of its own before the page write cost 13 us per block).
+  // to the pages rotates q and k in the same pass (where the projection has too few tiles for the fused epilogue, a
+  // rotary kernel of its own before the page write cost 13 us per block of d 4096 and 512 rows).
   const bool roped = !gpt && mt != LS_F32 && (!kv || gemm_qkv_rope_fuses(mt, T, d, c.head_dim, true));
   // Serving calls whose projection is split over k: one kernel sums the parts, rotates q and k and writes the pages (in
   // place of a reduce kernel and the rotary / page kernel).  LS_ESTATE from the split-K launcher means "this shape is
